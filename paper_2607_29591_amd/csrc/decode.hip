@@ -53,6 +53,10 @@ constexpr int kWaves = 4;
 constexpr int kUnit = 64;              // slots per wave unit
 constexpr int kTiles = kUnit / 16;     // 16-slot MFMA tiles per unit
 constexpr int kChunk = kWaves * kUnit; // slots per split block
+// split records per head from which the combine deals a head's outputs to
+// several blocks (calls without an append): one block pulls 256 outputs'
+// worth of every record through one CU
+constexpr int kSliceRecords = 32;
 constexpr int kWholeHeadMin = 256;     // (b, kv head) pairs that fill the 256 CUs
 
 struct DecodeArgs {
@@ -414,8 +418,14 @@ __global__ __launch_bounds__(kThreads) void decode_split(DecodeArgs a) {
 // the cache lengths are issued before those arrive: the (max, sum) of the
 // first 16 kML records of this thread's query head and the accumulators of
 // the first kPF records of its outputs. Records of chunks without slots hold
-// stale values; they are masked once the lengths are known.
-template <int D, int GP>
+// stale values; they are masked once the lengths are known. Further records'
+// accumulators are requested kPF at a time: bound by load latency, one record
+// at a time they cost a memory round trip each (129 records of 16 query heads,
+// 16 heads: 181 us a launch before, about 17 us batched and sliced).
+// kSliced: the outputs are dealt to gridDim.z blocks (256 each in turn), every
+// block forming all weights; only for calls without an append, since main_len
+// may advance only after every block has read it.
+template <int D, int GP, bool kSliced>
 __global__ __launch_bounds__(kThreads) void decode_combine(DecodeArgs a) {
   extern __shared__ float s_w[];  // [GP][P] weights of the records
   const int kvh = blockIdx.x, b = blockIdx.y;
@@ -424,8 +434,9 @@ __global__ __launch_bounds__(kThreads) void decode_combine(DecodeArgs a) {
   const float2* ml = reinterpret_cast<const float2*>(a.part_ml) + (size_t)bh * a.P * GP;
   const float* pacc = a.part_acc + (size_t)bh * a.P * GP * D;
   constexpr int kML = 4;
-  constexpr int kOut = (GP * D + kThreads - 1) / kThreads;
+  constexpr int kOut = kSliced ? 1 : (GP * D + kThreads - 1) / kThreads;
   constexpr int kPF = kOut >= 8 ? 8 : 16;
+  const int tid0 = kSliced ? (int)blockIdx.z * kThreads + tid : tid;  // this thread's first output
   const bool hv = h < a.G;
   float2 mlv[kML];
 #pragma unroll
@@ -436,7 +447,7 @@ __global__ __launch_bounds__(kThreads) void decode_combine(DecodeArgs a) {
   float pv[kOut][kPF];
 #pragma unroll
   for (int k = 0; k < kOut; ++k) {
-    const int idx = min(tid + k * kThreads, a.G * D - 1), hh = idx / D, d = idx % D;
+    const int idx = min(tid0 + k * kThreads, a.G * D - 1), hh = idx / D, d = idx % D;
 #pragma unroll
     for (int j = 0; j < kPF; ++j) pv[k][j] = j < a.P ? pacc[(j * GP + hh) * D + d] : 0.f;
   }
@@ -487,7 +498,7 @@ __global__ __launch_bounds__(kThreads) void decode_combine(DecodeArgs a) {
       }
       s_w[h * a.P + p] = w;
     }
-    if (lane16 == 0) {
+    if (lane16 == 0 && (!kSliced || blockIdx.z == 0)) {
       if (a.dbg_lse_main) a.dbg_lse_main[qh] = lM > 0.f ? (mM + log2f(lM)) * kLn2 : kNegInf;
       if (a.dbg_lse_res) a.dbg_lse_res[qh] = lR > 0.f ? (mR + log2f(lR)) * kLn2 : kNegInf;
       if (a.dbg_gate) a.dbg_gate[qh] = g;
@@ -496,7 +507,7 @@ __global__ __launch_bounds__(kThreads) void decode_combine(DecodeArgs a) {
   __syncthreads();
 #pragma unroll
   for (int k = 0; k < kOut; ++k) {
-    const int idx = tid + k * kThreads;
+    const int idx = tid0 + k * kThreads;
     if (idx >= a.G * D) continue;
     const int hh = idx / D, d = idx % D;
     const float* w = s_w + hh * a.P;
@@ -504,8 +515,14 @@ __global__ __launch_bounds__(kThreads) void decode_combine(DecodeArgs a) {
 #pragma unroll
     for (int j = 0; j < kPF; ++j)
       if (j < a.P && valid(j)) o = fmaf(w[j], pv[k][j], o);
-    for (int j = kPF; j < a.P; ++j)
-      if (valid(j)) o = fmaf(w[j], pacc[(j * GP + hh) * D + d], o);
+    for (int j0 = kPF; j0 < a.P; j0 += kPF) {  // further records, kPF requests in flight
+      float v[kPF];
+#pragma unroll
+      for (int j = 0; j < kPF; ++j) v[j] = j0 + j < a.P ? pacc[((j0 + j) * GP + hh) * D + d] : 0.f;
+#pragma unroll
+      for (int j = 0; j < kPF; ++j)
+        if (j0 + j < a.P && valid(j0 + j)) o = fmaf(w[j0 + j], v[j], o);
+    }
     a.out[((size_t)b * a.Hq + kvh * a.G + hh) * D + d] = o;
   }
   // the appended token is in the cache: advance main_len (one block per
@@ -1216,8 +1233,11 @@ hipError_t launch_typed(const DecodePlan& pl, const DecodeArgs& da, hipStream_t 
   const size_t lds = (size_t)GP * pl.P * sizeof(float);
   if (da.out_res)
     hipLaunchKernelGGL((decode_branches<D, GP>), dim3(pl.Hkv, pl.B), dim3(kThreads), lds, stream, da);
+  else if (pl.P >= kSliceRecords && GP * D > kThreads && !da.k_new)
+    hipLaunchKernelGGL((decode_combine<D, GP, true>), dim3(pl.Hkv, pl.B, (pl.G * D + kThreads - 1) / kThreads),
+                       dim3(kThreads), lds, stream, da);
   else
-    hipLaunchKernelGGL((decode_combine<D, GP>), dim3(pl.Hkv, pl.B), dim3(kThreads), lds, stream, da);
+    hipLaunchKernelGGL((decode_combine<D, GP, false>), dim3(pl.Hkv, pl.B), dim3(kThreads), lds, stream, da);
   return hipGetLastError();
 }
 
