@@ -27,8 +27,10 @@
 //   T x { lloyd_assign   MFMA distances ||mu||^2 - 2 k.mu with mu = hi + lo,
 //                        argmin with ties to the lower centre, and per-block
 //                        group histograms
-//         lloyd_offsets  group starts and per-block offsets (counting sort)
+//         lloyd_offsets  group starts and per-block offsets (counting sort),
+//                        and the update's pieces
 //         lloyd_scatter  stable placement of E by group
+//        [lloyd_sort     both in one launch where E is short]
 //         lloyd_update   fp64 sums of the members in fixed order -> new
 //                        centres; in the last round also the mean values,
 //                        counts and log-counts written to the cache }
@@ -64,6 +66,7 @@ constexpr int kSelPer = 8;                          // scores per selection thre
 constexpr int kSelChunk = kSelPer * kSelThreads;   // scores per selection block
 constexpr int kSelHist = 4 * 2 * 256;              // selection pass histograms per head: [pass][threshold][digit]
 constexpr int kAdaThreads = 1024;
+constexpr int kPieceMin = 4096;                     // update pieces of 1024 members from which they are not cut smaller
 
 struct BuildArgs {
   const void* k;
@@ -91,12 +94,15 @@ struct BuildArgs {
   float* cnorm;        // [BH][Rcap]
   int32_t* assign;     // [BH][S]   group of evicted token i
   int32_t* hist;       // [BH][NBLK][Rcap] block histograms -> block offsets
-  int32_t* cstart;     // [BH][Rcap]
-  int32_t* ccount;     // [BH][Rcap]
   int32_t* order;      // [BH][S]   evicted positions grouped by centre
+  int4* items;         // [BH][NIT] update pieces: group | piece << 12, partial slot or -1, first entry of order, group size
+  int32_t* nitem;      // [BH]
+  int32_t* parrive;    // [BH][Rcap] pieces of a split group that have left their sums
+  double* part;        // [BH][NPART][2][D] key and value sums of split groups' pieces
   int32_t* sel_hist;   // [BH][4][2][256] selection pass histograms (zeroed by pool_scores)
   int32_t* sel_cnt;    // [BH][NSEL][4] per selection block: above / equal to each threshold
   int B, Hq, Hkv, G, C, Rcap, S, w, R, LG, NCH, NBLK, NSEL, T;
+  int lpiece, NIT, NPART;  // log2 of the members per update piece, pieces and partial slots per head
   int wr;              // leading window rows per query head that score (R = G * wr)
   int pool_half;       // pooling taps on each side of a position
   int cap_slots;       // slots a head may fill at construction (C minus the decode reserve)
@@ -399,22 +405,22 @@ __global__ __launch_bounds__(kThreads) void pool_scores(BuildArgs a) {
 
 // -------------------------------------------------------------- selection
 
-// Exclusive scan of one int per thread over a block of NT threads.
-template <int NT>
-__device__ __forceinline__ int block_excl_scan(int v, int* s_tmp, int& total) {
+// Exclusive scan of one whole number per thread over a block of NT threads.
+template <int NT, typename I>
+__device__ __forceinline__ I block_excl_scan(I v, I* s_tmp, I& total) {
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  int x = v;
+  I x = v;
 #pragma unroll
   for (int o = 1; o < 64; o <<= 1) {
-    const int y = __shfl_up(x, o, 64);
+    const I y = __shfl_up(x, o, 64);
     if (lane >= o) x += y;
   }
   if (lane == 63) s_tmp[wave] = x;
   __syncthreads();
-  int off = 0, tot = 0;
+  I off = 0, tot = 0;
 #pragma unroll
   for (int w2 = 0; w2 < NT / 64; ++w2) {
-    const int t = s_tmp[w2];
+    const I t = s_tmp[w2];
     if (w2 < wave) off += t;
     tot += t;
   }
@@ -1193,7 +1199,9 @@ __global__ __launch_bounds__((AssignShape<T, D, kLo>::kThreads), (AssignShape<T,
     }
   }
   // group histograms of the 256-token blocks of the evicted list that this
-  // block covers and that hold tokens, one at a time through LDS
+  // block covers and that hold tokens, one at a time through LDS (none where
+  // one block sorts the head)
+  if (a.hist == nullptr) return;
   for (int q = 0; q < kSubs && t0 + q * kTokBlock < hm.nE; ++q) {  // block-uniform
     for (int j = tid; j < hm.r_eff; j += kNT) s_hist[j] = 0;
     __syncthreads();
@@ -1209,6 +1217,30 @@ __global__ __launch_bounds__((AssignShape<T, D, kLo>::kThreads), (AssignShape<T,
   }
 }
 
+// First sorted position of group j (cnt members), and its update pieces: a
+// group of up to 2^lpiece members is one piece, a larger one is cut into
+// pieces that leave partial sums (parrive counts them). Called by every
+// thread of an NT-thread block, in group order, `on` where it holds a group;
+// the scan carries members, pieces (bits 32..47) and split groups' pieces
+// (bits 48..63), each below its field's limit, from earlier calls in `carry`
+// to `all`.
+template <int NT>
+__device__ __forceinline__ int emit_pieces(const BuildArgs& a, int bh, int j, bool on, int cnt, unsigned long long carry,
+                                           unsigned long long* s_tmp, unsigned long long& all) {
+  const int np = max(1, (cnt + (1 << a.lpiece) - 1) >> a.lpiece);
+  const unsigned long long own =
+      on ? (unsigned)cnt | (unsigned long long)np << 32 | (unsigned long long)(np > 1 ? np : 0) << 48 : 0ull;
+  const unsigned long long at = carry + block_excl_scan<NT>(own, s_tmp, all);
+  const int start = (int)(at & 0xffffffffu);
+  if (on) {
+    a.parrive[(size_t)bh * a.Rcap + j] = 0;
+    int4* it = a.items + (size_t)bh * a.NIT + (int)(at >> 32 & 0xffff);
+    for (int q = 0; q < np; ++q)
+      it[q] = make_int4(j | q << 12, np > 1 ? (int)(at >> 48) + q : -1, start + (q << a.lpiece), cnt);
+  }
+  return start;
+}
+
 // Group sizes and counting-sort offsets: hist[blk][j] becomes the first
 // output position of block blk's members of group j. One 1024-thread block
 // per head; the groups take `cols` threads (r' rounded up to a power of two,
@@ -1222,32 +1254,35 @@ __global__ __launch_bounds__(kOffThreads) void lloyd_offsets(BuildArgs a) {
   if (hm.r_eff == 0) return;
   __shared__ int s_part[kOffThreads];   // per (row group, group) row sums
   __shared__ int s_start[kOffThreads];  // first output position of each group
-  __shared__ int s_tmp[kOffThreads / 64];
+  __shared__ unsigned long long s_tmp[kOffThreads / 64];
   const int nblk = (hm.nE + kTokBlock - 1) / kTokBlock;
   int32_t* hist = a.hist + (size_t)bh * a.NBLK * a.Rcap;
-  int cols = 1;
-  while (cols < hm.r_eff && cols < kOffThreads) cols <<= 1;
-  const int ngrp = kOffThreads / cols;
-  const int c = threadIdx.x % cols, rg = threadIdx.x / cols;
-  const int per = (nblk + ngrp - 1) / ngrp;
+  int lc = 0;  // log2 of cols
+  while ((1 << lc) < hm.r_eff && (1 << lc) < kOffThreads) ++lc;
+  const int cols = 1 << lc, ngrp = kOffThreads >> lc;
+  const int c = threadIdx.x & (cols - 1), rg = threadIdx.x >> lc;
+  const int per = (nblk + ngrp - 1) >> (10 - lc);
+  static_assert(kOffThreads == 1 << 10, "row group split");
   const int q_lo = min(nblk, rg * per), q_hi = min(nblk, q_lo + per);
   // the rows of this thread's range are read in batches of kBatch independent
   // loads so the walk is not a chain of memory round trips
   constexpr int kBatch = 16;
-  int carry = 0;
+  unsigned long long carry = 0;  // running totals of the passes before (emit_pieces)
   for (int j0 = 0; j0 < hm.r_eff; j0 += cols) {
     const int j = j0 + c;
     const bool act = j < hm.r_eff;
     int tot = 0;
-    if (act) {
+    auto read = [&](int (&v)[kBatch], int q0) {
+#pragma unroll
+      for (int u = 0; u < kBatch; ++u) v[u] = q0 + u < q_hi ? hist[(size_t)(q0 + u) * a.Rcap + j] : 0;
+    };
+    if (act)
       for (int q0 = q_lo; q0 < q_hi; q0 += kBatch) {
         int v[kBatch];
-#pragma unroll
-        for (int u = 0; u < kBatch; ++u) v[u] = q0 + u < q_hi ? hist[(size_t)(q0 + u) * a.Rcap + j] : 0;
+        read(v, q0);
 #pragma unroll
         for (int u = 0; u < kBatch; ++u) tot += v[u];
       }
-    }
     s_part[threadIdx.x] = tot;
     __syncthreads();
     int before = 0, col_tot = 0;  // rows of lower row groups come first
@@ -1256,21 +1291,15 @@ __global__ __launch_bounds__(kOffThreads) void lloyd_offsets(BuildArgs a) {
       before += g2 < rg ? v : 0;
       col_tot += v;
     }
-    int all;
-    const int start = carry + block_excl_scan<kOffThreads>(rg == 0 && act ? col_tot : 0, s_tmp, all);
+    unsigned long long all;
+    const int start = emit_pieces<kOffThreads>(a, bh, j, rg == 0 && act, col_tot, carry, s_tmp, all);
     if (rg == 0) s_start[c] = start;  // the row-group-0 threads come first in the scan
     __syncthreads();
     if (act) {
-      const int first = s_start[c];
-      if (rg == 0) {
-        a.cstart[(size_t)bh * a.Rcap + j] = first;
-        a.ccount[(size_t)bh * a.Rcap + j] = col_tot;
-      }
-      int run = first + before;
+      int run = s_start[c] + before;
       for (int q0 = q_lo; q0 < q_hi; q0 += kBatch) {
         int v[kBatch];
-#pragma unroll
-        for (int u = 0; u < kBatch; ++u) v[u] = q0 + u < q_hi ? hist[(size_t)(q0 + u) * a.Rcap + j] : 0;
+        read(v, q0);
 #pragma unroll
         for (int u = 0; u < kBatch; ++u) {
           if (q0 + u < q_hi) hist[(size_t)(q0 + u) * a.Rcap + j] = run;
@@ -1280,6 +1309,87 @@ __global__ __launch_bounds__(kOffThreads) void lloyd_offsets(BuildArgs a) {
     }
     carry += all;
     __syncthreads();  // s_part and s_start are rewritten by the next pass
+  }
+  if (threadIdx.x == 0) a.nitem[bh] = (int)(carry >> 32 & 0xffff);
+}
+
+// Rank of this lane's token among the earlier lanes' tokens of the same group
+// (r_eff groups, one ballot per bit of the group index); peers = the lanes of
+// that group. Called by every lane of the wave, `live` where it holds a token.
+__device__ __forceinline__ int wave_group_rank(int g, bool live, int r_eff, int lane, uint64_t& peers) {
+  peers = __ballot(live);
+  const int nbits = r_eff > 1 ? 32 - __clz(r_eff - 1) : 0;
+  for (int bit = 0; bit < nbits; ++bit) {
+    const bool on = (g >> bit) & 1;
+    const uint64_t set = __ballot(live && on);
+    peers &= on ? set : ~set;
+  }
+  return __popcll(peers & ((1ull << lane) - 1));
+}
+
+// The whole counting sort of a head with few evicted tokens in one block: the
+// tokens in 64-token batches (up to kSortBatches per wave), a table of the
+// batches' group counts in LDS, prefixes over the batches and the groups, then
+// the stable placement. It takes the place of the per-block histograms, the
+// offsets and the scatter where those are bound by their launches (2 heads of
+// 928 tokens: 8.4 + 3.2 -> 5.2 us a round). The table and the batches per wave
+// set the line: 16384 entries of 16 bits, 128 batches (8192 tokens), 1024
+// groups.
+constexpr int kSortThreads = 1024;
+constexpr int kSortBatches = 8;
+constexpr int kSortTable = 16384;
+__global__ __launch_bounds__(kSortThreads) void lloyd_sort(BuildArgs a) {
+  const int kvh = blockIdx.y, b = blockIdx.z;
+  const int bh = b * a.Hkv + kvh;
+  const HeadMeta hm = a.meta[bh];
+  const int r = hm.r_eff;
+  if (r == 0) return;
+  __shared__ __align__(4) uint16_t s_cnt[kSortTable];  // [batch][group] counts, then prefixes over the batches
+  __shared__ int s_start[kSortThreads];
+  __shared__ unsigned long long s_tmp[kSortThreads / 64];
+  constexpr int kNW = kSortThreads / 64;
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int nb = (hm.nE + 63) / 64;
+  int g[kSortBatches], src[kSortBatches], rank[kSortBatches];
+#pragma unroll
+  for (int k = 0; k < kSortBatches; ++k) {
+    const int i = (k * kNW + wave) * 64 + lane;
+    g[k] = i < hm.nE ? a.assign[(size_t)bh * a.S + i] : 0;
+    src[k] = i < hm.nE ? a.elist[(size_t)bh * a.S + i] : 0;
+  }
+  for (int x = tid; x < (nb * r + 1) / 2; x += kSortThreads) reinterpret_cast<uint32_t*>(s_cnt)[x] = 0;
+  __syncthreads();  // the table is cleared
+#pragma unroll
+  for (int k = 0; k < kSortBatches; ++k) {
+    const int q = k * kNW + wave;
+    if (q >= nb) break;  // wave-uniform
+    const bool live = q * 64 + lane < hm.nE;
+    uint64_t peers;
+    rank[k] = wave_group_rank(g[k], live, r, lane, peers);
+    if (live && rank[k] == 0) s_cnt[q * r + g[k]] = (uint16_t)__popcll(peers);
+  }
+  __syncthreads();
+  int run = 0;
+  if (tid < r)
+    for (int q0 = 0; q0 < nb; q0 += 8) {
+      int v[8];
+#pragma unroll
+      for (int u = 0; u < 8; ++u) v[u] = q0 + u < nb ? s_cnt[(q0 + u) * r + tid] : 0;
+#pragma unroll
+      for (int u = 0; u < 8; ++u) {
+        if (q0 + u < nb) s_cnt[(q0 + u) * r + tid] = (uint16_t)run;
+        run += v[u];
+      }
+    }
+  unsigned long long all;
+  s_start[tid] = emit_pieces<kSortThreads>(a, bh, tid, tid < r, run, 0ull, s_tmp, all);
+  if (tid == 0) a.nitem[bh] = (int)(all >> 32 & 0xffff);
+  __syncthreads();  // starts and prefixes are complete
+#pragma unroll
+  for (int k = 0; k < kSortBatches; ++k) {
+    const int q = k * kNW + wave;
+    if (q >= nb) break;
+    if (q * 64 + lane < hm.nE) a.order[(size_t)bh * a.S + s_start[g[k]] + s_cnt[q * r + g[k]] + rank[k]] = src[k];
   }
 }
 
@@ -1302,14 +1412,8 @@ __global__ __launch_bounds__(kTokBlock) void lloyd_scatter(BuildArgs a) {
   const int g = live ? a.assign[(size_t)bh * a.S + i] : 0;
   const int src = live ? a.elist[(size_t)bh * a.S + i] : 0;
   for (int j = tid; j < kNW * hm.r_eff; j += kTokBlock) s_cnt[j] = 0;
-  uint64_t peers = __ballot(live);
-  const int nbits = hm.r_eff > 1 ? 32 - __clz(hm.r_eff - 1) : 0;
-  for (int bit = 0; bit < nbits; ++bit) {
-    const bool on = (g >> bit) & 1;
-    const uint64_t set = __ballot(live && on);
-    peers &= on ? set : ~set;
-  }
-  const int in_wave = __popcll(peers & ((1ull << lane) - 1));
+  uint64_t peers;
+  const int in_wave = wave_group_rank(g, live, hm.r_eff, lane, peers);
   __syncthreads();  // the table is cleared
   if (live && in_wave == 0) s_cnt[wave * hm.r_eff + g] = __popcll(peers);
   __syncthreads();
@@ -1320,58 +1424,82 @@ __global__ __launch_bounds__(kTokBlock) void lloyd_scatter(BuildArgs a) {
   a.order[(size_t)bh * a.S + dst] = src;
 }
 
-// Member indices q, q + NG, q + 2NG, q + 3NG of a group's sorted list.
-__device__ __forceinline__ void load_ids(int (&id)[4], const int32_t* mem, int q, int NG) {
+// Member indices q, q + NG, q + 2NG, q + 3NG of a piece's sorted list of cnt
+// members (past its end the last member's).
+__device__ __forceinline__ void load_ids(int (&id)[4], const int32_t* mem, int q, int NG, int cnt) {
 #pragma unroll
-  for (int u = 0; u < 4; ++u) id[u] = mem[q + u * NG];
+  for (int u = 0; u < 4; ++u) id[u] = mem[min(q + u * NG, cnt - 1)];
 }
 
-// New centre of group j = fp64 mean of its members' keys, summed in a fixed
+// acc += the 8 elements of one row piece (zeros where the row is past the end)
+__device__ __forceinline__ void add_row(double (&acc)[8], uint4 w, bool in) {
+  const uint32_t pw[4] = {in ? w.x : 0u, in ? w.y : 0u, in ? w.z : 0u, in ? w.w : 0u};
+#pragma unroll
+  for (int e = 0; e < 4; ++e) {
+    acc[2 * e] += (double)bf16_lo(pw[e]);
+    acc[2 * e + 1] += (double)bf16_hi(pw[e]);
+  }
+}
+
+// New centre of a group = fp64 mean of its members' keys, summed in a fixed
 // order; an empty group keeps its centre. The last round also writes the
-// entry: mean key and mean value in the cache dtype, and log c_j. Each
-// thread keeps four member rows in flight and requests the next four
-// members' indices right behind them, so a long group (the first round's
-// groups, grown around single seed keys, run from a few rows to thousands)
-// waits one memory round trip per step. bf16 rows stay packed until they are
-// added (68 registers, seven blocks per CU).
+// entry: mean key and mean value in the cache dtype, and log c_j. One block
+// per piece: a group of up to 2^lpiece members, or that many members of a
+// larger one, whose pieces leave their sums and whose last piece to arrive
+// adds them in piece order. Bound by the gathered rows' HBM traffic once no
+// block runs long: the first round's groups, grown around single seed keys,
+// run from a few members to tens of thousands, and with one block per group
+// the largest one set the time (32 heads of 130K tokens, 0 to 256 groups:
+// first round 519 -> 172 us, later rounds 191-213 -> 174 us; 8 heads of 32K
+// tokens: 78 -> 16 us and 18-30 -> 15 us).
+// Each thread keeps four member rows in flight and requests the next four
+// members' indices right behind them; the last step is padded with the last
+// member (added as zeros), so a group of 64 members or fewer costs one round
+// trip for the indices and one for the rows. bf16 rows stay packed until they
+// are added (seven blocks per CU).
 // kKV (last round, bf16): each member's key and value rows are read in the
 // same loop, twice the rows in flight of two passes one after the other.
 template <typename T, int D, bool kKV = false>
 __global__ __launch_bounds__(kThreads, (kKV && sizeof(T) == 2 ? 4 : sizeof(T) == 2 ? 7 : 4)) void lloyd_update(BuildArgs a, int last, int rev) {
-  const int j = blockIdx.x;
   int b, kvh, bh;
   block_head(a, rev, b, kvh, bh);
   const HeadMeta hm = a.meta[bh];
-  if (j >= hm.r_eff) return;
+  if (hm.r_eff == 0 || (int)blockIdx.x >= a.nitem[bh]) return;
   constexpr int CPR = D / 8;            // lanes per row, 8 elements each
   constexpr int NG = kThreads / CPR;    // member groups
   __shared__ double s_sum[NG][D];
   __shared__ float s_mu[D];
   __shared__ double s_red[D];
+  __shared__ int s_last;
   const int tid = threadIdx.x, c = tid % CPR, g = tid / CPR;
+  const int4 item = a.items[(size_t)bh * a.NIT + blockIdx.x];
+  const int j = item.x & 0xfff, piece = item.x >> 12, total = item.w;
   const size_t ci = (size_t)bh * a.Rcap + j;
-  const int cnt = a.ccount[ci];
-  const int32_t* mem = a.order + (size_t)bh * a.S + a.cstart[ci];
+  const int cnt = min(1 << a.lpiece, total - (piece << a.lpiece));  // members of this piece
+  const int32_t* mem = a.order + (size_t)bh * a.S + item.z;
   const T* K = static_cast<const T*>(a.k) + (size_t)bh * a.S * D;
   const T* V = static_cast<const T*>(a.v) + (size_t)bh * a.S * D;
+  double sk = 0.0, sv = 0.0;  // key and value sums of column tid (threads tid < D)
+  // the member groups' sums of one column in ascending order
+  auto reduce = [&](const double (&acc)[8]) {
+#pragma unroll
+    for (int e = 0; e < 8; ++e) s_sum[g][8 * c + e] = acc[e];
+    __syncthreads();
+    double t = 0.0;
+    if (tid < D)
+      for (int gg = 0; gg < NG; ++gg) t += s_sum[gg][tid];
+    __syncthreads();
+    return t;
+  };
+  int id[4];
   if constexpr (kKV && sizeof(T) == 2) {
     // last round: the key and value rows of each member are read together
     // (twice the rows in flight), each summed in member order as below
     double ak[8], av[8];
 #pragma unroll
     for (int e = 0; e < 8; ++e) ak[e] = av[e] = 0.0;
-    auto add8 = [](double (&acc)[8], const uint4& w) {
-      const uint32_t pw[4] = {w.x, w.y, w.z, w.w};
-#pragma unroll
-      for (int e = 0; e < 4; ++e) {
-        acc[2 * e] += (double)bf16_lo(pw[e]);
-        acc[2 * e + 1] += (double)bf16_hi(pw[e]);
-      }
-    };
-    int q = g;
-    int id[4];
-    if (q + 3 * NG < cnt) load_ids(id, mem, q, NG);
-    for (; q + 3 * NG < cnt; q += 4 * NG) {
+    if (g < cnt) load_ids(id, mem, g, NG, cnt);
+    for (int q = g; q < cnt; q += 4 * NG) {
       uint4 wk[4], wv[4];
 #pragma unroll
       for (int u = 0; u < 4; ++u) {
@@ -1379,106 +1507,100 @@ __global__ __launch_bounds__(kThreads, (kKV && sizeof(T) == 2 ? 4 : sizeof(T) ==
         wk[u] = *reinterpret_cast<const uint4*>(K + off);
         wv[u] = *reinterpret_cast<const uint4*>(V + off);
       }
-      if (q + 7 * NG < cnt) load_ids(id, mem, q + 4 * NG, NG);  // the next rows' indices
+      if (q + 4 * NG < cnt) load_ids(id, mem, q + 4 * NG, NG, cnt);  // the next rows' indices
 #pragma unroll
-      for (int u = 0; u < 4; ++u) add8(ak, wk[u]);
+      for (int u = 0; u < 4; ++u) add_row(ak, wk[u], q + u * NG < cnt);
 #pragma unroll
-      for (int u = 0; u < 4; ++u) add8(av, wv[u]);
+      for (int u = 0; u < 4; ++u) add_row(av, wv[u], q + u * NG < cnt);
     }
-    for (; q < cnt; q += NG) {
-      const size_t off = (size_t)mem[q] * D + 8 * c;
-      const uint4 wk = *reinterpret_cast<const uint4*>(K + off);
-      const uint4 wv = *reinterpret_cast<const uint4*>(V + off);
-      add8(ak, wk);
-      add8(av, wv);
-    }
-    for (int pass = 0; pass < 2; ++pass) {
+    sk = reduce(ak);
+    sv = reduce(av);
+  } else {
+    for (int pass = 0; pass < (last ? 2 : 1); ++pass) {
+      const T* X = pass == 0 ? K : V;
+      double acc[8];
 #pragma unroll
-      for (int e = 0; e < 8; ++e) s_sum[g][8 * c + e] = pass == 0 ? ak[e] : av[e];
-      __syncthreads();
-      if (tid < D) {
-        double t = 0.0;
-        for (int gg = 0; gg < NG; ++gg) t += s_sum[gg][tid];
-        const float mean = cnt > 0 ? (float)(t / cnt) : 0.f;
-        if (pass == 0) {
-          const float mu = cnt > 0 ? mean : a.cent[ci * D + tid];  // empty group keeps its centre
-          a.cent[ci * D + tid] = mu;
-          store_elem(static_cast<T*>(a.kc) + ((size_t)bh * a.C + j) * D + tid, mu);
+      for (int e = 0; e < 8; ++e) acc[e] = 0.0;
+      // members g, g + NG, g + 2NG, ... in order
+      if (g < cnt) load_ids(id, mem, g, NG, cnt);
+      for (int q = g; q < cnt; q += 4 * NG) {
+        if constexpr (sizeof(T) == 2) {  // rows stay packed until added: 4 registers each
+          uint4 w[4];
+#pragma unroll
+          for (int u = 0; u < 4; ++u) w[u] = *reinterpret_cast<const uint4*>(X + (size_t)id[u] * D + 8 * c);
+          if (q + 4 * NG < cnt) load_ids(id, mem, q + 4 * NG, NG, cnt);
+#pragma unroll
+          for (int u = 0; u < 4; ++u) add_row(acc, w[u], q + u * NG < cnt);
         } else {
-          store_elem(static_cast<T*>(a.vc) + ((size_t)bh * a.C + j) * D + tid, mean);
+          float x[4][8];
+#pragma unroll
+          for (int u = 0; u < 4; ++u) load8_f32(X + (size_t)id[u] * D + 8 * c, x[u]);
+          if (q + 4 * NG < cnt) load_ids(id, mem, q + 4 * NG, NG, cnt);
+#pragma unroll
+          for (int u = 0; u < 4; ++u)
+#pragma unroll
+            for (int e = 0; e < 8; ++e) acc[e] += q + u * NG < cnt ? (double)x[u][e] : 0.0;
         }
       }
-      __syncthreads();
+      const double t = reduce(acc);
+      if (pass == 0) sk = t;
+      else sv = t;
     }
-    if (tid == 0) a.logc[ci] = cnt > 0 ? logf((float)cnt) : kNegInf;
-    return;
   }
-  for (int pass = 0; pass < (last ? 2 : 1); ++pass) {
-    const T* X = pass == 0 ? K : V;
-    double acc[8];
-#pragma unroll
-    for (int e = 0; e < 8; ++e) acc[e] = 0.0;
-    // members g, g + NG, g + 2NG, ... in order; four 16-byte row loads in
-    // flight, and (wider variant) the next four members' indices requested
-    // behind them; the packed variant has no registers to spare for them
-    int q = g;
-    int id[4];
-    if (q + 3 * NG < cnt) load_ids(id, mem, q, NG);
-    for (; q + 3 * NG < cnt; q += 4 * NG) {
-      if constexpr (sizeof(T) == 2) {  // rows stay packed until added: 4 registers each
-        uint4 w[4];
-#pragma unroll
-        for (int u = 0; u < 4; ++u) w[u] = *reinterpret_cast<const uint4*>(X + (size_t)id[u] * D + 8 * c);
-        if (q + 7 * NG < cnt) load_ids(id, mem, q + 4 * NG, NG);
-#pragma unroll
-        for (int u = 0; u < 4; ++u) {
-          const uint32_t pw[4] = {w[u].x, w[u].y, w[u].z, w[u].w};
-#pragma unroll
-          for (int e = 0; e < 4; ++e) {
-            acc[2 * e] += (double)bf16_lo(pw[e]);
-            acc[2 * e + 1] += (double)bf16_hi(pw[e]);
-          }
-        }
-      } else {
-        float x[4][8];
-#pragma unroll
-        for (int u = 0; u < 4; ++u) load8_f32(X + (size_t)id[u] * D + 8 * c, x[u]);
-        if (q + 7 * NG < cnt) load_ids(id, mem, q + 4 * NG, NG);
-#pragma unroll
-        for (int u = 0; u < 4; ++u)
-#pragma unroll
-          for (int e = 0; e < 8; ++e) acc[e] += (double)x[u][e];
-      }
-    }
-    for (; q < cnt; q += NG) {
-      float x[8];
-      load8_f32(X + (size_t)mem[q] * D + 8 * c, x);
-#pragma unroll
-      for (int e = 0; e < 8; ++e) acc[e] += (double)x[e];
-    }
-#pragma unroll
-    for (int e = 0; e < 8; ++e) s_sum[g][8 * c + e] = acc[e];
-    __syncthreads();
+  if (item.y >= 0) {  // block-uniform: a piece of a split group
+    // Partial sums and arrivals go through agent-scope accesses (the pieces
+    // run on several XCDs, whose L2s do not see each other's plain stores);
+    // every store has completed before the block counts itself in, so the
+    // block that counts last reads complete sums.
+    const int np = (total + (1 << a.lpiece) - 1) >> a.lpiece;
+    unsigned long long* part = reinterpret_cast<unsigned long long*>(a.part) + (size_t)bh * a.NPART * 2 * D;
+    auto slot = [&](int p, int q) { return &part[((size_t)p * 2 + q) * D + tid]; };
     if (tid < D) {
-      double t = 0.0;
-      for (int gg = 0; gg < NG; ++gg) t += s_sum[gg][tid];
-      const float mean = cnt > 0 ? (float)(t / cnt) : 0.f;
-      if (pass == 0) {
-        const float mu = cnt > 0 ? mean : a.cent[ci * D + tid];  // empty group keeps its centre
-        s_mu[tid] = mu;
-        a.cent[ci * D + tid] = mu;
-        if (last) store_elem(static_cast<T*>(a.kc) + ((size_t)bh * a.C + j) * D + tid, mu);
-      } else {
-        store_elem(static_cast<T*>(a.vc) + ((size_t)bh * a.C + j) * D + tid, mean);
-      }
+      __hip_atomic_store(slot(item.y, 0), (unsigned long long)__double_as_longlong(sk), __ATOMIC_RELAXED,
+                         __HIP_MEMORY_SCOPE_AGENT);
+      if (last)
+        __hip_atomic_store(slot(item.y, 1), (unsigned long long)__double_as_longlong(sv), __ATOMIC_RELAXED,
+                           __HIP_MEMORY_SCOPE_AGENT);
     }
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
     __syncthreads();
+    if (tid == 0) s_last = atomicAdd(&a.parrive[ci], 1) == np - 1;
+    __syncthreads();
+    if (!s_last) return;
+    asm volatile("" ::: "memory");
+    auto gather = [&](int q) {
+      double t = 0.0;
+      for (int p0 = 0; p0 < np; p0 += 8) {  // 8 partial sums in flight, added in piece order
+        unsigned long long v[8];
+#pragma unroll
+        for (int u = 0; u < 8; ++u)
+          v[u] = __hip_atomic_load(slot(item.y - piece + min(p0 + u, np - 1), q), __ATOMIC_RELAXED,
+                                   __HIP_MEMORY_SCOPE_AGENT);
+#pragma unroll
+        for (int u = 0; u < 8; ++u) t += p0 + u < np ? __longlong_as_double((long long)v[u]) : 0.0;
+      }
+      return t;
+    };
+    if (tid < D) {
+      sk = gather(0);
+      if (last) sv = gather(1);
+    }
+  }
+  if (tid < D) {
+    const float mu = total > 0 ? (float)(sk / total) : a.cent[ci * D + tid];  // empty group keeps its centre
+    a.cent[ci * D + tid] = mu;
+    s_mu[tid] = mu;
+    if (last) {
+      store_elem(static_cast<T*>(a.kc) + ((size_t)bh * a.C + j) * D + tid, mu);
+      store_elem(static_cast<T*>(a.vc) + ((size_t)bh * a.C + j) * D + tid, total > 0 ? (float)(sv / total) : 0.f);
+    }
   }
   if (last) {
-    if (tid == 0) a.logc[ci] = cnt > 0 ? logf((float)cnt) : kNegInf;
-  } else {
-    prep_center<D>(a, ci, s_mu, s_red);
+    if (tid == 0) a.logc[ci] = total > 0 ? logf((float)total) : kNegInf;
+    return;
   }
+  __syncthreads();
+  prep_center<D>(a, ci, s_mu, s_red);
 }
 
 __global__ void fill_i32(int32_t* p, size_t n, int32_t v) {
@@ -1551,10 +1673,13 @@ BuildArgs make_args(const BuildPlan& pl, const void* k, const void* v, const voi
   a.cent_lo = reinterpret_cast<uint16_t*>(ws + pl.off_clo);
   a.cnorm = reinterpret_cast<float*>(ws + pl.off_cnorm);
   a.assign = reinterpret_cast<int32_t*>(ws + pl.off_assign);
-  a.hist = reinterpret_cast<int32_t*>(ws + pl.off_hist);
-  a.cstart = reinterpret_cast<int32_t*>(ws + pl.off_cstart);
-  a.ccount = reinterpret_cast<int32_t*>(ws + pl.off_ccount);
+  a.hist = pl.one_sort ? nullptr : reinterpret_cast<int32_t*>(ws + pl.off_hist);
   a.order = reinterpret_cast<int32_t*>(ws + pl.off_order);
+  a.items = reinterpret_cast<int4*>(ws + pl.off_items);
+  a.nitem = reinterpret_cast<int32_t*>(ws + pl.off_nitem);
+  a.parrive = reinterpret_cast<int32_t*>(ws + pl.off_parrive);
+  a.part = reinterpret_cast<double*>(ws + pl.off_part);
+  a.lpiece = pl.lpiece; a.NIT = pl.NIT; a.NPART = pl.NPART;
   a.sel_hist = reinterpret_cast<int32_t*>(ws + pl.off_selh);
   a.sel_cnt = reinterpret_cast<int32_t*>(ws + pl.off_selc);
   a.NSEL = pl.NSEL;
@@ -1635,16 +1760,20 @@ hipError_t launch_candidate_typed(const BuildPlan& pl, const BuildArgs& a, hipSt
         hipLaunchKernelGGL((lloyd_assign<T, D>), grid((pl.max_E + S2::kTokens - 1) / S2::kTokens), dim3(S2::kThreads),
                            hist_lds, st, a, it);
       RESKV_CHECK();
-      hipLaunchKernelGGL(lloyd_offsets, bhg, dim3(kOffThreads), 0, st, a); RESKV_CHECK();
-      hipLaunchKernelGGL(lloyd_scatter, grid(pl.NBLK), dim3(kTokBlock), (kTokBlock / 64) * hist_lds, st, a);
-      RESKV_CHECK();
+      if (pl.one_sort) {
+        hipLaunchKernelGGL(lloyd_sort, bhg, dim3(kSortThreads), 0, st, a); RESKV_CHECK();
+      } else {
+        hipLaunchKernelGGL(lloyd_offsets, bhg, dim3(kOffThreads), 0, st, a); RESKV_CHECK();
+        hipLaunchKernelGGL(lloyd_scatter, grid(pl.NBLK), dim3(kTokBlock), (kTokBlock / 64) * hist_lds, st, a);
+        RESKV_CHECK();
+      }
       // the update walks the heads in reverse of the assignment before and
       // after it, so each starts on the keys the other read last
       const int last = it == pl.T - 1 ? 1 : 0;
       if (last)
-        hipLaunchKernelGGL((lloyd_update<T, D, true>), grid(pl.max_reff), dim3(kThreads), 0, st, a, last, 1);
+        hipLaunchKernelGGL((lloyd_update<T, D, true>), grid(pl.NIT), dim3(kThreads), 0, st, a, last, 1);
       else
-        hipLaunchKernelGGL((lloyd_update<T, D>), grid(pl.max_reff), dim3(kThreads), 0, st, a, last, 1);
+        hipLaunchKernelGGL((lloyd_update<T, D>), grid(pl.NIT), dim3(kThreads), 0, st, a, last, 1);
       RESKV_CHECK();
     }
   }
@@ -1704,6 +1833,15 @@ bool layout_build_plan(BuildPlan* plan) {
   if (pl.NBLK < 1) pl.NBLK = 1;
   pl.NSEL = (pl.max_s + kSelChunk - 1) / kSelChunk;
   if (pl.NSEL < 1) pl.NSEL = 1;
+  const int nb64 = (pl.max_E + 63) / 64;
+  pl.one_sort = nb64 <= kSortBatches * (kSortThreads / 64) && pl.max_reff <= kSortThreads &&
+                (long long)nb64 * pl.max_reff <= kSortTable;
+  // update pieces of 256 members while the whole construction has fewer than
+  // kPieceMin of 1024 (short chains where few blocks are in flight), else 1024
+  pl.lpiece = BH * (size_t)((pl.max_E + 1023) / 1024) < kPieceMin ? 8 : 10;
+  while (pl.max_E >> pl.lpiece > 16384) ++pl.lpiece;  // piece counts stay below 2^16 (lloyd_offsets packs them)
+  pl.NIT = pl.max_reff + (pl.max_E >> pl.lpiece);  // sum over groups of max(1, ceil(count / piece))
+  pl.NPART = 2 * (pl.max_E >> pl.lpiece);        // groups above one piece: ceil(c / piece) <= 2 c / piece
   size_t off = 0;
   auto take = [&](size_t bytes) { const size_t o = off; off = align_up(off + bytes, 256); return o; };
   pl.off_meta = take(BH * sizeof(HeadMeta));
@@ -1718,10 +1856,12 @@ bool layout_build_plan(BuildPlan* plan) {
   pl.off_clo = take(BH * pl.Rcap * pl.D * sizeof(uint16_t));
   pl.off_cnorm = take(BH * pl.Rcap * sizeof(float));
   pl.off_assign = take(BH * pl.S * sizeof(int32_t));
-  pl.off_hist = take(BH * pl.NBLK * pl.Rcap * sizeof(int32_t));
-  pl.off_cstart = take(BH * pl.Rcap * sizeof(int32_t));
-  pl.off_ccount = take(BH * pl.Rcap * sizeof(int32_t));
+  pl.off_hist = take(pl.one_sort ? 0 : BH * pl.NBLK * pl.Rcap * sizeof(int32_t));
   pl.off_order = take(BH * pl.S * sizeof(int32_t));
+  pl.off_items = take(BH * pl.NIT * sizeof(int4));
+  pl.off_nitem = take(BH * sizeof(int32_t));
+  pl.off_parrive = take(BH * pl.Rcap * sizeof(int32_t));
+  pl.off_part = take(BH * pl.NPART * 2 * pl.D * sizeof(double));
   pl.off_selh = take(BH * kSelHist * sizeof(int32_t));
   pl.off_selc = take(BH * pl.NSEL * 4 * sizeof(int32_t));
   pl.bytes = off;

@@ -87,8 +87,11 @@ struct BuildPlan {
   int NBLK;   // 256-token blocks of the largest evicted set
   int NSEL;   // selection blocks (8192 scores each) of the longest sequence
   int max_s, max_main, max_reff, max_E;
+  bool one_sort;  // one block sorts a head's evicted tokens (short lists)
+  int lpiece, NIT, NPART;  // log2 of the members per update piece; pieces and partial-sum slots per head
   size_t off_meta, off_lsep, off_lse, off_raw, off_score, off_elist, off_seeds, off_cent, off_chi,
-      off_clo, off_cnorm, off_assign, off_hist, off_cstart, off_ccount, off_order, off_selh, off_selc, bytes;
+      off_clo, off_cnorm, off_assign, off_hist, off_order, off_items, off_nitem, off_parrive, off_part, off_selh,
+      off_selc, bytes;
 };
 
 // Device buffers one construction writes.

@@ -4,6 +4,9 @@ one kernel variant to another, each against the fp64 oracle."""
 import numpy as np
 import pytest
 
+from paper_2607_29591_amd import synth
+from tests.build_check import check_head, run_build
+from tests.test_build_gpu import host_copies
 from tests.test_decode_gpu import cache_case, check
 
 pytestmark = pytest.mark.gpu
@@ -20,3 +23,22 @@ def test_combine_many_records(dtype, d, G, C):
     main = [[C, 700, C - 3]]
     shape, q, kc, vc, logc = cache_case(40 + G, 1, G * Hkv, Hkv, d, dtype, C, Rcap, res, main)
     check(dtype, shape, q, kc, vc, logc, res, main)
+
+
+@pytest.mark.parametrize("dtype,d,evicted,res,budget", [
+    ("bf16", 128, 8192, (128, 3), 160),    # the sorting table of one block exactly full; groups of several pieces
+    ("bf16", 64, 8193, (128, 127), 160),   # one token more: offsets and scatter launches
+    ("bf16", 128, 1600, (600, 590), 640),  # 25 batches of 600 groups: 15000 of the table's 16384 entries
+    ("f32", 64, 1025, (1, 2), 40),         # one and two groups, cut into pieces of 256 members
+    ("f32", 128, 1100, (1030, 8), 1060),   # more than 1024 groups: offsets and scatter launches
+])
+def test_lloyd_sort_and_pieces(dtype, d, evicted, res, budget):
+    """Evicted sets and group counts at the edges of the one-block counting
+    sort and of the update's pieces (256 members each at these sizes)."""
+    s = evicted + budget - max(res)
+    wl = synth.tiny_workload(s=s, d=d, hq=4, hkv=2, budget=budget, res=0, window=8, dtype=dtype, n_heavy=6)
+    wl.res = np.asarray(res, np.int64).reshape(1, 1, 2)
+    x = host_copies(synth.gen_layer(wl, 0, seed=evicted, n_decode=1))
+    got = run_build(wl, x)
+    for h in range(2):
+        check_head(wl, x, got, 0, h)
