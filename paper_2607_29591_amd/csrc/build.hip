@@ -51,8 +51,8 @@ namespace reskv {
 namespace {
 
 constexpr int kThreads = 256;
-constexpr int kKeyGroups = 4;     // 256-key groups per score-pass block, one after the other
-constexpr int kKeyChunk = 256 * kKeyGroups;  // keys per score-pass block
+constexpr int kKeyGroups = 4;     // 256-key groups per lse chunk (at least) and per score-pass block
+constexpr int kFewChunks = 512;   // lse chunks (score-pass blocks) below which each is spread over more waves (blocks)
 // window rows staged in LDS per scoring step: 128, or 256 when there are
 // more than 128 (each key group is then loaded once for all of them)
 constexpr int kRowChunk = 128;
@@ -101,7 +101,7 @@ struct BuildArgs {
   double* part;        // [BH][NPART][2][D] key and value sums of split groups' pieces
   int32_t* sel_hist;   // [BH][4][2][256] selection pass histograms (zeroed by pool_scores)
   int32_t* sel_cnt;    // [BH][NSEL][4] per selection block: above / equal to each threshold
-  int B, Hq, Hkv, G, C, Rcap, S, w, R, LG, NCH, NBLK, NSEL, T;
+  int B, Hq, Hkv, G, C, Rcap, S, w, R, LG, KG, NCH, NBLK, NSEL, T;
   int lpiece, NIT, NPART;  // log2 of the members per update piece, pieces and partial slots per head
   int wr;              // leading window rows per query head that score (R = G * wr)
   int pool_half;       // pooling taps on each side of a position
@@ -127,34 +127,48 @@ __device__ __forceinline__ void store_elem(float* p, float x) { *p = x; }
 
 // Scoring row t = h*wr + i of the group: query head kvh*G + h, window row i
 // (position s-w+i); only the leading wr rows of each head's window score.
-// Rows [r0, r0 + nrows) are copied into LDS with rows of D*sizeof(T) + 16
-// bytes (the pad keeps MFMA fragment reads free of bank conflicts); rows at
-// or past R are zero.
+// Rows [r0, r0 + nrows) are copied into LDS, rows at or past R as zeros. The
+// 16-byte pieces of a row are permuted by the row's low bits, which keeps the
+// MFMA fragment reads free of bank conflicts without padding the rows.
 template <typename T, int D>
-__device__ __forceinline__ void stage_window_rows(unsigned char* s_q, const BuildArgs& a, int b, int kvh, int r0,
-                                                  int nrows) {
-  constexpr int kPieces = D * (int)sizeof(T) / 16;
-  constexpr int kQRowB = D * (int)sizeof(T) + 16;
-  for (int x = threadIdx.x; x < nrows * kPieces; x += blockDim.x) {
-    const int rr = x / kPieces, pc = x % kPieces, t = r0 + rr;
-    uint4 v = make_uint4(0, 0, 0, 0);
-    if (t < a.R) {
-      const int h = t / a.wr, i = t % a.wr;
-      const T* q = static_cast<const T*>(a.q_obs) + (((size_t)b * a.Hq + kvh * a.G + h) * a.w + i) * D;
-      v = reinterpret_cast<const uint4*>(q)[pc];
+struct WindowRows {
+  static constexpr int kRowB = D * (int)sizeof(T);
+  static constexpr int kPieces = kRowB / 16;  // 8 or more
+  static __device__ __forceinline__ int at(int row, int pc) { return row * kRowB + (pc ^ (row & 7)) * 16; }
+  static __device__ __forceinline__ void stage(unsigned char* s_q, const BuildArgs& a, int b, int kvh, int r0,
+                                               int nrows) {
+    for (int x = threadIdx.x; x < nrows * kPieces; x += blockDim.x) {
+      const int rr = x / kPieces, pc = x % kPieces, t = r0 + rr;
+      uint4 v = make_uint4(0, 0, 0, 0);
+      if (t < a.R) {
+        const int h = t / a.wr, i = t % a.wr;
+        const T* q = static_cast<const T*>(a.q_obs) + (((size_t)b * a.Hq + kvh * a.G + h) * a.w + i) * D;
+        v = reinterpret_cast<const uint4*>(q)[pc];
+      }
+      *reinterpret_cast<uint4*>(s_q + at(rr, pc)) = v;
     }
-    *reinterpret_cast<uint4*>(s_q + rr * kQRowB + pc * 16) = v;
   }
-}
+  // Fragment of row 16 rt + col: its pieces grp + 4 i lie at
+  // (grp ^ col % 4) + 4 (i ^ (col / 4) % 2), so two addresses (even and odd
+  // i) and constant offsets reach them all.
+  static __device__ __forceinline__ int lane_at(int col, int grp, int odd) {
+    return col * kRowB + ((grp ^ (col & 3)) + 4 * (odd ^ ((col >> 2) & 1))) * 16;
+  }
+  static __device__ __forceinline__ void load(Frag<T, D>& f, const unsigned char* even, const unsigned char* odd) {
+#pragma unroll
+    for (int i = 0; i < Frag<T, D>::kSteps; ++i)
+      f.w[i] = *reinterpret_cast<const typename Frag<T, D>::Word*>((i & 1 ? odd : even) + 128 * (i >> 1));
+  }
+};
 
 // ---------------------------------------------------------------- scoring
 
 // Scoring blocks stream groups of 256 keys one after the other (the lse pass
-// 4, 8 or 16 groups per block as the plan chooses, the score pass 4); in each
-// group a wave owns 64 keys and runs over every window row. The window rows
-// are staged in LDS once per block, RC at a time: every row chunk loads the
-// block's keys again, so with more than 128 rows (G w = 224, 256) the wide
-// chunk of 256 rows reads each key once per pass, at two blocks per CU.
+// 4, 8 or 16 groups per chunk, the score pass 4 or 1 per block, as the plan
+// chooses); in each group a wave owns 64 keys and runs over every window row.
+// The window rows are staged in LDS once per block, RC at a time: every row
+// chunk loads the block's keys again, so with more than 128 rows (G w = 224,
+// 256) the wide chunk of 256 rows reads each key once per pass.
 
 // Key fragments of the 64 keys from kw (clamped to the sequence).
 template <typename T, int D>
@@ -165,37 +179,56 @@ __device__ __forceinline__ void load_score_keys(Frag<T, D> (&f)[4], const T* K, 
 
 // lse pass: the MFMA is oriented keys x rows, C[key][row]: a lane holds 16
 // keys of one row, so a row's max and sum need only two cross-lane steps.
-// Each wave keeps a running (max, sum) per row over its key groups. A wave
-// holds one 64-key group at a time (no second key buffer): at three waves
-// per SIMD (bf16) the other blocks on the CU cover its load latency.
-template <typename T, int D, int RC>
-__global__ __launch_bounds__(kThreads, (RC > kRowChunk ? 2 : sizeof(T) == 2 ? 3 : 2)) void lse_partial(BuildArgs a) {
-  const int ch = blockIdx.x, kvh = blockIdx.y, b = blockIdx.z;
+// A chunk is four waves, each keeping a running (max, sum) per row over its
+// key groups, one 64-key group at a time (no second key buffer): the other
+// waves of the SIMD hide its key loads and the chain max -> exponentials ->
+// sum of a row tile. Bound by issue: MFMA and VALU instructions take turns on
+// a SIMD here, and a row tile of 64 keys costs 16 MFMAs (17 cycles each), 17
+// exponentials (9) and about 60 other VALU operations (4). Variants, none of
+// which changes a row's arithmetic:
+//   kRQ = 2, wide row chunk: two copies of a chunk's waves deal its row tiles
+//   between them, so two blocks of eight waves share a CU's LDS and 128
+//   registers give four waves per SIMD (28 query heads, 64 ragged contexts of
+//   4K-64K tokens, window 32: 239 -> 214 us);
+//   kRQ = 1, up to 128 rows: three waves per SIMD;
+//   kSplit: a block takes one of the chunk's row chunks, for fp32 where the
+//   chunks alone leave most CUs idle (2 heads of 1024 tokens, 64 rows: 28 ->
+//   14 us; bf16 passes that short gained nothing from it).
+template <typename T, int D, int RC, int kRQ, bool kSplit>
+__global__ __launch_bounds__(256 * kRQ, (sizeof(T) == 4 ? 2 : kRQ > 1 ? 4 : 3)) void lse_partial(BuildArgs a) {
+  constexpr int NT = 256 * kRQ;
+  const int kvh = blockIdx.y, b = blockIdx.z;
   const int bh = b * a.Hkv + kvh;
   const HeadMeta hm = a.meta[bh];
-  const int k0 = ch * 256 * a.LG;
-  if (hm.all_main || k0 >= hm.s) return;
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const int span = 256 * a.LG;  // keys per chunk
+  const int nrs = kSplit ? (a.R + RC - 1) / RC : 1;  // blocks that share a chunk's row chunks
+  const int ch = blockIdx.x / nrs, rs = blockIdx.x - ch * nrs;
+  if (hm.all_main || ch * span >= hm.s) return;
+  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int col = lane & 15, grp = lane >> 4;
-  constexpr int kQRowB = D * (int)sizeof(T) + 16;
-  __shared__ __align__(16) unsigned char s_q[RC * kQRowB];
+  const int vw = wave & 3, rq = wave >> 2;  // wave of the chunk, its share of the row tiles
+  const int k0 = ch * span + 64 * vw;       // this wave's first key
+  using Rows = WindowRows<T, D>;
+  __shared__ __align__(16) unsigned char s_q[RC * Rows::kRowB];
   __shared__ float2 s_ml[4][RC];
+  const unsigned char *q_even = s_q + Rows::lane_at(col, grp, 0), *q_odd = s_q + Rows::lane_at(col, grp, 1);
   const T* K = static_cast<const T*>(a.k) + (size_t)bh * a.S * D;
-  for (int r0 = 0; r0 < a.R; r0 += RC) {
+  for (int r0 = rs * RC; r0 < a.R; r0 += nrs * RC) {
     const int nrt = (min(RC, a.R - r0) + 15) / 16;
-    if (r0 > 0) __syncthreads();  // the previous chunk's rows and records are consumed
+    if (r0 >= nrs * RC) __syncthreads();  // the previous chunk's rows and records are consumed
     Frag<T, D> kf[4];
-    load_score_keys<T, D>(kf, K, k0 + 64 * wave, hm.s, col, grp);
-    stage_window_rows<T, D>(s_q, a, b, kvh, r0, 16 * nrt);
+    load_score_keys<T, D>(kf, K, k0, hm.s, col, grp);
+    Rows::stage(s_q, a, b, kvh, r0, 16 * nrt);
     __syncthreads();
     // running (max, sum) of row 16 rt + col over this wave's keys, kept in
     // LDS so the row-tile loop need not be unrolled; the four lane groups
     // hold the same reduced values and each lane reads back its own writes
-    for (int rt = 0; rt < nrt; ++rt) s_ml[wave][16 * rt + col] = make_float2(kNegInf, 0.f);
+    for (int rt = rq; rt < nrt; rt += kRQ) s_ml[vw][16 * rt + col] = make_float2(kNegInf, 0.f);
     __builtin_amdgcn_s_waitcnt(kWaitVmcnt0);  // the first group's keys have landed
+    const int last = min(a.LG, (hm.s - k0 + 255) / 256);  // this wave's groups that hold keys (may be none)
 #pragma unroll 1
-    for (int gi = 0; gi < a.LG; ++gi) {
-      const int kw = k0 + 256 * gi + 64 * wave;  // this wave's keys in group gi
+    for (int gi = 0; gi < last; ++gi) {
+      const int kw = k0 + 256 * gi;  // this wave's keys in group gi
       if (gi > 0) load_score_keys<T, D>(kf, K, kw, hm.s, col, grp);
       __builtin_amdgcn_sched_barrier(0);  // the group's key loads go out before its work
       // keys up to s - w are visible to every window row (and lie below s):
@@ -203,11 +236,13 @@ __global__ __launch_bounds__(kThreads, (RC > kRowChunk ? 2 : sizeof(T) == 2 ? 3 
       auto rows = [&](auto full_tag) {
         constexpr bool kFull = decltype(full_tag)::value;
 #pragma unroll 1
-        for (int rt = 0; rt < nrt; ++rt) {
-          const int t_row = r0 + 16 * rt + col;  // window row of this lane's column
+        for (int rt = rq; rt < nrt; rt += kRQ) {
+          const int row = 16 * rt + col;  // window row of this lane's column
+          const float2 st = s_ml[vw][row];
           Frag<T, D> qf;
-          qf.load(reinterpret_cast<const T*>(s_q + (16 * rt + col) * kQRowB), grp);
-          const int pos = t_row < a.R ? hm.s - a.w + t_row % a.wr : -1;
+          Rows::load(qf, q_even + rt * 16 * Rows::kRowB, q_odd + rt * 16 * Rows::kRowB);
+          int pos = 0;
+          if constexpr (!kFull) pos = r0 + row < a.R ? hm.s - a.w + (r0 + row) % a.wr : -1;
           // raw logits; the scale is positive, so the max commutes with it
           float v[16];
           float m = kNegInf;
@@ -222,28 +257,24 @@ __global__ __launch_bounds__(kThreads, (RC > kRowChunk ? 2 : sizeof(T) == 2 ? 3 
               m = fmaxf(m, x);
             }
           }
-          m = wave_xor_max(m, 16);
-          m = wave_xor_max(m, 32);
+          m = rows4_max(m);
           m = m == kNegInf ? kNegInf : m * a.scale2;
-          const float2 st = s_ml[wave][16 * rt + col];
           const float m_new = fmaxf(st.x, m);
-          if (m_new == kNegInf) continue;
+          const bool none = m_new == kNegInf;  // no key seen yet: the state stays
+          const float ref = none ? 0.f : m_new;
           float l = 0.f;
 #pragma unroll
-          for (int j = 0; j < 16; ++j) l += fast_exp2(fmaf(v[j], a.scale2, -m_new));
-          l = wave_xor_add(l, 16);
-          l = wave_xor_add(l, 32);
-          s_ml[wave][16 * rt + col] = make_float2(m_new, fmaf(st.y, fast_exp2(st.x - m_new), l));
+          for (int j = 0; j < 16; ++j) l += fast_exp2(fmaf(v[j], a.scale2, -ref));
+          l = rows4_sum(l);
+          s_ml[vw][row] = make_float2(m_new, none ? st.y : fmaf(st.y, fast_exp2(st.x - ref), l));
         }
       };
-      if (kw < hm.s) {  // wave-uniform
-        if (kw + 64 <= hm.s - a.w + 1) rows(std::true_type{});
-        else rows(std::false_type{});
-      }
-
+      if (kw + 64 <= hm.s - a.w + 1) rows(std::true_type{});
+      else rows(std::false_type{});
     }
     __syncthreads();
-    for (int t = threadIdx.x; t < min(RC, a.R - r0); t += kThreads) {
+    // per row, the four waves' states into one record
+    for (int t = threadIdx.x; t < min(RC, a.R - r0); t += NT) {
       float M = kNegInf;
 #pragma unroll
       for (int w = 0; w < 4; ++w) M = fmaxf(M, s_ml[w][t].x);
@@ -260,6 +291,8 @@ __global__ __launch_bounds__(kThreads, (RC > kRowChunk ? 2 : sizeof(T) == 2 ? 3 
   }
 }
 
+// One thread per row: the chunk records merged in chunk order, requested 16 at
+// a time (bound by their latency: one at a time, 32 chunks took 15 us).
 __global__ __launch_bounds__(kThreads) void lse_final(BuildArgs a) {
   const int kvh = blockIdx.y, b = blockIdx.z;
   const int bh = b * a.Hkv + kvh;
@@ -268,12 +301,24 @@ __global__ __launch_bounds__(kThreads) void lse_final(BuildArgs a) {
   if (hm.all_main || t >= a.R) return;
   const int nch = (hm.s + 256 * a.LG - 1) / (256 * a.LG);
   const float2* pp = a.lse_part + (size_t)bh * a.NCH * a.R + t;
+  constexpr int kB = 16;
+  float2 e[kB];
+  auto read = [&](int c0) {
+#pragma unroll
+    for (int u = 0; u < kB; ++u) e[u] = c0 + u < nch ? pp[(size_t)(c0 + u) * a.R] : make_float2(kNegInf, 0.f);
+  };
   float M = kNegInf;
-  for (int c = 0; c < nch; ++c) M = fmaxf(M, pp[(size_t)c * a.R].x);
+  for (int c0 = 0; c0 < nch; c0 += kB) {
+    read(c0);
+#pragma unroll
+    for (int u = 0; u < kB; ++u) M = fmaxf(M, e[u].x);
+  }
   float L = 0.f;
-  for (int c = 0; c < nch; ++c) {
-    const float2 e = pp[(size_t)c * a.R];
-    if (e.x != kNegInf) L = fmaf(e.y, exp2f(e.x - M), L);
+  for (int c0 = 0; c0 < nch; c0 += kB) {
+    if (nch > kB) read(c0);
+#pragma unroll
+    for (int u = 0; u < kB; ++u)
+      if (e[u].x != kNegInf) L = fmaf(e[u].y, exp2f(e[u].x - M), L);
   }
   a.lse2[(size_t)bh * a.R + t] = M + log2f(L);
 }
@@ -281,54 +326,60 @@ __global__ __launch_bounds__(kThreads) void lse_final(BuildArgs a) {
 // Score pass: C[row][key]: a lane holds one key of 4 rows, so the per-key
 // sums stay in registers until two final cross-lane steps, and no cross-wave
 // merge is needed. One key group per wave at a time and a rolled row-tile
-// loop keep it at four waves per SIMD (bf16).
-template <typename T, int D, int RC>
-__global__ __launch_bounds__(kThreads, (RC > kRowChunk ? 2 : sizeof(T) == 2 ? 4 : 2)) void score_accum(BuildArgs a, int rev) {
-  const int ch = blockIdx.x;
+// loop keep it at four waves per SIMD (bf16); with the wide row chunk two
+// blocks of eight waves (NT = 512) share a CU (32 heads of 128K tokens, 256
+// rows: 413 -> 323 us with four waves per SIMD instead of two). Bound by issue
+// like the lse pass: 16 MFMAs, 16 exponentials and about 45 other VALU
+// operations per row tile of 64 keys, and by the keys' HBM reads at 128 rows.
+template <typename T, int D, int RC, int NT>
+__global__ __launch_bounds__(NT, (sizeof(T) == 2 ? 4 : 2)) void score_accum(BuildArgs a, int rev) {
   int b, kvh, bh;
   block_head(a, rev, b, kvh, bh);
   const HeadMeta hm = a.meta[bh];
-  const int k0 = ch * kKeyChunk;
+  const int k0 = blockIdx.x * 256 * a.KG;
   if (hm.all_main || k0 >= hm.n_sc) return;
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int col = lane & 15, grp = lane >> 4;
-  constexpr int kQRowB = D * (int)sizeof(T) + 16;
-  constexpr int kRT = RC / 16;
-  __shared__ __align__(16) unsigned char s_q[RC * kQRowB];
-  __shared__ float s_lse[RC];
+  using Rows = WindowRows<T, D>;
+  __shared__ __align__(16) unsigned char s_q[RC * Rows::kRowB];
+  __shared__ __align__(16) float s_lse[RC];
+  const unsigned char *q_even = s_q + Rows::lane_at(col, grp, 0), *q_odd = s_q + Rows::lane_at(col, grp, 1);
   const T* K = static_cast<const T*>(a.k) + (size_t)bh * a.S * D;
   for (int r0 = 0; r0 < a.R; r0 += RC) {
-    const int nr = min(RC, a.R - r0), nrt = (nr + 15) / 16;
+    const int nrt = (min(RC, a.R - r0) + 15) / 16;
     if (r0 > 0) __syncthreads();  // the previous chunk's rows are consumed
     Frag<T, D> kf[4];
     load_score_keys<T, D>(kf, K, k0 + 64 * wave, hm.s, col, grp);
-    stage_window_rows<T, D>(s_q, a, b, kvh, r0, 16 * nrt);
-    for (int t = threadIdx.x; t < nr; t += kThreads) s_lse[t] = a.lse2[(size_t)bh * a.R + r0 + t];
+    Rows::stage(s_q, a, b, kvh, r0, 16 * nrt);
+    // padded rows carry lse = +inf and add 0
+    for (int t = threadIdx.x; t < 16 * nrt; t += NT)
+      s_lse[t] = r0 + t < a.R ? a.lse2[(size_t)bh * a.R + r0 + t] : __builtin_huge_valf();
     __syncthreads();
     __builtin_amdgcn_s_waitcnt(kWaitVmcnt0);  // the first group's keys have landed
 #pragma unroll 1
-    for (int gi = 0; gi < kKeyGroups; ++gi) {
-      const int kw = k0 + 256 * gi + 64 * wave;  // this wave's keys in group gi
-      if (gi > 0) load_score_keys<T, D>(kf, K, kw, hm.s, col, grp);
+    for (int kg = 0; kg < 256 * a.KG; kg += NT) {
+      const int kw = k0 + kg + 64 * wave;  // this wave's keys
+      if (kw >= hm.n_sc || kg + 64 * wave >= 256 * a.KG) break;  // wave-uniform
+      if (kg > 0) load_score_keys<T, D>(kf, K, kw, hm.s, col, grp);
       __builtin_amdgcn_sched_barrier(0);  // the group's key loads go out before its work
       float ksum[4] = {0.f, 0.f, 0.f, 0.f};
       // keys up to s - w are visible to every window row: such waves skip the
-      // per-element causal test (padded rows carry lse = +inf and add 0)
+      // per-element causal test
       auto rows = [&](auto full_tag) {
         constexpr bool kFull = decltype(full_tag)::value;
 #pragma unroll 1
-        for (int rt = 0; rt < kRT; ++rt) {
-          if (rt >= nrt) break;
+        for (int rt = 0; rt < nrt; ++rt) {
           Frag<T, D> qf;
-          qf.load(reinterpret_cast<const T*>(s_q + (16 * rt + col) * kQRowB), grp);
-          float lse[4];
+          Rows::load(qf, q_even + rt * 16 * Rows::kRowB, q_odd + rt * 16 * Rows::kRowB);
+          const float4 l4 = *reinterpret_cast<const float4*>(s_lse + 16 * rt + 4 * grp);
+          const float lse[4] = {l4.x, l4.y, l4.z, l4.w};
           int pos[4];
+          if constexpr (!kFull)
 #pragma unroll
-          for (int i = 0; i < 4; ++i) {
-            const int tl = 16 * rt + 4 * grp + i, t = r0 + tl;
-            lse[i] = t < a.R ? s_lse[tl] : __builtin_huge_valf();
-            pos[i] = t < a.R ? hm.s - a.w + t % a.wr : -1;  // padded rows see no key
-          }
+            for (int i = 0; i < 4; ++i) {
+              const int t = r0 + 16 * rt + 4 * grp + i;
+              pos[i] = t < a.R ? hm.s - a.w + t % a.wr : -1;  // padded rows see no key
+            }
 #pragma unroll
           for (int t = 0; t < 4; ++t) {
             const f32x4_t c = mma<D>(qf, kf[t], zero4());
@@ -341,23 +392,18 @@ __global__ __launch_bounds__(kThreads, (RC > kRowChunk ? 2 : sizeof(T) == 2 ? 4 
           }
         }
       };
-      if (kw < hm.n_sc) {  // wave-uniform
-        if (kw + 64 <= hm.s - a.w + 1) rows(std::true_type{});
-        else rows(std::false_type{});
+      if (kw + 64 <= hm.s - a.w + 1) rows(std::true_type{});
+      else rows(std::false_type{});
 #pragma unroll
-        for (int t = 0; t < 4; ++t) {
-          float v = ksum[t];
-          v = wave_xor_add(v, 16);
-          v = wave_xor_add(v, 32);
-          const int p = kw + 16 * t + col;
-          if (grp == 0 && p < hm.n_sc) {
-            float* dst = a.raw + (size_t)bh * a.S + p;
-            if (r0 == 0) *dst = v;
-            else *dst += v;  // later row chunks add to this lane's own sums
-          }
+      for (int t = 0; t < 4; ++t) {
+        const float v = rows4_sum(ksum[t]);
+        const int p = kw + 16 * t + col;
+        if (grp == 0 && p < hm.n_sc) {
+          float* dst = a.raw + (size_t)bh * a.S + p;
+          if (r0 == 0) *dst = v;
+          else *dst += v;  // later row chunks add to this lane's own sums
         }
       }
-
     }
   }
 }
@@ -1684,7 +1730,7 @@ BuildArgs make_args(const BuildPlan& pl, const void* k, const void* v, const voi
   a.sel_cnt = reinterpret_cast<int32_t*>(ws + pl.off_selc);
   a.NSEL = pl.NSEL;
   a.B = pl.B; a.Hq = pl.Hq; a.Hkv = pl.Hkv; a.G = pl.G; a.C = pl.C; a.Rcap = pl.Rcap; a.S = pl.S; a.w = pl.w;
-  a.wr = pl.wr; a.pool_half = pl.pool_half; a.R = pl.R; a.LG = pl.LG; a.NCH = pl.NCH; a.NBLK = pl.NBLK; a.T = pl.T;
+  a.wr = pl.wr; a.pool_half = pl.pool_half; a.R = pl.R; a.LG = pl.LG; a.KG = pl.KG; a.NCH = pl.NCH; a.NBLK = pl.NBLK; a.T = pl.T;
   a.cap_slots = pl.C;
   a.scale2 = kLog2e / sqrtf((float)pl.D);
   return a;
@@ -1692,26 +1738,38 @@ BuildArgs make_args(const BuildPlan& pl, const void* k, const void* v, const voi
 
 #define RESKV_CHECK() do { e = hipGetLastError(); if (e != hipSuccess) return e; } while (0)
 
-// The two scoring passes with RC window rows per chunk.
-template <typename T, int D, int RC>
-hipError_t launch_score_passes(const BuildPlan& pl, const BuildArgs& a, hipStream_t st) {
-  auto grid = [&](int x) { return dim3(x < 1 ? 1 : x, pl.Hkv, pl.B); };
-  hipError_t e;
-  hipLaunchKernelGGL((lse_partial<T, D, RC>), grid(pl.NCH), dim3(kThreads), 0, st, a); RESKV_CHECK();
-  hipLaunchKernelGGL(lse_final, grid((pl.R + kThreads - 1) / kThreads), dim3(kThreads), 0, st, a); RESKV_CHECK();
-  // the second pass over the keys walks the heads in reverse (cache reuse)
-  hipLaunchKernelGGL((score_accum<T, D, RC>), grid(pl.NSC), dim3(kThreads), 0, st, a, 1); RESKV_CHECK();
-  return hipSuccess;
-}
-
-// Raw window scores of every scored position (lse, then weights summed).
-// The wide chunk only at bf16 rows or rows of 64 (fp32 rows of 128 would
-// hold one block per CU).
+// Raw window scores of every scored position: the log-sum-exp per window row,
+// then the normalised weights summed. Which shapes: up to 128 rows one chunk
+// of rows; more than 128 the wide chunk, at bf16 rows or rows of 64 (fp32 rows
+// of 128 would hold one block per CU); and for fp32 the lse pass's rows dealt
+// to blocks 16 at a time where the chunks alone give a CU under two blocks.
 template <typename T, int D>
 hipError_t launch_scores_typed(const BuildPlan& pl, const BuildArgs& a, hipStream_t st) {
-  if constexpr (sizeof(T) == 2 || D == 64)
-    if (pl.R > kRowChunk) return launch_score_passes<T, D, kRowChunkWide>(pl, a, st);
-  return launch_score_passes<T, D, kRowChunk>(pl, a, st);
+  auto grid = [&](int x) { return dim3(x < 1 ? 1 : x, pl.Hkv, pl.B); };
+  hipError_t e;
+  const dim3 gf = grid((pl.R + kThreads - 1) / kThreads);
+  const bool few = (size_t)pl.B * pl.Hkv * pl.NCH < kFewChunks;
+  constexpr bool kBf = sizeof(T) == 2;
+  const bool wide = (kBf || D == 64) && pl.R > kRowChunk;
+  if constexpr (!kBf)
+    if (few)
+      hipLaunchKernelGGL((lse_partial<T, D, 16, 1, true>), grid(pl.NCH * ((pl.R + 15) / 16)), dim3(256), 0, st, a);
+  if constexpr (kBf || D == 64)
+    if (wide && (kBf || !few))
+      hipLaunchKernelGGL((lse_partial<T, D, kRowChunkWide, 2, false>), grid(pl.NCH), dim3(512), 0, st, a);
+  if (!wide && (kBf || !few))
+    hipLaunchKernelGGL((lse_partial<T, D, kRowChunk, 1, false>), grid(pl.NCH), dim3(256), 0, st, a);
+  RESKV_CHECK();
+  hipLaunchKernelGGL(lse_final, gf, dim3(kThreads), 0, st, a); RESKV_CHECK();
+  // the second pass over the keys walks the heads in reverse (cache reuse)
+  if constexpr (kBf || D == 64)
+    if (wide) {
+      hipLaunchKernelGGL((score_accum<T, D, kRowChunkWide, 512>), grid(pl.NSC), dim3(512), 0, st, a, 1);
+      RESKV_CHECK();
+      return hipSuccess;
+    }
+  hipLaunchKernelGGL((score_accum<T, D, kRowChunk, 256>), grid(pl.NSC), dim3(256), 0, st, a, 1); RESKV_CHECK();
+  return hipSuccess;
 }
 
 // Pooling, selection, gather and the Lloyd rounds of one candidate.
@@ -1828,7 +1886,8 @@ bool layout_build_plan(BuildPlan* plan) {
       break;
     }
   pl.NCH = (pl.max_s + 256 * pl.LG - 1) / (256 * pl.LG);
-  pl.NSC = (pl.max_s + kKeyChunk - 1) / kKeyChunk;
+  pl.KG = BH * (size_t)((pl.max_s + 256 * kKeyGroups - 1) / (256 * kKeyGroups)) < kFewChunks ? 1 : kKeyGroups;
+  pl.NSC = (pl.max_s + 256 * pl.KG - 1) / (256 * pl.KG);
   pl.NBLK = (pl.max_E + kTokBlock - 1) / kTokBlock;
   if (pl.NBLK < 1) pl.NBLK = 1;
   pl.NSEL = (pl.max_s + kSelChunk - 1) / kSelChunk;

@@ -56,6 +56,24 @@ __device__ __forceinline__ float wave_xor_add(float v, int mask) {
   return v + __shfl_xor(v, mask, 64);
 }
 
+// The same butterflies over the four 16-lane rows of a wave on the VALU (no LDS
+// round trip): swapping odd with even rows, then the upper with the lower
+// half, of a register with itself leaves every lane its own and its partner's
+// value, and fp32 add and max are commutative, so the bits are those of the
+// shuffles by 16 and 32. Every lane of the wave must be active.
+__device__ __forceinline__ float rows4_max(float v) {
+  auto a = __builtin_amdgcn_permlane16_swap(__float_as_uint(v), __float_as_uint(v), false, false);
+  v = fmaxf(__uint_as_float(a[0]), __uint_as_float(a[1]));
+  auto b = __builtin_amdgcn_permlane32_swap(__float_as_uint(v), __float_as_uint(v), false, false);
+  return fmaxf(__uint_as_float(b[0]), __uint_as_float(b[1]));
+}
+__device__ __forceinline__ float rows4_sum(float v) {
+  auto a = __builtin_amdgcn_permlane16_swap(__float_as_uint(v), __float_as_uint(v), false, false);
+  v = __uint_as_float(a[0]) + __uint_as_float(a[1]);
+  auto b = __builtin_amdgcn_permlane32_swap(__float_as_uint(v), __float_as_uint(v), false, false);
+  return __uint_as_float(b[0]) + __uint_as_float(b[1]);
+}
+
 // Reductions over the 16 lanes of one DPP row (lanes 16g .. 16g+15) with DPP
 // moves: swap neighbours, swap pairs, mirror within 8, mirror within 16. Each
 // step combines a lane with a partner that holds the same partial set size,
@@ -99,7 +117,8 @@ struct Frag;
 template <int D>
 struct Frag<uint16_t, D> {        // bf16: 16x16x32 steps, 8 elements per step
   static constexpr int kSteps = D / 32;
-  uint4 w[kSteps];
+  using Word = uint4;
+  Word w[kSteps];
   __device__ __forceinline__ void load(const uint16_t* row, int grp) {
 #pragma unroll
     for (int i = 0; i < kSteps; ++i) w[i] = *reinterpret_cast<const uint4*>(row + 8 * grp + 32 * i);
@@ -117,7 +136,8 @@ struct Frag<uint16_t, D> {        // bf16: 16x16x32 steps, 8 elements per step
 template <int D>
 struct Frag<float, D> {           // fp32: 16x16x4 steps, 1 element per step
   static constexpr int kSteps = D / 16;  // float4 groups
-  float4 w[kSteps];
+  using Word = float4;
+  Word w[kSteps];
   __device__ __forceinline__ void load(const float* row, int grp) {
 #pragma unroll
     for (int i = 0; i < kSteps; ++i) w[i] = *reinterpret_cast<const float4*>(row + 4 * grp + 16 * i);

@@ -83,6 +83,7 @@ struct BuildPlan {
   int R;      // scoring rows per kv head, G * wr
   int LG;     // 256-key groups per lse block
   int NCH;    // lse key chunks (256 * LG keys) of the longest sequence
+  int KG;     // 256-key groups per score-pass block
   int NSC;    // score-pass key chunks of the longest sequence
   int NBLK;   // 256-token blocks of the largest evicted set
   int NSEL;   // selection blocks (8192 scores each) of the longest sequence

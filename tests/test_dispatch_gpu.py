@@ -42,3 +42,21 @@ def test_lloyd_sort_and_pieces(dtype, d, evicted, res, budget):
     got = run_build(wl, x)
     for h in range(2):
         check_head(wl, x, got, 0, h)
+
+
+@pytest.mark.parametrize("dtype,d,G,window,s", [
+    ("bf16", 128, 7, 19, 1100),   # 133 rows: the wide row chunk, a short last row tile
+    ("bf16", 64, 8, 32, 1025),    # 256 rows: the wide chunk exactly full
+    ("bf16", 128, 8, 33, 700),    # 264 rows: a second row chunk
+    ("f32", 64, 8, 17, 1030),     # fp32: rows dealt to blocks 16 at a time, 136 rows
+    ("f32", 128, 5, 27, 515),     # fp32 rows of 128: 135 rows, two row chunks in the score pass
+])
+def test_scoring_row_chunks(dtype, d, G, window, s):
+    """Window row counts around the row chunks of the scoring passes, short
+    contexts whose last chunk is ragged."""
+    wl = synth.tiny_workload(s=s, d=d, hq=2 * G, hkv=2, budget=80, res=0, window=window, dtype=dtype, n_heavy=5)
+    wl.res = np.asarray((16, 5), np.int64).reshape(1, 1, 2)
+    x = host_copies(synth.gen_layer(wl, 0, seed=window, n_decode=1))
+    got = run_build(wl, x)
+    for h in range(2):
+        check_head(wl, x, got, 0, h)
