@@ -10,14 +10,14 @@
 //   score_accum    recomputes the logits; raw[p] = sum over rows of the
 //                  normalised weight of key p, for the scored positions
 //   pool_scores    centred zero-padded sum (5 taps by default) over the
-//                  scored positions
+//                  scored positions, and the selection's first radix pass
 //   [adakv_alloc]  with cross-head allocation only: moves top-k budget
 //                  between the KV heads of a sequence (one ranking of all
 //                  heads' scores, per-head safeguard floor and slot cap) and
 //                  rewrites each head's sizes before the selection
-//   select_hist x4 radix select (4 x 8-bit digits of the fp32 bit pattern) of
-//   select_count   the k_top-th and (k_top + r')-th largest score over blocks
-//   select_write   of 8192 scores; ties at a threshold go to the lower
+//   select_hist x2 radix select (11, 11 and 10 bits of the fp32 bit pattern)
+//   select_write   of the k_top-th and (k_top + r')-th largest score over blocks
+//                  of 8192 scores; ties at a threshold go to the lower
 //                  position. Stable compaction writes main_idx (top-k, then
 //                  the protected window), the evicted list E and the Lloyd
 //                  seeds, all ascending
@@ -64,7 +64,8 @@ constexpr int kTokBlock = 256;     // evicted tokens per counting-sort block (hi
 constexpr int kSelThreads = 1024;
 constexpr int kSelPer = 8;                          // scores per selection thread
 constexpr int kSelChunk = kSelPer * kSelThreads;   // scores per selection block
-constexpr int kSelHist = 4 * 2 * 256;              // selection pass histograms per head: [pass][threshold][digit]
+constexpr int kSelBins = 2048;                     // digits of the wider selection passes
+constexpr int kSelHist = 4 * kSelBins;             // selection pass histograms per head (sel_at)
 constexpr int kAdaThreads = 1024;
 constexpr int kPieceMin = 4096;                     // update pieces of 1024 members from which they are not cut smaller
 
@@ -99,9 +100,9 @@ struct BuildArgs {
   int32_t* nitem;      // [BH]
   int32_t* parrive;    // [BH][Rcap] pieces of a split group that have left their sums
   double* part;        // [BH][NPART][2][D] key and value sums of split groups' pieces
-  int32_t* sel_hist;   // [BH][4][2][256] selection pass histograms (zeroed by pool_scores)
-  int32_t* sel_cnt;    // [BH][NSEL][4] per selection block: above / equal to each threshold
-  int B, Hq, Hkv, G, C, Rcap, S, w, R, LG, KG, NCH, NBLK, NSEL, T;
+  int32_t* sel_hist;   // [BH][kSelHist] selection pass histograms (zeroed by lse_final and, for the next candidate, gather_init)
+  uint32_t* sel_state; // [BH][2][4] thresholds' prefixes and remaining ranks after the first and second pass
+  int B, Hq, Hkv, G, C, Rcap, S, w, R, LG, KG, NCH, NBLK, T;
   int lpiece, NIT, NPART;  // log2 of the members per update piece, pieces and partial slots per head
   int wr;              // leading window rows per query head that score (R = G * wr)
   int pool_half;       // pooling taps on each side of a position
@@ -291,6 +292,12 @@ __global__ __launch_bounds__(256 * kRQ, (sizeof(T) == 4 ? 2 : kRQ > 1 ? 4 : 3)) 
   }
 }
 
+// The head's selection histograms start from zero.
+__device__ __forceinline__ void zero_sel_hist(const BuildArgs& a, int bh, int i, int step) {
+  for (int4* h = reinterpret_cast<int4*>(a.sel_hist + (size_t)bh * kSelHist); i < kSelHist / 4; i += step)
+    h[i] = make_int4(0, 0, 0, 0);
+}
+
 // One thread per row: the chunk records merged in chunk order, requested 16 at
 // a time (bound by their latency: one at a time, 32 chunks took 15 us).
 __global__ __launch_bounds__(kThreads) void lse_final(BuildArgs a) {
@@ -298,6 +305,7 @@ __global__ __launch_bounds__(kThreads) void lse_final(BuildArgs a) {
   const int bh = b * a.Hkv + kvh;
   const HeadMeta hm = a.meta[bh];
   const int t = blockIdx.x * kThreads + threadIdx.x;
+  zero_sel_hist(a, bh, t, gridDim.x * kThreads);
   if (hm.all_main || t >= a.R) return;
   const int nch = (hm.s + 256 * a.LG - 1) / (256 * a.LG);
   const float2* pp = a.lse_part + (size_t)bh * a.NCH * a.R + t;
@@ -415,15 +423,49 @@ __global__ __launch_bounds__(NT, (sizeof(T) == 2 ? 4 : 2)) void score_accum(Buil
 // order as the one-position form does.
 constexpr int kPoolPer = 4;
 constexpr int kPoolHalfMax = 15;  // pool_half <= 15 (pool_kernel <= 31)
-__global__ __launch_bounds__(kThreads) void pool_scores(BuildArgs a) {
+constexpr int kPoolThreads = 1024;
+
+// Histogram increment of bin `dig` by the lanes with `act` set. Scores share
+// their leading digits (sign and exponent), so the lanes of a wave often hit
+// one bin: up to two leader rounds count the lanes that share the leader's
+// bin with one atomic each; the remaining lanes add their own. Called by
+// every lane of the wave (act false where a lane has nothing to count).
+__device__ __forceinline__ void wave_hist_add(int* hist, int dig, bool act, int lane) {
+#pragma unroll
+  for (int it = 0; it < 2; ++it) {
+    const unsigned long long m = __ballot(act);
+    if (m == 0ull) return;  // wave-uniform
+    const int leader = __ffsll((long long)m) - 1;
+    const int d = __shfl(dig, leader, 64);
+    const unsigned long long same = __ballot(act && dig == d);
+    if (lane == leader) atomicAdd(&hist[d], __popcll(same));
+    act = act && dig != d;
+  }
+  if (act) atomicAdd(&hist[dig], 1);
+}
+
+// Radix passes of the selection: 11, 11 and 10 bits of the fp32 bit pattern,
+// most significant first. A pass's histograms in the head's sel_hist: one for
+// both thresholds in the first pass, one each in the others.
+__host__ __device__ constexpr int sel_shift(int pass) { return pass == 0 ? 21 : pass == 1 ? 10 : 0; }
+__host__ __device__ constexpr int sel_bins(int pass) { return pass == 2 ? 1024 : kSelBins; }
+__device__ __forceinline__ int sel_at(int pass, int q) {
+  return pass == 0 ? 0 : pass == 1 ? kSelBins * (1 + q) : 3 * kSelBins + 1024 * q;
+}
+
+// The block also counts its scores' leading digits into the head's first
+// selection histogram.
+__global__ __launch_bounds__(kPoolThreads) void pool_scores(BuildArgs a) {
   const int kvh = blockIdx.y, b = blockIdx.z;
   const int bh = b * a.Hkv + kvh;
   const HeadMeta hm = a.meta[bh];
-  if (blockIdx.x == 0)  // the selection's pass histograms start from zero
-    for (int i = threadIdx.x; i < kSelHist; i += kThreads) a.sel_hist[(size_t)bh * kSelHist + i] = 0;
-  const int p0 = (blockIdx.x * kThreads + threadIdx.x) * kPoolPer;
-  if (p0 >= a.S) return;
   const int n = hm.all_main ? 0 : hm.n_sc;
+  const int b0 = blockIdx.x * kPoolThreads * kPoolPer;
+  if (b0 >= n && !a.dbg_scores) return;  // block-uniform
+  __shared__ int s_hist[kSelBins];
+  const int tid = threadIdx.x, lane = tid & 63;
+  for (int i = tid; i < kSelBins; i += kPoolThreads) s_hist[i] = 0;
+  const int p0 = b0 + tid * kPoolPer;
   const int ph = a.pool_half;
   const float* raw = a.raw + (size_t)bh * a.S;
   float w[kPoolPer + 2 * kPoolHalfMax];  // raw[p0 - kPoolHalfMax + i]
@@ -433,10 +475,10 @@ __global__ __launch_bounds__(kThreads) void pool_scores(BuildArgs a) {
     const bool tap = q >= p0 - ph && q < p0 + kPoolPer + ph;
     w[i] = tap && q >= 0 && q < n ? raw[q] : 0.f;
   }
+  __syncthreads();  // the histogram is cleared
 #pragma unroll
   for (int k = 0; k < kPoolPer; ++k) {
     const int p = p0 + k;
-    if (p >= a.S) break;
     float v = -1.f;
     if (p < n) {
       v = 0.f;
@@ -445,8 +487,13 @@ __global__ __launch_bounds__(kThreads) void pool_scores(BuildArgs a) {
         if (j >= -ph && j <= ph) v += w[k + kPoolHalfMax + j];
       a.score[(size_t)bh * a.S + p] = v;
     }
-    if (a.dbg_scores) a.dbg_scores[(size_t)bh * a.S + p] = v;
+    if (a.dbg_scores && p < a.S) a.dbg_scores[(size_t)bh * a.S + p] = v;
+    wave_hist_add(s_hist, __float_as_uint(v) >> sel_shift(0), p < n, lane);
   }
+  __syncthreads();
+  int* gh = a.sel_hist + (size_t)bh * kSelHist;
+  for (int i = tid; i < kSelBins; i += kPoolThreads)
+    if (s_hist[i]) atomicAdd(&gh[i], s_hist[i]);
 }
 
 // -------------------------------------------------------------- selection
@@ -475,205 +522,120 @@ __device__ __forceinline__ I block_excl_scan(I v, I* s_tmp, I& total) {
   return off + x - v;
 }
 
-// Histogram increment of bin `dig` by the lanes with `act` set. Scores share
-// their leading digits (sign and exponent), so the lanes of a wave often hit
-// one bin: up to two leader rounds count the lanes that share the leader's
-// bin with one atomic each; the remaining lanes add their own. Called by
-// every lane of the wave (act false where a lane has nothing to count).
-__device__ __forceinline__ void wave_hist_add(int* hist, int dig, bool act, int lane) {
-#pragma unroll
-  for (int it = 0; it < 2; ++it) {
-    const unsigned long long m = __ballot(act);
-    if (m == 0ull) return;  // wave-uniform
-    const int leader = __ffsll((long long)m) - 1;
-    const int d = __shfl(dig, leader, 64);
-    const unsigned long long same = __ballot(act && dig == d);
-    if (lane == leader) atomicAdd(&hist[d], __popcll(same));
-    act = act && dig != d;
-  }
-  if (act) atomicAdd(&hist[dig], 1);
-}
-
 // Selection runs over blocks of kSelChunk consecutive scores per head, so a
-// head's long score list is spread over many CUs: four radix passes (8-bit
-// digits, most significant first) each add the block's digit histogram of
-// the scores still matching a threshold's prefix into the head's pass
-// histogram; every block of the next kernel replays the digit choices from
-// the completed histograms. Then the blocks count the scores above and equal
-// to each threshold, and finally each block places its scores: the earlier
-// blocks' counts give its output offsets and the tie ranks of its equal
-// scores (ties are taken lowest position first).
+// head's long score list is spread over many CUs: three radix passes (the
+// first inside pool_scores) each add the block's digit histogram of the scores
+// still matching a threshold's prefix into the head's pass histogram; the
+// blocks of the next kernel find the digits from the completed histogram.
+// Finally each block places its scores: the counts of the scores before the
+// block above and equal to each threshold give its output offsets and the tie
+// ranks of its equal scores (ties are taken lowest position first). Short
+// lists are bound by the launches and the chain of digits: 8 heads of 32K
+// scores took 52 us in seven launches (8-bit passes, a count of their own) and
+// take 34 us in these four, 256 heads 185 and 137 us.
 
-// Digit of one threshold in one radix pass from its 256-bin histogram h of
-// the scores matching its prefix, krem = its rank among them: the digit d and
-// the count of scores in higher digits. Run by a whole wave (every lane gets
-// the values).
-__device__ __forceinline__ void radix_digit(const int* h, int krem, int lane, int& d, int& above) {
-  // each lane holds 4 bins in descending digit order; an inclusive scan over
-  // lanes gives the count of scores at or above each digit
-  int c[4], own = 0;
-#pragma unroll
-  for (int v = 0; v < 4; ++v) { c[v] = h[255 - 4 * lane - v]; own += c[v]; }
-  int incl = own;
-#pragma unroll
-  for (int o = 1; o < 64; o <<= 1) {
-    const int y = __shfl_up(incl, o, 64);
-    if (lane >= o) incl += y;
-  }
-  int run = incl - own;  // scores above this lane's first digit
-  int hit_d = -1, hit_acc = 0;
-#pragma unroll
-  for (int v = 0; v < 4; ++v) {
-    if (hit_d < 0 && run + c[v] >= krem) { hit_d = 255 - 4 * lane - v; hit_acc = run; }
-    run += c[v];
-  }
-  // the first lane (highest digits) that reaches krem owns the digit
-  const unsigned long long hit = __ballot(hit_d >= 0);
-  const int src = hit ? __ffsll((long long)hit) - 1 : 63;
-  d = __shfl(hit_d, src, 64);
-  above = __shfl(hit_acc, src, 64);
-  if (!hit) { d = 0; above = __shfl(incl, 63, 64) - h[0]; }
-}
-
-// Prefixes and remaining ranks of both thresholds (k1-th and k2-th largest)
-// after radix passes [0, npass), from the head's completed pass histograms
-// gh; while the two share their prefix one histogram (threshold 0's) served
-// both. Run by a whole wave.
-__device__ __forceinline__ void radix_replay(const int* gh, int npass, int k1, int k2, int lane, uint32_t (&pref)[2],
-                                             int (&krem)[2]) {
-  pref[0] = pref[1] = 0u;
-  krem[0] = k1;
-  krem[1] = k2;
-  for (int p = 0; p < npass; ++p) {
-    const int shift = 24 - 8 * p;
-    const bool shared = krem[0] > 0 && krem[1] > 0 && pref[0] == pref[1];
-#pragma unroll
-    for (int q = 0; q < 2; ++q) {
-      if (krem[q] > 0) {  // wave-uniform
-        int d, above;
-        radix_digit(gh + (p * 2 + (shared ? 0 : q)) * 256, krem[q], lane, d, above);
-        pref[q] |= (uint32_t)d << shift;
-        krem[q] -= above;
-      }
-    }
-  }
-}
-
-// Setup shared by the selection kernels: the head's scored length, the
-// block's first score and the threshold state after `npass` radix passes
-// (replayed by wave 0, then read by every thread; synchronises the block).
+// Threshold state: prefixes of the k1-th and k2-th largest score's bits and
+// the ranks that remain among the scores matching them.
 struct SelState {
-  int n, i0;
-  int k1, k2;
   uint32_t pref[2];
   int krem[2];
 };
-__device__ __forceinline__ void sel_state(const BuildArgs& a, const HeadMeta& hm, int bh, int npass, SelState& st,
-                                          int* s_gh, uint32_t* s_pref, int* s_krem) {
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  st.n = hm.n_sc;
-  st.i0 = blockIdx.x * kSelChunk;
-  st.k1 = hm.k_top;
-  st.k2 = hm.k_top + hm.r_eff;
-  // the completed pass histograms into LDS in one round trip, then replayed
+
+// Both thresholds' digits of pass `pass` from the head's completed histogram:
+// every thread holds two bins in descending digit order, a block scan counts
+// the scores above them, and the bin that reaches the remaining rank is the
+// digit. While the thresholds share their prefix one histogram serves both.
+// Called by every thread of a kSelThreads block.
+__device__ __forceinline__ void sel_digit(const BuildArgs& a, int bh, int pass, SelState& st) {
+  __shared__ unsigned long long s_scan[kSelThreads / 64];
+  __shared__ int s_dig[2], s_above[2];
   const int* gh = a.sel_hist + (size_t)bh * kSelHist;
-  for (int x = threadIdx.x; x < npass * 512; x += blockDim.x) s_gh[x] = gh[x];
-  __syncthreads();
-  if (wave == 0) {
-    uint32_t pf[2];
-    int kr[2];
-    radix_replay(s_gh, npass, st.k1, st.k2, lane, pf, kr);
-    if (lane == 0) {
-      s_pref[0] = pf[0]; s_pref[1] = pf[1];
-      s_krem[0] = kr[0]; s_krem[1] = kr[1];
+  const int tid = threadIdx.x, top = sel_bins(pass) - 1 - 2 * tid;
+  const bool shared = pass == 0 || (st.krem[0] > 0 && st.krem[1] > 0 && st.pref[0] == st.pref[1]);
+  int c[2][2];
+#pragma unroll
+  for (int q = 0; q < 2; ++q) {
+    const int* h = gh + sel_at(pass, shared ? 0 : q);
+    const int2 w = top >= 1 ? *reinterpret_cast<const int2*>(h + top - 1) : make_int2(0, 0);
+    c[q][0] = w.y;
+    c[q][1] = w.x;
+  }
+  if (tid < 2) s_dig[tid] = s_above[tid] = 0;
+  unsigned long long total;
+  const unsigned long long ex = block_excl_scan<kSelThreads>(
+      (unsigned)(c[0][0] + c[0][1]) | (unsigned long long)(unsigned)(c[1][0] + c[1][1]) << 32, s_scan, total);
+#pragma unroll
+  for (int q = 0; q < 2; ++q) {
+    const int above = q == 0 ? (int)(ex & 0xffffffffu) : (int)(ex >> 32), k = st.krem[q];
+    if (k > above && k <= above + c[q][0] + c[q][1]) {  // one thread
+      const bool first = k <= above + c[q][0];
+      s_dig[q] = first ? top : top - 1;
+      s_above[q] = first ? above : above + c[q][0];
     }
   }
   __syncthreads();
-  st.pref[0] = s_pref[0]; st.pref[1] = s_pref[1];
-  st.krem[0] = s_krem[0]; st.krem[1] = s_krem[1];
+#pragma unroll
+  for (int q = 0; q < 2; ++q)
+    if (st.krem[q] > 0) {
+      st.pref[q] |= (uint32_t)s_dig[q] << sel_shift(pass);
+      st.krem[q] -= s_above[q];
+    }
 }
 
-// Radix pass `pass` over one block's scores: digit histograms of the scores
-// matching each threshold's prefix, added into the head's pass histogram
-// (zeroed by pool_scores).
-__global__ __launch_bounds__(kSelThreads) void select_hist(BuildArgs a, int pass) {
+// Four consecutive scores at any position (4-byte aligned).
+__device__ __forceinline__ void load4(uint32_t* u, const uint32_t* p) {
+  typedef uint32_t u32x4 __attribute__((ext_vector_type(4), aligned(4)));
+  const u32x4 w = *reinterpret_cast<const u32x4*>(p);
+#pragma unroll
+  for (int e = 0; e < 4; ++e) u[e] = w[e];
+}
+
+// State after pass 0 or 1, as the kernel after that pass left it.
+__device__ __forceinline__ SelState sel_load(const BuildArgs& a, int bh, int pass) {
+  const uint4 w = *reinterpret_cast<const uint4*>(a.sel_state + ((size_t)bh * 2 + pass) * 4);
+  return SelState{{w.x, w.y}, {(int)w.z, (int)w.w}};
+}
+
+// Radix pass 1 or 2 over one block's scores: the previous pass's digits, then
+// the digit histograms of the scores matching each threshold's prefix, added
+// into the head's pass histogram.
+template <int kPass>
+__global__ __launch_bounds__(kSelThreads) void select_hist(BuildArgs a) {
   const int bh = blockIdx.z * a.Hkv + blockIdx.y;
   const HeadMeta hm = a.meta[bh];
-  if (hm.all_main || (int)blockIdx.x * kSelChunk >= hm.n_sc) return;  // block-uniform
-  __shared__ int s_hist[2][256];
-  __shared__ int s_gh[kSelHist];
-  __shared__ uint32_t s_pref[2];
-  __shared__ int s_krem[2];
+  const int i0 = blockIdx.x * kSelChunk, n = hm.n_sc;
+  if (hm.all_main || i0 >= n) return;  // block-uniform
+  constexpr int kBins = sel_bins(kPass), kShift = sel_shift(kPass);
+  constexpr uint32_t kMask = ~0u << sel_shift(kPass - 1);
+  __shared__ int s_hist[2][kBins];
   const int tid = threadIdx.x, lane = tid & 63;
-  for (int i = tid; i < 512; i += kSelThreads) (&s_hist[0][0])[i] = 0;
-  SelState st;
-  sel_state(a, hm, bh, pass, st, s_gh, s_pref, s_krem);  // synchronises the block
-  if (st.krem[0] <= 0 && st.krem[1] <= 0) return;  // block-uniform
-  const bool shared = st.krem[0] > 0 && st.krem[1] > 0 && st.pref[0] == st.pref[1];
-  const int shift = 24 - 8 * pass;
-  const uint32_t mask = pass == 0 ? 0u : ~0u << (32 - 8 * pass);
   const uint32_t* key = reinterpret_cast<const uint32_t*>(a.score + (size_t)bh * a.S);
   uint32_t u[kSelPer];
 #pragma unroll
   for (int v = 0; v < kSelPer; ++v) {  // coalesced, all loads in flight together
-    const int i = st.i0 + v * kSelThreads + tid;
-    u[v] = i < st.n ? key[i] : 0u;
+    const int i = i0 + v * kSelThreads + tid;
+    u[v] = i < n ? key[i] : 0u;
   }
+  for (int i = tid; i < 2 * kBins; i += kSelThreads) (&s_hist[0][0])[i] = 0;
+  SelState st = kPass == 1 ? SelState{{0u, 0u}, {hm.k_top, hm.k_top + hm.r_eff}} : sel_load(a, bh, 0);
+  sel_digit(a, bh, kPass - 1, st);  // synchronises the block
+  if (blockIdx.x == 0 && tid == 0)
+    *reinterpret_cast<uint4*>(a.sel_state + ((size_t)bh * 2 + kPass - 1) * 4) =
+        make_uint4(st.pref[0], st.pref[1], (uint32_t)st.krem[0], (uint32_t)st.krem[1]);
+  if (st.krem[0] <= 0 && st.krem[1] <= 0) return;  // block-uniform
+  const bool shared = st.krem[0] > 0 && st.krem[1] > 0 && st.pref[0] == st.pref[1];
 #pragma unroll
   for (int v = 0; v < kSelPer; ++v) {
-    const bool in = st.i0 + v * kSelThreads + tid < st.n;
-    const int dig = (u[v] >> shift) & 0xff;
-    wave_hist_add(s_hist[0], dig, in && st.krem[0] > 0 && (u[v] & mask) == st.pref[0], lane);
-    if (!shared) wave_hist_add(s_hist[1], dig, in && st.krem[1] > 0 && (u[v] & mask) == st.pref[1], lane);
+    const bool in = i0 + v * kSelThreads + tid < n;
+    const int dig = (u[v] >> kShift) & (kBins - 1);
+    wave_hist_add(s_hist[0], dig, in && st.krem[0] > 0 && (u[v] & kMask) == st.pref[0], lane);
+    if (!shared) wave_hist_add(s_hist[1], dig, in && st.krem[1] > 0 && (u[v] & kMask) == st.pref[1], lane);
   }
   __syncthreads();
-  int* gh = a.sel_hist + (size_t)bh * kSelHist + pass * 512;
-  for (int x = tid; x < 512; x += kSelThreads) {
+  int* gh = a.sel_hist + (size_t)bh * kSelHist + sel_at(kPass, 0);
+  for (int x = tid; x < 2 * kBins; x += kSelThreads) {
     const int c = (&s_hist[0][0])[x];
     if (c) atomicAdd(&gh[x], c);
-  }
-}
-
-// Thresholds T_q = the final prefixes; krem[q] = how many scores equal to
-// T_q are taken (lowest positions first); a threshold with k = 0 takes none.
-// Per block: scores above and equal to each threshold.
-__global__ __launch_bounds__(kSelThreads) void select_count(BuildArgs a) {
-  const int bh = blockIdx.z * a.Hkv + blockIdx.y;
-  const HeadMeta hm = a.meta[bh];
-  if (hm.all_main || (int)blockIdx.x * kSelChunk >= hm.n_sc) return;  // block-uniform
-  __shared__ int s_gh[kSelHist];
-  __shared__ uint32_t s_pref[2];
-  __shared__ int s_krem[2];
-  SelState st;
-  sel_state(a, hm, bh, 4, st, s_gh, s_pref, s_krem);
-  const int tid = threadIdx.x;
-  const uint32_t* key = reinterpret_cast<const uint32_t*>(a.score + (size_t)bh * a.S);
-  int c[4] = {0, 0, 0, 0};  // above T1, equal T1, above T2, equal T2
-#pragma unroll
-  for (int v = 0; v < kSelPer; ++v) {
-    const int i = st.i0 + v * kSelThreads + tid;
-    if (i < st.n) {
-      const uint32_t u = key[i];
-      c[0] += u > st.pref[0]; c[1] += u == st.pref[0];
-      c[2] += u > st.pref[1]; c[3] += u == st.pref[1];
-    }
-  }
-  // block sums: across each wave, then the waves' partials in LDS
-  __shared__ int s_part[kSelThreads / 64][4];
-  const int lane = tid & 63, wave = tid >> 6;
-#pragma unroll
-  for (int q = 0; q < 4; ++q) {
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1) c[q] += __shfl_xor(c[q], o, 64);
-  }
-  if (lane == 0)
-#pragma unroll
-    for (int q = 0; q < 4; ++q) s_part[wave][q] = c[q];
-  __syncthreads();
-  if (tid < 4) {
-    int t = 0;
-    for (int w = 0; w < kSelThreads / 64; ++w) t += s_part[w][tid];
-    a.sel_cnt[((size_t)bh * a.NSEL + blockIdx.x) * 4 + tid] = t;
   }
 }
 
@@ -699,38 +661,67 @@ __global__ __launch_bounds__(kSelThreads) void select_write(BuildArgs a) {
   if (blk == 0)
     for (int i = tid; i < hm.P; i += kSelThreads) main_idx[hm.k_top + i] = hm.n_sc + i;
   if (blk * kSelChunk >= hm.n_sc) return;  // block-uniform
-  __shared__ int s_gh[kSelHist];
-  __shared__ uint32_t s_pref[2];
-  __shared__ int s_krem[2];
   __shared__ int s_tmp[kSelThreads / 64];
-  SelState st;
-  sel_state(a, hm, bh, 4, st, s_gh, s_pref, s_krem);
+  __shared__ unsigned long long s_cnt[2][kSelThreads / 64];
+  const int n = hm.n_sc, i0 = blk * kSelChunk;
+  const uint32_t* key = reinterpret_cast<const uint32_t*>(a.score + (size_t)bh * a.S);
+  const int lo = i0 + tid * kSelPer;
+  uint32_t seg[kSelPer];
+  if (lo + kSelPer <= n) {
+#pragma unroll
+    for (int v = 0; v < kSelPer; v += 4) load4(seg + v, key + lo + v);
+  } else {
+#pragma unroll
+    for (int v = 0; v < kSelPer; ++v) seg[v] = lo + v < n ? key[lo + v] : 0u;
+  }
+  // Thresholds T_q = the final prefixes; krem[q] = how many scores equal to
+  // T_q are taken (lowest positions first); a threshold with k = 0 takes none.
+  SelState st = sel_load(a, bh, 1);
+  sel_digit(a, bh, 2, st);  // synchronises the block
   const uint32_t T1 = st.pref[0], T2 = st.pref[1];
   const int need1 = st.krem[0], need2 = st.krem[1];
-  const bool on1 = st.k1 > 0, on2 = st.k2 > 0;
-  // offsets and tie ranks from the earlier blocks' counts (full chunks)
+  const bool on1 = hm.k_top > 0, on2 = hm.k_top + hm.r_eff > 0;
+  // scores before this block (full chunks) above and equal to each threshold
   int base_e1 = 0, base_e2 = 0, base_top = 0, base_seed = 0;
-  const int32_t* cnt = a.sel_cnt + (size_t)bh * a.NSEL * 4;
-  for (int pb = 0; pb < blk; ++pb) {
-    const int gt1 = cnt[4 * pb], eq1 = cnt[4 * pb + 1], gt2 = cnt[4 * pb + 2], eq2 = cnt[4 * pb + 3];
-    const int top = on1 ? gt1 + min(max(need1 - base_e1, 0), eq1) : 0;
-    const int sel2 = on2 ? gt2 + min(max(need2 - base_e2, 0), eq2) : 0;
-    base_top += top;
-    base_seed += sel2 - top;  // the top scores are among the first k2
-    base_e1 += eq1;
-    base_e2 += eq2;
+  if (blk > 0) {  // block-uniform
+    unsigned long long c1 = 0, c2 = 0;  // above in the low half, equal in the high half
+    int g1 = 0, q1 = 0, g2 = 0, q2 = 0;
+    constexpr int kV = 8;  // 16-byte requests in flight
+    for (int x0 = 4 * tid; x0 < i0; x0 += 4 * kV * kSelThreads) {
+      uint32_t u[kV][4];
+#pragma unroll
+      for (int v = 0; v < kV; ++v)
+        if (x0 + 4 * v * kSelThreads < i0) load4(u[v], key + x0 + 4 * v * kSelThreads);
+#pragma unroll
+      for (int v = 0; v < kV; ++v)
+        if (x0 + 4 * v * kSelThreads < i0)
+#pragma unroll
+          for (int e = 0; e < 4; ++e) {
+            g1 += u[v][e] > T1; q1 += u[v][e] == T1;
+            g2 += u[v][e] > T2; q2 += u[v][e] == T2;
+          }
+    }
+    c1 = (unsigned)g1 | (unsigned long long)(unsigned)q1 << 32;
+    c2 = (unsigned)g2 | (unsigned long long)(unsigned)q2 << 32;
+#pragma unroll
+    for (int o = 32; o > 0; o >>= 1) { c1 += __shfl_xor(c1, o, 64); c2 += __shfl_xor(c2, o, 64); }
+    if ((tid & 63) == 0) { s_cnt[0][tid >> 6] = c1; s_cnt[1][tid >> 6] = c2; }
+    __syncthreads();
+    c1 = c2 = 0;
+#pragma unroll
+    for (int w = 0; w < kSelThreads / 64; ++w) { c1 += s_cnt[0][w]; c2 += s_cnt[1][w]; }
+    base_e1 = (int)(c1 >> 32);
+    base_e2 = (int)(c2 >> 32);
+    // top scores taken, and those of ranks k1 .. k2 - 1 (the top ones are among the first k2)
+    base_top = on1 ? (int)(c1 & 0xffffffffu) + min(need1, base_e1) : 0;
+    base_seed = (on2 ? (int)(c2 & 0xffffffffu) + min(need2, base_e2) : 0) - base_top;
   }
   const int base_ev = blk * kSelChunk - base_top;
-  const uint32_t* key = reinterpret_cast<const uint32_t*>(a.score + (size_t)bh * a.S);
-  const int lo = st.i0 + tid * kSelPer;
-  uint32_t seg[kSelPer];
-#pragma unroll
-  for (int v = 0; v < kSelPer; ++v) seg[v] = lo + v < st.n ? key[lo + v] : 0u;
   // equal-to-threshold counts per thread, scanned: the tie ranks
   int e1 = 0, e2 = 0;
 #pragma unroll
   for (int v = 0; v < kSelPer; ++v)
-    if (lo + v < st.n) { e1 += (seg[v] == T1); e2 += (seg[v] == T2); }
+    if (lo + v < n) { e1 += (seg[v] == T1); e2 += (seg[v] == T2); }
   // both counts in one scan (each block total is at most kSelChunk < 2^16)
   int tot;
   const int eb12 = block_excl_scan<kSelThreads>(e1 | (e2 << 16), s_tmp, tot);
@@ -746,7 +737,7 @@ __global__ __launch_bounds__(kSelThreads) void select_write(BuildArgs a) {
     int r1 = eb1, r2 = eb2;
 #pragma unroll
     for (int v = 0; v < kSelPer; ++v) {
-      if (lo + v < st.n) {
+      if (lo + v < n) {
         bool top, sel2;
         classify(seg[v], r1, r2, top, sel2);
         c_top += top;
@@ -761,32 +752,33 @@ __global__ __launch_bounds__(kSelThreads) void select_write(BuildArgs a) {
   int nts;
   const int ots = block_excl_scan<kSelThreads>(c_top | (c_seed << 16), s_tmp, nts);
   const int n_top = nts & 0xffff, n_seed = nts >> 16;
-  const int n_valid = min(kSelChunk, st.n - st.i0);
+  const int n_valid = min(kSelChunk, n - i0);
   const int n_ev = n_valid - n_top;
   int ob_top = ots & 0xffff;
   int ob_seed = ots >> 16;
   int ob_ev = n_top + min(tid * kSelPer, n_valid) - ob_top;
-  __shared__ int s_run[kSelChunk];
-  __shared__ int s_seed[kSelChunk];
+  __shared__ uint16_t s_run[kSelChunk];  // positions within the block's chunk
+  __shared__ uint16_t s_seed[kSelChunk];
   int r1 = eb1, r2 = eb2;
 #pragma unroll
   for (int v = 0; v < kSelPer; ++v) {
-    if (lo + v < st.n) {
+    if (lo + v < n) {
       bool top, sel2;
       classify(seg[v], r1, r2, top, sel2);
-      if (top) s_run[ob_top++] = lo + v;
-      else s_run[ob_ev++] = lo + v;
-      if (sel2 && !top) s_seed[ob_seed++] = lo + v;
+      const uint16_t at = (uint16_t)(tid * kSelPer + v);
+      if (top) s_run[ob_top++] = at;
+      else s_run[ob_ev++] = at;
+      if (sel2 && !top) s_seed[ob_seed++] = at;
     }
   }
   __syncthreads();
   int32_t* elist = a.elist + (size_t)bh * a.S;
   int32_t* seeds = a.seeds + (size_t)bh * a.Rcap;
   for (int i = tid; i < n_top + n_ev; i += kSelThreads) {
-    if (i < n_top) main_idx[base_top + i] = s_run[i];
-    else elist[base_ev + i - n_top] = s_run[i];
+    if (i < n_top) main_idx[base_top + i] = i0 + s_run[i];
+    else elist[base_ev + i - n_top] = i0 + s_run[i];
   }
-  for (int i = tid; i < n_seed; i += kSelThreads) seeds[base_seed + i] = s_seed[i];
+  for (int i = tid; i < n_seed; i += kSelThreads) seeds[base_seed + i] = i0 + s_seed[i];
 }
 
 // ------------------------------------- AdaKV cross-head budget allocation
@@ -962,6 +954,7 @@ __global__ __launch_bounds__(kThreads) void gather_init(BuildArgs a) {
     reinterpret_cast<uint4*>(kc + (size_t)dst * D)[ck] = kv;
     reinterpret_cast<uint4*>(vc + (size_t)dst * D)[ck] = vv;
   }
+  zero_sel_hist(a, bh, blockIdx.x * kThreads + threadIdx.x, gridDim.x * kThreads);
   // every log-count starts empty
   for (int j = blockIdx.x * kThreads + threadIdx.x; j < a.Rcap; j += gridDim.x * kThreads)
     a.logc[(size_t)bh * a.Rcap + j] = kNegInf;
@@ -1727,8 +1720,7 @@ BuildArgs make_args(const BuildPlan& pl, const void* k, const void* v, const voi
   a.part = reinterpret_cast<double*>(ws + pl.off_part);
   a.lpiece = pl.lpiece; a.NIT = pl.NIT; a.NPART = pl.NPART;
   a.sel_hist = reinterpret_cast<int32_t*>(ws + pl.off_selh);
-  a.sel_cnt = reinterpret_cast<int32_t*>(ws + pl.off_selc);
-  a.NSEL = pl.NSEL;
+  a.sel_state = reinterpret_cast<uint32_t*>(ws + pl.off_sels);
   a.B = pl.B; a.Hq = pl.Hq; a.Hkv = pl.Hkv; a.G = pl.G; a.C = pl.C; a.Rcap = pl.Rcap; a.S = pl.S; a.w = pl.w;
   a.wr = pl.wr; a.pool_half = pl.pool_half; a.R = pl.R; a.LG = pl.LG; a.KG = pl.KG; a.NCH = pl.NCH; a.NBLK = pl.NBLK; a.T = pl.T;
   a.cap_slots = pl.C;
@@ -1784,18 +1776,15 @@ hipError_t launch_candidate_typed(const BuildPlan& pl, const BuildArgs& a, hipSt
                        (size_t)pl.T * pl.B * pl.Hkv * pl.S, -1);
     RESKV_CHECK();
   }
-  hipLaunchKernelGGL(pool_scores, grid((pl.S + kThreads * kPoolPer - 1) / (kThreads * kPoolPer)), dim3(kThreads), 0,
-                     st, a);
+  constexpr int kPoolChunk = kPoolThreads * kPoolPer;
+  hipLaunchKernelGGL(pool_scores, grid((pl.S + kPoolChunk - 1) / kPoolChunk), dim3(kPoolThreads), 0, st, a);
   RESKV_CHECK();
   if (alloc_meta) {
     hipLaunchKernelGGL(adakv_alloc, dim3(pl.B), dim3(kAdaThreads), 0, st, a, alloc_meta, safeguard);
     RESKV_CHECK();
   }
-  for (int pass = 0; pass < 4; ++pass) {
-    hipLaunchKernelGGL(select_hist, grid(pl.NSEL), dim3(kSelThreads), 0, st, a, pass);
-    RESKV_CHECK();
-  }
-  hipLaunchKernelGGL(select_count, grid(pl.NSEL), dim3(kSelThreads), 0, st, a); RESKV_CHECK();
+  hipLaunchKernelGGL(select_hist<1>, grid(pl.NSEL), dim3(kSelThreads), 0, st, a); RESKV_CHECK();
+  hipLaunchKernelGGL(select_hist<2>, grid(pl.NSEL), dim3(kSelThreads), 0, st, a); RESKV_CHECK();
   hipLaunchKernelGGL(select_write, grid(pl.NSEL), dim3(kSelThreads), 0, st, a); RESKV_CHECK();
   const int rows = pl.max_main + pl.Rcap;
   const int gblocks = (rows * (D * (int)sizeof(T) / 16) + kThreads - 1) / kThreads;
@@ -1922,7 +1911,7 @@ bool layout_build_plan(BuildPlan* plan) {
   pl.off_parrive = take(BH * pl.Rcap * sizeof(int32_t));
   pl.off_part = take(BH * pl.NPART * 2 * pl.D * sizeof(double));
   pl.off_selh = take(BH * kSelHist * sizeof(int32_t));
-  pl.off_selc = take(BH * pl.NSEL * 4 * sizeof(int32_t));
+  pl.off_sels = take(BH * 8 * sizeof(uint32_t));
   pl.bytes = off;
   return true;
 }

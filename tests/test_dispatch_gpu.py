@@ -60,3 +60,35 @@ def test_scoring_row_chunks(dtype, d, G, window, s):
     got = run_build(wl, x)
     for h in range(2):
         check_head(wl, x, got, 0, h)
+
+
+@pytest.mark.parametrize("s,budget,res,recent", [
+    (8192 + 8, 200, (60, 0), 8),      # exactly one selection block of scores
+    (8193 + 8, 4200, (100, 3), 8),    # one score in the second block, both thresholds deep
+    (16385 + 8, 9000, (9, 800), 8),   # thresholds that cross the blocks
+    (3 * 8192 - 5, 64, (63, 1), 70),  # all main slots protected: nothing selected, seeds only
+    (5001, 5000, (1, 300), 4),        # nearly every score kept; unaligned rows of scores
+])
+def test_selection_blocks(s, budget, res, recent):
+    """Score lists at the edges of the selection's 8192-score blocks, with the
+    thresholds high, low and absent; two heads (the second head's scores start
+    unaligned where the context length is odd)."""
+    wl = synth.tiny_workload(s=s, d=64, hq=4, hkv=2, budget=budget, res=0, window=8, dtype="bf16", n_heavy=6)
+    wl.res = np.asarray(res, np.int64).reshape(1, 1, 2)
+    x = host_copies(synth.gen_layer(wl, 0, seed=s, n_decode=1))
+    got = run_build(wl, x, recent=recent, iters=1)
+    for h in range(2):
+        check_head(wl, x, got, 0, h, recent=recent, iters=1)
+
+
+def test_selection_tied_scores():
+    """Equal keys give equal scores over several blocks: the lowest positions
+    are taken, counted over the blocks before."""
+    s, window = 20000, 8
+    wl = synth.tiny_workload(s=s, d=64, hq=4, hkv=2, budget=10100, res=0, window=window, dtype="bf16", n_heavy=6)
+    wl.res = np.asarray((40, 0), np.int64).reshape(1, 1, 2)
+    x = synth.gen_layer(wl, 0, seed=3, n_decode=1)
+    x["K"][:, :, 200:19000] = x["K"][:, :, 200:201]
+    got = run_build(wl, host_copies(x), iters=1)
+    for h in range(2):
+        check_head(wl, x, got, 0, h, iters=1)
