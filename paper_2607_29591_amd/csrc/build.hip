@@ -65,8 +65,8 @@ constexpr int kSelThreads = 1024;
 constexpr int kSelPer = 8;                          // scores per selection thread
 constexpr int kSelChunk = kSelPer * kSelThreads;   // scores per selection block
 constexpr int kSelBins = 2048;                     // digits of the wider selection passes
+constexpr int kAdaHist = kSelBins + 1024;          // cross-head search histograms per head (second and third pass)
 constexpr int kSelHist = 4 * kSelBins;             // selection pass histograms per head (sel_at)
-constexpr int kAdaThreads = 1024;
 constexpr int kPieceMin = 4096;                     // update pieces of 1024 members from which they are not cut smaller
 
 struct BuildArgs {
@@ -101,6 +101,8 @@ struct BuildArgs {
   int32_t* parrive;    // [BH][Rcap] pieces of a split group that have left their sums
   double* part;        // [BH][NPART][2][D] key and value sums of split groups' pieces
   int32_t* sel_hist;   // [BH][kSelHist] selection pass histograms (zeroed by lse_final and, for the next candidate, gather_init)
+  int32_t* ada_hist;   // [BH][kAdaHist] cross-head search histograms (zeroed by pool_scores), or NULL
+  uint32_t* ada_state; // [2][B][kAdaState] per sequence: prefix, then the heads' tokens above its range
   uint32_t* sel_state; // [BH][2][4] thresholds' prefixes and remaining ranks after the first and second pass
   int B, Hq, Hkv, G, C, Rcap, S, w, R, LG, KG, NCH, NBLK, T;
   int lpiece, NIT, NPART;  // log2 of the members per update piece, pieces and partial slots per head
@@ -461,6 +463,8 @@ __global__ __launch_bounds__(kPoolThreads) void pool_scores(BuildArgs a) {
   const HeadMeta hm = a.meta[bh];
   const int n = hm.all_main ? 0 : hm.n_sc;
   const int b0 = blockIdx.x * kPoolThreads * kPoolPer;
+  if (a.ada_hist && blockIdx.x == 0)
+    for (int i = threadIdx.x; i < kAdaHist; i += kPoolThreads) a.ada_hist[(size_t)bh * kAdaHist + i] = 0;
   if (b0 >= n && !a.dbg_scores) return;  // block-uniform
   __shared__ int s_hist[kSelBins];
   const int tid = threadIdx.x, lane = tid & 63;
@@ -799,130 +803,180 @@ __global__ __launch_bounds__(kSelThreads) void select_write(BuildArgs a) {
 // h's tokens above x after taking min(room_h, max(0, N_h(x) - floor_h)) of
 // them (room_h = cap_h - floor_h). A radix search over the fp32 bit pattern
 // (non-negative floats order as unsigned integers) finds the score x* of the
-// last slot handed out from per-head digit histograms; the tokens tied at
-// x* then go to the heads in ascending order.
-__global__ __launch_bounds__(kAdaThreads) void adakv_alloc(BuildArgs a, HeadMeta* meta, double safeguard) {
+// last slot handed out from per-head digit histograms, in the selection's
+// three passes: the first histogram is the one the pooling counted, the other
+// two count the scores matching the sequence's prefix over blocks of
+// kSelChunk scores, each kernel resolving the digit before it; the tokens tied
+// at x* then go to the heads in ascending order. (One block per sequence
+// reading every score four times took 143 us at 16 sequences of 4 heads and
+// 4K-64K tokens, the three launches 50 us.)
+constexpr int kAdaState = 1 + kAdaMaxHeads;  // per sequence: prefix, then the heads' tokens above its range
+
+struct AdaShared {
+  int floor[kAdaMaxHeads], room[kAdaMaxHeads], above[kAdaMaxHeads];
+  int live[kAdaMaxHeads];              // 0 for heads that keep every token and take no part
+  int higher[kAdaMaxHeads], equal[kAdaMaxHeads];  // of the current prefix range: tokens in higher digits, in the digit
+  unsigned long long scan[kSelThreads / 64];
+  int extra, total_room;
+};
+
+// The sequence's floors, rooms and slots to hand out; whether a search is
+// needed. Called by every thread of a kSelThreads block.
+__device__ __forceinline__ bool ada_setup(const BuildArgs& a, double safeguard, int b, AdaShared& s) {
+  const int tid = threadIdx.x;
+  if (tid < 64) {
+    int fl = 0, room = 0, k = 0, live = 0;
+    if (tid < a.Hkv) {
+      const HeadMeta hm = a.meta[b * a.Hkv + tid];
+      if (!hm.all_main) {
+        live = 1;
+        k = hm.k_top;
+        fl = (int)floor(safeguard * (double)k);
+        room = min(hm.n_sc, a.cap_slots - hm.r - hm.P) - fl;
+      }
+      s.floor[tid] = fl;
+      s.room[tid] = room;
+      s.above[tid] = 0;
+      s.live[tid] = live;
+    }
+    int extra = k - fl, total = room;
+#pragma unroll
+    for (int o = 32; o > 0; o >>= 1) { extra += __shfl_xor(extra, o, 64); total += __shfl_xor(total, o, 64); }
+    if (tid == 0) { s.extra = extra; s.total_room = total; }
+  }
+  __syncthreads();
+  return s.extra > 0 && s.total_room > s.extra;
+}
+
+// Digit of pass `pass` for the whole sequence, and each head's tokens in
+// higher digits and in it. Slots handed out down to digit d are non-increasing
+// in d, so the digits reaching `extra` are a prefix 0 .. d*; their count gives
+// d*. Called by every thread of a kSelThreads block.
+__device__ __forceinline__ int ada_digit(const BuildArgs& a, int b, int pass, AdaShared& s) {
+  const int H = a.Hkv, tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int bins = sel_bins(pass), top = bins - 1 - 2 * tid;  // this thread's two bins, descending
+  auto hist = [&](int h) {
+    const size_t bh = (size_t)b * H + h;
+    return pass == 0 ? a.sel_hist + bh * kSelHist : a.ada_hist + bh * kAdaHist + (pass == 2 ? kSelBins : 0);
+  };
+  auto load2 = [&](int h) {
+    return h < H && s.live[h] && top >= 1 ? *reinterpret_cast<const int2*>(hist(h) + top - 1) : make_int2(0, 0);
+  };
+  long long f0 = 0, f1 = 0;  // slots handed out down to the two bins
+  for (int h = 0; h < H; h += 2) {  // two heads per scan
+    const int2 x = load2(h), y = load2(h + 1);
+    unsigned long long all;
+    const unsigned long long ex = block_excl_scan<kSelThreads>(
+        (unsigned)(x.x + x.y) | (unsigned long long)(unsigned)(y.x + y.y) << 32, s.scan, all);
+    auto add = [&](int hh, int e, const int2& c) {
+      if (hh >= H) return;
+      const int base = s.above[hh] + e - s.floor[hh];
+      f0 += min(s.room[hh], max(0, base + c.y));
+      f1 += min(s.room[hh], max(0, base + c.y + c.x));
+    };
+    add(h, (int)(ex & 0xffffffffu), x);
+    add(h + 1, (int)(ex >> 32), y);
+  }
+  const int n0 = __syncthreads_count(top >= 1 && f0 >= s.extra), n1 = __syncthreads_count(top >= 1 && f1 >= s.extra);
+  const int digit = n0 + n1 > 0 ? n0 + n1 - 1 : 0;
+  for (int h = wave; h < H; h += kSelThreads / 64) {
+    int hi = 0;
+    if (s.live[h])
+      for (int d = digit + 1 + lane; d < bins; d += 64) hi += hist(h)[d];
+#pragma unroll
+    for (int o = 32; o > 0; o >>= 1) hi += __shfl_xor(hi, o, 64);
+    if (lane == 0) {
+      s.higher[h] = hi;
+      s.equal[h] = s.live[h] ? hist(h)[digit] : 0;
+    }
+  }
+  __syncthreads();
+  return digit;
+}
+
+// Pass 1 or 2 of the search over one block of a head's scores.
+template <int kPass>
+__global__ __launch_bounds__(kSelThreads) void adakv_hist(BuildArgs a, double safeguard) {
+  const int b = blockIdx.z, h = blockIdx.y, bh = b * a.Hkv + h, tid = threadIdx.x, lane = tid & 63;
+  constexpr int kBins = sel_bins(kPass), kShift = sel_shift(kPass);
+  constexpr uint32_t kMask = ~0u << sel_shift(kPass - 1);
+  const HeadMeta hm = a.meta[bh];
+  const int i0 = blockIdx.x * kSelChunk, n = hm.all_main ? 0 : hm.n_sc;
+  const bool first = blockIdx.x == 0 && h == 0;  // leaves the sequence's state
+  if (i0 >= n && !first) return;  // block-uniform
+  __shared__ AdaShared s;
+  __shared__ int s_hist[kBins];
+  const uint32_t* key = reinterpret_cast<const uint32_t*>(a.score + (size_t)bh * a.S);
+  uint32_t u[kSelPer];
+#pragma unroll
+  for (int v = 0; v < kSelPer; ++v) {
+    const int i = i0 + v * kSelThreads + tid;
+    u[v] = i < n ? key[i] : 0u;
+  }
+  for (int i = tid; i < kBins; i += kSelThreads) s_hist[i] = 0;
+  if (!ada_setup(a, safeguard, b, s)) return;
+  uint32_t* state = a.ada_state + (size_t)b * kAdaState;
+  uint32_t prefix = 0u;
+  if (kPass == 2) {
+    prefix = state[0];
+    if (tid < a.Hkv) s.above[tid] = (int)state[1 + tid];
+    __syncthreads();
+  }
+  // the second pass's state goes to its own slot: blocks still read the first's
+  uint32_t* next = kPass == 2 ? state + (size_t)a.B * kAdaState : state;
+  prefix |= (uint32_t)ada_digit(a, b, kPass - 1, s) << sel_shift(kPass - 1);
+  if (first) {
+    if (tid == 0) next[0] = prefix;
+    if (tid < a.Hkv) next[1 + tid] = (uint32_t)(s.above[tid] + s.higher[tid]);
+  }
+#pragma unroll
+  for (int v = 0; v < kSelPer; ++v)
+    wave_hist_add(s_hist, (u[v] >> kShift) & (kBins - 1),
+                  i0 + v * kSelThreads + tid < n && (u[v] & kMask) == prefix, lane);
+  __syncthreads();
+  int* gh = a.ada_hist + (size_t)bh * kAdaHist + (kPass == 2 ? kSelBins : 0);
+  for (int i = tid; i < kBins; i += kSelThreads)
+    if (s_hist[i]) atomicAdd(&gh[i], s_hist[i]);
+}
+
+// The last digit, the counts, and the heads' sizes rewritten. One block per
+// sequence.
+__global__ __launch_bounds__(kSelThreads) void adakv_alloc(BuildArgs a, HeadMeta* meta, double safeguard) {
   const int b = blockIdx.x, H = a.Hkv, tid = threadIdx.x;
-  const int wave = tid >> 6, lane = tid & 63;
-  __shared__ int s_hist[kAdaMaxHeads][256];  // digit counts, then suffix sums
-  __shared__ int s_floor[kAdaMaxHeads], s_room[kAdaMaxHeads], s_n[kAdaMaxHeads], s_above[kAdaMaxHeads];
-  __shared__ int s_extra, s_total_room, s_digit;
-  if (tid < H) {
-    const HeadMeta hm = meta[b * H + tid];
-    const bool live = !hm.all_main;
-    const int fl = live ? (int)floor(safeguard * (double)hm.k_top) : 0;
-    const int cap = live ? min(hm.n_sc, a.cap_slots - hm.r - hm.P) : 0;
-    s_floor[tid] = fl;
-    s_room[tid] = live ? cap - fl : 0;
-    s_n[tid] = live ? hm.n_sc : 0;
-    s_above[tid] = 0;
-  }
-  __syncthreads();
-  if (tid == 0) {
-    int extra = 0, room = 0;
-    for (int h = 0; h < H; ++h) {
-      const HeadMeta hm = meta[b * H + h];
-      if (!hm.all_main) extra += hm.k_top - s_floor[h];
-      room += s_room[h];
-    }
-    s_extra = extra;
-    s_total_room = room;
-    s_digit = 0;
-  }
-  __syncthreads();
-  const int extra = s_extra;
-  const bool search = extra > 0 && s_total_room > extra;  // block-uniform
-  uint32_t prefix = 0u, mask = 0u;
-  int digit = 0;
-  for (int shift = 24; search && shift >= 0; shift -= 8) {
-    for (int i = tid; i < H * 256; i += kAdaThreads) (&s_hist[0][0])[i] = 0;
+  __shared__ AdaShared s;
+  __shared__ int s_take[kAdaMaxHeads];
+  const bool search = ada_setup(a, safeguard, b, s);  // block-uniform
+  if (search) {
+    const uint32_t* state = a.ada_state + (size_t)(a.B + b) * kAdaState;
+    if (tid < H) s.above[tid] = (int)state[1 + tid];
     __syncthreads();
-    for (int h = 0; h < H; ++h) {
-      const int n = s_n[h];
-      const uint32_t* key = reinterpret_cast<const uint32_t*>(a.score + ((size_t)b * H + h) * a.S);
-      for (int i0 = tid; i0 < n; i0 += 4 * kAdaThreads) {
-        uint32_t u[4];
-#pragma unroll
-        for (int v = 0; v < 4; ++v) u[v] = i0 + v * kAdaThreads < n ? key[i0 + v * kAdaThreads] : 0u;
-#pragma unroll
-        for (int v = 0; v < 4; ++v)
-          wave_hist_add(s_hist[h], (u[v] >> shift) & 0xff, i0 + v * kAdaThreads < n && (u[v] & mask) == prefix, lane);
-      }
-    }
-    __syncthreads();
-    // per head, suffix sums over digits: S_h[d] = tokens of the current
-    // prefix range whose digit is >= d (lane l holds digits 4l .. 4l+3)
-    for (int h = wave; h < H; h += kAdaThreads / 64) {
-      int c[4], own = 0;
-#pragma unroll
-      for (int v = 0; v < 4; ++v) { c[v] = s_hist[h][4 * lane + v]; own += c[v]; }
-      int incl = own;
-#pragma unroll
-      for (int o = 1; o < 64; o <<= 1) {
-        const int y = __shfl_down(incl, o, 64);
-        if (lane + o < 64) incl += y;
-      }
-      int run = incl - own;  // digits above this lane's four
-#pragma unroll
-      for (int v = 3; v >= 0; --v) { run += c[v]; s_hist[h][4 * lane + v] = run; }
-    }
-    __syncthreads();
-    // slots handed out down to digit d: non-increasing in d, so the digits
-    // reaching `extra` are a prefix 0 .. d*; their count gives d*
-    bool reach = false;
-    if (tid < 256) {
-      long long f = 0;
+    ada_digit(a, b, 2, s);
+    if (tid == 0) {
+      // slots above x*, then the tokens tied at x* to the heads in order
+      int rem = s.extra;
       for (int h = 0; h < H; ++h) {
-        const int above = s_above[h] + s_hist[h][tid] - s_floor[h];
-        f += min(s_room[h], max(0, above));
+        s_take[h] = min(s.room[h], max(0, s.above[h] + s.higher[h] - s.floor[h]));
+        rem -= s_take[h];
       }
-      reach = f >= extra;
+      for (int h = 0; h < H; ++h) {
+        const int gt = s.above[h] + s.higher[h], ge = gt + s.equal[h];
+        const int tied = max(0, ge - s.floor[h]) - max(0, gt - s.floor[h]);
+        const int t = min(min(s.room[h] - s_take[h], tied), rem);
+        s_take[h] += t;
+        rem -= t;
+      }
     }
-    const int cnt = __syncthreads_count(reach);
-    digit = cnt > 0 ? cnt - 1 : 0;
-    if (tid < H) {
-      const int higher = digit < 255 ? s_hist[tid][digit + 1] : 0;
-      if (shift > 0) s_above[tid] += higher;
-    }
-    if (tid == 0) s_digit = digit;
-    prefix |= (uint32_t)digit << shift;
-    mask |= 0xffu << shift;
     __syncthreads();
   }
-  if (tid != 0) return;
-  // counts: slots above x*, then the tokens tied at x* to the heads in order
-  // (s_above counts the tokens above the last digit's range, s_hist holds
-  // the last digit's suffix sums)
-  int rem = extra;
-  int take[kAdaMaxHeads];
-  const int d = s_digit;
-  for (int h = 0; h < H; ++h) {
-    if (!search) {
-      take[h] = extra == 0 ? 0 : s_room[h];
-      continue;
-    }
-    const int gt = s_above[h] + (d < 255 ? s_hist[h][d + 1] : 0);  // tokens > x*
-    take[h] = min(s_room[h], max(0, gt - s_floor[h]));
-    rem -= take[h];
-  }
-  for (int h = 0; search && h < H; ++h) {
-    const int ge = s_above[h] + s_hist[h][d];                      // tokens >= x*
-    const int gt = s_above[h] + (d < 255 ? s_hist[h][d + 1] : 0);
-    const int tied = max(0, ge - s_floor[h]) - max(0, gt - s_floor[h]);
-    const int t = min(min(s_room[h] - take[h], tied), rem);
-    take[h] += t;
-    rem -= t;
-  }
-  for (int h = 0; h < H; ++h) {
-    HeadMeta hm = meta[b * H + h];
-    if (hm.all_main) continue;
-    hm.k_top = s_floor[h] + take[h];
-    hm.m = hm.P + hm.k_top;
-    hm.main_len = hm.m;
-    hm.nE = hm.s - hm.m;
-    hm.r_eff = hm.r < hm.nE ? hm.r : hm.nE;
-    meta[b * H + h] = hm;
-  }
+  if (tid >= H) return;
+  HeadMeta hm = meta[b * H + tid];
+  if (hm.all_main) return;
+  hm.k_top = s.floor[tid] + (search ? s_take[tid] : s.extra == 0 ? 0 : s.room[tid]);
+  hm.m = hm.P + hm.k_top;
+  hm.main_len = hm.m;
+  hm.nE = hm.s - hm.m;
+  hm.r_eff = hm.r < hm.nE ? hm.r : hm.nE;
+  meta[b * H + tid] = hm;
 }
 
 // ------------------------------------------------ gather + centre seeding
@@ -1780,7 +1834,9 @@ hipError_t launch_candidate_typed(const BuildPlan& pl, const BuildArgs& a, hipSt
   hipLaunchKernelGGL(pool_scores, grid((pl.S + kPoolChunk - 1) / kPoolChunk), dim3(kPoolThreads), 0, st, a);
   RESKV_CHECK();
   if (alloc_meta) {
-    hipLaunchKernelGGL(adakv_alloc, dim3(pl.B), dim3(kAdaThreads), 0, st, a, alloc_meta, safeguard);
+    hipLaunchKernelGGL(adakv_hist<1>, grid(pl.NSEL), dim3(kSelThreads), 0, st, a, safeguard); RESKV_CHECK();
+    hipLaunchKernelGGL(adakv_hist<2>, grid(pl.NSEL), dim3(kSelThreads), 0, st, a, safeguard); RESKV_CHECK();
+    hipLaunchKernelGGL(adakv_alloc, dim3(pl.B), dim3(kSelThreads), 0, st, a, alloc_meta, safeguard);
     RESKV_CHECK();
   }
   hipLaunchKernelGGL(select_hist<1>, grid(pl.NSEL), dim3(kSelThreads), 0, st, a); RESKV_CHECK();
@@ -1931,7 +1987,11 @@ bool make_build_plan_adakv(const reskv_shape_t& s, const reskv_build_params_t& p
     m.nE = m.s - m.P - fl;
     m.r_eff = m.r < m.nE ? m.r : m.nE;
   }
-  return fold_build_plan(hm, plan) && layout_build_plan(plan);
+  if (!fold_build_plan(hm, plan) || !layout_build_plan(plan)) return false;
+  plan->off_adah = plan->bytes;
+  plan->off_adas = align_up(plan->off_adah + (size_t)plan->B * plan->Hkv * kAdaHist * sizeof(int32_t), 256);
+  plan->bytes = align_up(plan->off_adas + (size_t)2 * plan->B * kAdaState * sizeof(uint32_t), 256);
+  return true;
 }
 
 bool make_build_plan(const reskv_shape_t& s, const reskv_build_params_t& p, const int32_t* seq_len,
@@ -1987,6 +2047,8 @@ hipError_t launch_build_adakv(const reskv_shape_t& s, const reskv_build_params_t
   const BuildOut out{kc, vc, logc, main_idx, res_len, main_len};
   BuildArgs a = make_args(pl, k, v, nullptr, meta, out, dbg_scores, dbg_assign, dbg_centers, workspace);
   a.cap_slots = pl.C - decode_reserve;
+  a.ada_hist = reinterpret_cast<int32_t*>(static_cast<char*>(workspace) + pl.off_adah);
+  a.ada_state = reinterpret_cast<uint32_t*>(static_cast<char*>(workspace) + pl.off_adas);
   const bool bf = pl.dtype == RESKV_BF16;
   if (pl.D == 128)
     return bf ? launch_candidate_typed<uint16_t, 128>(pl, a, stream, meta, safeguard)

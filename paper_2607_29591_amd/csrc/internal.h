@@ -92,7 +92,7 @@ struct BuildPlan {
   int lpiece, NIT, NPART;  // log2 of the members per update piece; pieces and partial-sum slots per head
   size_t off_meta, off_lsep, off_lse, off_raw, off_score, off_elist, off_seeds, off_cent, off_chi,
       off_clo, off_cnorm, off_assign, off_hist, off_order, off_items, off_nitem, off_parrive, off_part, off_selh,
-      off_sels, bytes;
+      off_sels, off_adah, off_adas, bytes;
 };
 
 // Device buffers one construction writes.

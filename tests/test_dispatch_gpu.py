@@ -6,6 +6,7 @@ import pytest
 
 from paper_2607_29591_amd import synth
 from tests.build_check import check_head, run_build
+from tests.test_adakv_gpu import check_sequence, workload as ada_workload
 from tests.test_build_gpu import host_copies
 from tests.test_decode_gpu import cache_case, check
 
@@ -92,3 +93,19 @@ def test_selection_tied_scores():
     got = run_build(wl, host_copies(x), iters=1)
     for h in range(2):
         check_head(wl, x, got, 0, h, iters=1)
+
+
+@pytest.mark.parametrize("hkv,ctx,budget,alpha", [
+    (5, [9000, 17001], [600, 301], 0.2),   # an odd head count, scores over several blocks, unaligned rows
+    (32, [400], [60], 0.0),                # the most heads that share budgets
+    (1, [8300], [64], 0.5),                # one head: the search runs against its own cap
+])
+def test_adakv_search_blocks(hkv, ctx, budget, alpha):
+    """The cross-head search over several score blocks and head counts."""
+    rng = np.random.default_rng(hkv)
+    res = [[int(r) for r in rng.integers(0, b // 2, size=hkv)] for b in budget]
+    wl, x = ada_workload(20 + hkv, "bf16", 64, ctx, budget, res, 2 * hkv, hkv)
+    C = 2 * max(budget)
+    got = run_build(wl, x, adakv=alpha, slot_cap=C)
+    for b in range(len(ctx)):
+        check_sequence(wl, x, got, b, alpha, C, wl.window, replay_heads=())
