@@ -120,8 +120,9 @@ reskv_status_t reskv_decode_attn_static(const reskv_shape_t* shape, const reskv_
   const DecodePlan plan = make_decode_plan(*shape);
   if ((size_t)plan.GP * plan.P * sizeof(float) > decode_max_lds_weights())
     return fail(RESKV_ERR_UNSUPPORTED, "%d split-K records per head do not fit the combine", plan.P);
-  // one block per (b, kv head) writes no split-K records
-  const size_t need = plan.whole_head ? 0 : plan.bytes;
+  // from 256 (b, kv head) pairs on no capacity needs split-K records; below,
+  // the limit is that of the split path whichever path a capacity takes
+  const size_t need = plan.no_records ? 0 : plan.bytes;
   if (need > kStaticScratchBytes)
     return fail(RESKV_ERR_WORKSPACE,
                 "this shape needs %zu bytes of split-K scratch, above the %zu bytes of the library's static "

@@ -57,7 +57,6 @@ constexpr int kChunk = kWaves * kUnit; // slots per split block
 // several blocks (calls without an append): one block pulls 256 outputs'
 // worth of every record through one CU
 constexpr int kSliceRecords = 32;
-constexpr int kWholeHeadMin = 256;     // (b, kv head) pairs that fill the 256 CUs
 
 struct DecodeArgs {
   const void* q;
@@ -1287,9 +1286,27 @@ DecodePlan make_decode_plan(const reskv_shape_t& s) {
   const int rmax = s.res_cap < s.slot_cap ? s.res_cap : s.slot_cap;
   p.PR = (rmax + kChunk - 1) / kChunk;
   p.P = p.PR + (s.slot_cap + kChunk - 1) / kChunk;
-  // one block per (b, kv head) when those alone fill the chip's CUs (fp32
-  // rows of 128 take the split kernels: the head kernel would spill)
-  p.whole_head = (long long)p.B * p.Hkv >= kWholeHeadMin && (s.dtype == RESKV_BF16 || p.D == 64);
+  // One block per (b, kv head) or split-K blocks and a merge launch: a block
+  // streams 512 slots a round (8 waves of 64), about 4 us each while the pairs
+  // leave CUs idle, and saves the merge's 5 us. Measured at d = 128, bf16, 4
+  // query heads per KV head, us split / one block:
+  //   pairs     C = 320    512       640       1024      1536      2048
+  //     1     9.6/ 8.5  9.7/ 8.8 10.0/10.0 10.1/12.8 10.5/18.1 10.5/22.6
+  //    32    11.5/ 9.3 11.5/ 9.6 11.6/11.5 11.8/14.1 12.4/18.9 15.5/24.0
+  //    64    11.7/ 9.4 11.7/ 9.7 12.2/11.6 15.4/14.6 18.5/22.0 22.8/28.2
+  //    96    12.5/ 9.5 14.1/ 9.8 14.8/11.7 18.5/18.0 25.4/25.3 27.9/32.1
+  //   128    12.7/ 9.6 14.9/10.4 18.0/14.8 23.7/18.8 28.0/25.4 32.7/32.7
+  // so one block from 32 pairs per round on (two rounds: 64 pairs), always
+  // from 256 pairs on, which fill the CUs, and at any count for one round;
+  // bf16 up to 640 slots, where only two waves have a second unit (fp32 rows
+  // of 64 at 640: 14.8/15.9 at 32 pairs). fp32 rows of 128 always split: the
+  // head kernel would spill.
+  const long long pairs = (long long)p.B * p.Hkv;
+  const int round = kHeadWaves * kUnit, rounds = (s.slot_cap + round - 1) / round;
+  const bool fits = s.dtype == RESKV_BF16 || p.D == 64;
+  p.whole_head = fits && (s.slot_cap <= (s.dtype == RESKV_BF16 ? round + 2 * kUnit : round) || pairs >= 256 ||
+                          pairs >= 32LL * rounds);
+  p.no_records = fits && pairs >= 256;
   const size_t recs = (size_t)p.B * p.Hkv * p.P * p.GP;
   p.acc_off = 0;
   p.ml_off = align_up(recs * p.D * sizeof(float), 256);

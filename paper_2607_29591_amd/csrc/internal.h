@@ -15,6 +15,7 @@ struct DecodePlan {
   int B, Hq, Hkv, G, GP, D, C, Rcap;
   int PR, P;  // residual blocks and all blocks of the split grid per (b, kv head)
   bool whole_head;  // one block per (b, kv head), no split-K records
+  bool no_records;  // enough pairs that every capacity takes one block per head
   size_t acc_off, ml_off, bytes;
 };
 

@@ -9,6 +9,7 @@ from tests.build_check import check_head, run_build
 from tests.test_adakv_gpu import check_sequence, workload as ada_workload
 from tests.test_build_gpu import host_copies
 from tests.test_decode_gpu import cache_case, check
+from tests.test_graph_gpu import test_decode_step_graph_replays_match_eager as graph_replays
 
 pytestmark = pytest.mark.gpu
 
@@ -109,3 +110,29 @@ def test_adakv_search_blocks(hkv, ctx, budget, alpha):
     got = run_build(wl, x, adakv=alpha, slot_cap=C)
     for b in range(len(ctx)):
         check_sequence(wl, x, got, b, alpha, C, wl.window, replay_heads=())
+
+
+@pytest.mark.parametrize("dtype,d,B,Hkv,C", [
+    ("bf16", 128, 1, 2, 640), ("bf16", 128, 1, 2, 641),    # ten and eleven units of one head
+    ("f32", 64, 1, 2, 512), ("f32", 64, 1, 2, 513),
+    ("bf16", 64, 16, 4, 1024), ("bf16", 64, 16, 4, 1025),  # 64 pairs: two rounds of units, three
+    ("bf16", 64, 15, 4, 1024),                             # one pair count below
+])
+def test_one_block_per_head_line(dtype, d, B, Hkv, C):
+    """Both sides of the line between one block per head and split-K blocks,
+    heads from nearly empty to full."""
+    rng = np.random.default_rng(C)
+    res = rng.integers(0, 200, size=(B, Hkv))
+    main = np.array([[int(rng.integers(1, C - r + 1)) for r in row] for row in res])
+    main[0, 0] = C - res[0, 0]
+    main[0, 1] = 1
+    shape, q, kc, vc, logc = cache_case(C, B, 4 * Hkv, Hkv, d, dtype, C, 200, res, main)
+    heads = [(0, 0), (0, 4)] + [(int(b), int(h)) for b, h in zip(rng.integers(0, B, 6), rng.integers(0, 4 * Hkv, 6))]
+    check(dtype, shape, q, kc, vc, logc, res, main, heads=heads)
+
+
+def test_split_decode_graph_replays():
+    """Graph replays of the split-K path with its append: partial blocks that
+    read and store the new token, then the combine, which advances the main
+    lengths."""
+    graph_replays(2, 2, 7, 900)
