@@ -348,7 +348,9 @@ size_t reskv_decode_workspace_size(const reskv_shape_t* shape);
  * an equal range of that list, so no compute unit waits on the longest
  * head. Heads that span several blocks are merged by a second kernel, which
  * also advances main_len. Outputs equal reskv_decode_attn's within rounding
- * (a different order of the same fp32 sums).
+ * (a different order of the same fp32 sums). Where the kernels of
+ * reskv_decode_attn are faster whatever the lengths are (up to 256 pairs of
+ * capacities up to 1536 slots, fewer pairs up to 2304) they serve the call.
  *
  *   workspace       device scratch of reskv_decode_ragged_workspace_size()
  *                   bytes (the per-call plan and the partial records of

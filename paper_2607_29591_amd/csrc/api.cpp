@@ -141,7 +141,8 @@ size_t reskv_decode_ragged_workspace_size(const reskv_shape_t* shape) {
   if (check_shape(shape) != RESKV_OK) return 0;
   RaggedPlan plan;
   if (!make_ragged_plan(*shape, &plan)) return 0;
-  return plan.bytes;
+  const size_t other = ragged_takes_decode(*shape) ? make_decode_plan(*shape).bytes : 0;
+  return plan.bytes > other ? plan.bytes : other;
 }
 
 reskv_status_t reskv_decode_attn_ragged(const reskv_shape_t* shape, const reskv_gate_t* gate, const void* q,
@@ -164,6 +165,15 @@ reskv_status_t reskv_decode_attn_ragged(const reskv_shape_t* shape, const reskv_
   if (!workspace || workspace_bytes < plan.bytes)
     return fail(RESKV_ERR_WORKSPACE, "ragged decode needs %zu workspace bytes, got %zu", plan.bytes,
                 workspace ? workspace_bytes : (size_t)0);
+  if (ragged_takes_decode(*shape)) {
+    const DecodePlan dp = make_decode_plan(*shape);
+    if (workspace_bytes >= dp.bytes) {
+      const hipError_t e = launch_decode(*shape, *gate, dp, q, kc, vc, logc, res_len, main_len, k_new, v_new, out,
+                                         dbg_lse_main, dbg_lse_res, dbg_gate, workspace, (hipStream_t)stream);
+      if (e != hipSuccess) return fail(RESKV_ERR_HIP, "decode launch failed: %s", hipGetErrorString(e));
+      return ok();
+    }
+  }
   hipError_t e = launch_decode_ragged(*shape, *gate, plan, q, kc, vc, logc, res_len, main_len, k_new, v_new, out,
                                       dbg_lse_main, dbg_lse_res, dbg_gate, workspace, (hipStream_t)stream);
   if (e != hipSuccess) return fail(RESKV_ERR_HIP, "decode launch failed: %s", hipGetErrorString(e));

@@ -1340,6 +1340,27 @@ bool make_ragged_plan(const reskv_shape_t& s, RaggedPlan* plan) {
   return true;
 }
 
+// Equal unit ranges cost a plan prologue in every block and a merge launch
+// (about 13 us together); per-head kernels cost the wait for the longest head.
+// Measured with lengths uniform in [C/4, C], with one full head among quarter
+// ones and with every 16th full among eighths, us per head / equal ranges at
+// the three:
+//     8 pairs, C = 2304:  14/ 49   13/50   13/49
+//   128 pairs, C = 2304:  29/ 30   19/23   19/22
+//   192 pairs, C = 1536:  25/ 36   23/26   23/30
+//   192 pairs, C = 2304:  36/ 61   31/31   31/30
+//   256 pairs, C = 1152:  23/ 37   20/26   20/25
+//   256 pairs, C = 1536:  30/ 43   25/30   26/28
+//   256 pairs, C = 2304:  42/ 65   34/35   34/32
+//   384 pairs, C = 1152:  34/ 55   21/25   34/23
+// so up to 256 pairs (one block per head runs them all at once) and 256 x 1536
+// slots the per-head kernels, never slower there; beyond, and on caches longer
+// than measured, the equal ranges.
+bool ragged_takes_decode(const reskv_shape_t& s) {
+  const long long pairs = (long long)s.batch * s.num_kv_heads;
+  return pairs <= 256 && s.slot_cap <= 2304 && pairs * s.slot_cap <= 256LL * 1536;
+}
+
 hipError_t launch_decode_ragged(const reskv_shape_t& s, const reskv_gate_t& g, const RaggedPlan& pl,
                                 const void* q, void* kc, void* vc, const float* logc, const int32_t* res_len,
                                 int32_t* main_len, const void* k_new, const void* v_new, float* out,

@@ -36,6 +36,9 @@ struct RaggedPlan {
   size_t plan_off, rec_off, bytes;
 };
 bool make_ragged_plan(const reskv_shape_t& s, RaggedPlan* plan);
+// Shapes whose ragged calls reskv_decode_attn's kernels serve faster whatever
+// the lengths are.
+bool ragged_takes_decode(const reskv_shape_t& s);
 hipError_t launch_decode_ragged(const reskv_shape_t& s, const reskv_gate_t& g, const RaggedPlan& pl,
                                 const void* q, void* kc, void* vc, const float* logc, const int32_t* res_len,
                                 int32_t* main_len, const void* k_new, const void* v_new, float* out,

@@ -9,6 +9,7 @@ from tests.build_check import check_head, run_build
 from tests.test_adakv_gpu import check_sequence, workload as ada_workload
 from tests.test_build_gpu import host_copies
 from tests.test_decode_gpu import cache_case, check
+from tests.test_decode_ragged_gpu import run_ragged
 from tests.test_graph_gpu import test_decode_step_graph_replays_match_eager as graph_replays
 
 pytestmark = pytest.mark.gpu
@@ -136,3 +137,20 @@ def test_split_decode_graph_replays():
     read and store the new token, then the combine, which advances the main
     lengths."""
     graph_replays(2, 2, 7, 900)
+
+
+@pytest.mark.parametrize("dtype,d,B,Hkv,G,C,longest", [
+    ("bf16", 128, 64, 4, 7, 1536, 1500),  # the per-head kernels' last capacity at 256 pairs
+    ("bf16", 64, 3, 4, 7, 2304, 700),     # and their longest capacity, split-K
+    ("bf16", 128, 3, 4, 7, 2305, 700),    # one slot more: fewer units than blocks, equal ranges
+    ("f32", 64, 2, 2, 2, 2400, 2390),     # equal ranges, a head over many one-unit blocks
+    ("bf16", 64, 65, 4, 4, 300, 290),     # 260 pairs: equal ranges
+])
+def test_ragged_schedule_line(dtype, d, B, Hkv, G, C, longest):
+    """Both sides of the line between the per-head kernels and the equal unit
+    ranges of ragged calls, with appends."""
+    rng = np.random.default_rng(C)
+    res = rng.choice([0, 16, 40, 64], size=(B, Hkv))
+    main = rng.integers(1, longest - 64, size=(B, Hkv))
+    main[0, 0] = longest - res[0, 0]
+    run_ragged(dtype, B, Hkv, G, d, C, 64, res, main, seed=C, compare_head=True)
