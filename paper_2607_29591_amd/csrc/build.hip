@@ -104,6 +104,8 @@ struct BuildArgs {
   int32_t* ada_hist;   // [BH][kAdaHist] cross-head search histograms (zeroed by pool_scores), or NULL
   uint32_t* ada_state; // [2][B][kAdaState] per sequence: prefix, then the heads' tokens above its range
   uint32_t* sel_state; // [BH][2][4] thresholds' prefixes and remaining ranks after the first and second pass
+  int NC;              // candidates built in one batch
+  int SBH;             // heads with keys and values of their own, B * Hkv of one candidate
   int B, Hq, Hkv, G, C, Rcap, S, w, R, LG, KG, NCH, NBLK, T;
   int lpiece, NIT, NPART;  // log2 of the members per update piece, pieces and partial slots per head
   int wr;              // leading window rows per query head that score (R = G * wr)
@@ -122,6 +124,10 @@ __device__ __forceinline__ void block_head(const BuildArgs& a, int rev, int& b, 
   b = bh / a.Hkv;
   kvh = bh - b * a.Hkv;
 }
+
+// Head whose keys, values and raw scores head bh reads: with several candidate
+// constructions in one batch (the proxy's), heads bh, bh + SBH, ... are copies.
+__device__ __forceinline__ int source_head(const BuildArgs& a, int bh) { return bh % a.SBH; }
 
 __device__ __forceinline__ float to_f32(uint16_t x) { return __uint_as_float((uint32_t)x << 16); }
 __device__ __forceinline__ float to_f32(float x) { return x; }
@@ -307,7 +313,7 @@ __global__ __launch_bounds__(kThreads) void lse_final(BuildArgs a) {
   const int bh = b * a.Hkv + kvh;
   const HeadMeta hm = a.meta[bh];
   const int t = blockIdx.x * kThreads + threadIdx.x;
-  zero_sel_hist(a, bh, t, gridDim.x * kThreads);
+  for (int c = 0; c < a.NC; ++c) zero_sel_hist(a, c * a.SBH + bh, t, gridDim.x * kThreads);
   if (hm.all_main || t >= a.R) return;
   const int nch = (hm.s + 256 * a.LG - 1) / (256 * a.LG);
   const float2* pp = a.lse_part + (size_t)bh * a.NCH * a.R + t;
@@ -471,7 +477,7 @@ __global__ __launch_bounds__(kPoolThreads) void pool_scores(BuildArgs a) {
   for (int i = tid; i < kSelBins; i += kPoolThreads) s_hist[i] = 0;
   const int p0 = b0 + tid * kPoolPer;
   const int ph = a.pool_half;
-  const float* raw = a.raw + (size_t)bh * a.S;
+  const float* raw = a.raw + (size_t)source_head(a, bh) * a.S;
   float w[kPoolPer + 2 * kPoolHalfMax];  // raw[p0 - kPoolHalfMax + i]
 #pragma unroll
   for (int i = 0; i < kPoolPer + 2 * kPoolHalfMax; ++i) {
@@ -987,8 +993,8 @@ __global__ __launch_bounds__(kThreads) void gather_init(BuildArgs a) {
   const int bh = b * a.Hkv + kvh;
   const HeadMeta hm = a.meta[bh];
   constexpr int kChunks = D * (int)sizeof(T) / 16;  // 16-byte chunks per row
-  const T* K = static_cast<const T*>(a.k) + (size_t)bh * a.S * D;
-  const T* V = static_cast<const T*>(a.v) + (size_t)bh * a.S * D;
+  const T* K = static_cast<const T*>(a.k) + (size_t)source_head(a, bh) * a.S * D;
+  const T* V = static_cast<const T*>(a.v) + (size_t)source_head(a, bh) * a.S * D;
   T* kc = static_cast<T*>(a.kc) + (size_t)bh * a.C * D;
   T* vc = static_cast<T*>(a.vc) + (size_t)bh * a.C * D;
   const int32_t* main_idx = a.main_idx + (size_t)bh * a.C;
@@ -1148,7 +1154,7 @@ __global__ __launch_bounds__((AssignShape<T, D, kLo>::kThreads), (AssignShape<T,
   __shared__ float s_norm[kCC];
   extern __shared__ int s_hist[];  // [r_eff]: one 256-token histogram block at a time
 
-  const T* K = static_cast<const T*>(a.k) + (size_t)bh * a.S * D;
+  const T* K = static_cast<const T*>(a.k) + (size_t)source_head(a, bh) * a.S * D;
   const int32_t* elist = a.elist + (size_t)bh * a.S;
   const int tw = t0 + wave * 16 * kTT;  // this wave's first token
   Frag<T, D> tk[kTT];
@@ -1570,8 +1576,8 @@ __global__ __launch_bounds__(kThreads, (kKV && sizeof(T) == 2 ? 4 : sizeof(T) ==
   const size_t ci = (size_t)bh * a.Rcap + j;
   const int cnt = min(1 << a.lpiece, total - (piece << a.lpiece));  // members of this piece
   const int32_t* mem = a.order + (size_t)bh * a.S + item.z;
-  const T* K = static_cast<const T*>(a.k) + (size_t)bh * a.S * D;
-  const T* V = static_cast<const T*>(a.v) + (size_t)bh * a.S * D;
+  const T* K = static_cast<const T*>(a.k) + (size_t)source_head(a, bh) * a.S * D;
+  const T* V = static_cast<const T*>(a.v) + (size_t)source_head(a, bh) * a.S * D;
   double sk = 0.0, sv = 0.0;  // key and value sums of column tid (threads tid < D)
   // the member groups' sums of one column in ascending order
   auto reduce = [&](const double (&acc)[8]) {
@@ -1775,6 +1781,7 @@ BuildArgs make_args(const BuildPlan& pl, const void* k, const void* v, const voi
   a.lpiece = pl.lpiece; a.NIT = pl.NIT; a.NPART = pl.NPART;
   a.sel_hist = reinterpret_cast<int32_t*>(ws + pl.off_selh);
   a.sel_state = reinterpret_cast<uint32_t*>(ws + pl.off_sels);
+  a.NC = pl.NC; a.SBH = pl.B * pl.Hkv;
   a.B = pl.B; a.Hq = pl.Hq; a.Hkv = pl.Hkv; a.G = pl.G; a.C = pl.C; a.Rcap = pl.Rcap; a.S = pl.S; a.w = pl.w;
   a.wr = pl.wr; a.pool_half = pl.pool_half; a.R = pl.R; a.LG = pl.LG; a.KG = pl.KG; a.NCH = pl.NCH; a.NBLK = pl.NBLK; a.T = pl.T;
   a.cap_slots = pl.C;
@@ -1822,8 +1829,8 @@ hipError_t launch_scores_typed(const BuildPlan& pl, const BuildArgs& a, hipStrea
 template <typename T, int D>
 hipError_t launch_candidate_typed(const BuildPlan& pl, const BuildArgs& a, hipStream_t st,
                                   HeadMeta* alloc_meta = nullptr, double safeguard = 1.0) {
-  const dim3 bhg(1, pl.Hkv, pl.B);
-  auto grid = [&](int x) { return dim3(x < 1 ? 1 : x, pl.Hkv, pl.B); };
+  const dim3 bhg(1, pl.Hkv, a.B);
+  auto grid = [&](int x) { return dim3(x < 1 ? 1 : x, pl.Hkv, a.B); };
   hipError_t e;
   if (a.dbg_assign) {
     hipLaunchKernelGGL(fill_i32, dim3(1024), dim3(256), 0, st, a.dbg_assign,
@@ -1902,6 +1909,7 @@ void init_build_plan(const reskv_shape_t& s, const reskv_build_params_t& p, Buil
   pl.D = s.head_dim; pl.C = s.slot_cap; pl.Rcap = s.res_cap; pl.S = p.max_seq_len; pl.w = p.obs_window;
   pl.wr = p.fit_rows > 0 ? p.fit_rows : p.obs_window;
   pl.pool_half = (p.pool_kernel > 0 ? p.pool_kernel : 5) / 2;
+  pl.NC = 1;
   pl.R = pl.G * pl.wr; pl.T = p.lloyd_iters; pl.dtype = s.dtype;
 }
 
@@ -1921,6 +1929,7 @@ bool layout_build_plan(BuildPlan* plan) {
   BuildPlan& pl = *plan;
   if (pl.R > 1024 || pl.Rcap > 4096) return false;
   const size_t BH = (size_t)pl.B * pl.Hkv;
+  const size_t CH = BH * pl.NC;  // heads the candidates build at a time
   // the lse pass takes 16, 8 or 4 key groups per block: the longest chunks
   // that still give at least 1024 blocks (fewer blocks write fewer partial
   // records and stage the window rows fewer times)
@@ -1942,7 +1951,7 @@ bool layout_build_plan(BuildPlan* plan) {
                 (long long)nb64 * pl.max_reff <= kSortTable;
   // update pieces of 256 members while the whole construction has fewer than
   // kPieceMin of 1024 (short chains where few blocks are in flight), else 1024
-  pl.lpiece = BH * (size_t)((pl.max_E + 1023) / 1024) < kPieceMin ? 8 : 10;
+  pl.lpiece = CH * (size_t)((pl.max_E + 1023) / 1024) < kPieceMin ? 8 : 10;
   while (pl.max_E >> pl.lpiece > 16384) ++pl.lpiece;  // piece counts stay below 2^16 (lloyd_offsets packs them)
   pl.NIT = pl.max_reff + (pl.max_E >> pl.lpiece);  // sum over groups of max(1, ceil(count / piece))
   pl.NPART = 2 * (pl.max_E >> pl.lpiece);        // groups above one piece: ceil(c / piece) <= 2 c / piece
@@ -1952,22 +1961,22 @@ bool layout_build_plan(BuildPlan* plan) {
   pl.off_lsep = take(BH * pl.NCH * pl.R * sizeof(float2));
   pl.off_lse = take(BH * pl.R * sizeof(float));
   pl.off_raw = take(BH * pl.S * sizeof(float));
-  pl.off_score = take(BH * pl.S * sizeof(float));
-  pl.off_elist = take(BH * pl.S * sizeof(int32_t));
-  pl.off_seeds = take(BH * pl.Rcap * sizeof(int32_t));
-  pl.off_cent = take(BH * pl.Rcap * pl.D * sizeof(float));
-  pl.off_chi = take(BH * pl.Rcap * pl.D * sizeof(uint16_t));
-  pl.off_clo = take(BH * pl.Rcap * pl.D * sizeof(uint16_t));
-  pl.off_cnorm = take(BH * pl.Rcap * sizeof(float));
-  pl.off_assign = take(BH * pl.S * sizeof(int32_t));
-  pl.off_hist = take(pl.one_sort ? 0 : BH * pl.NBLK * pl.Rcap * sizeof(int32_t));
-  pl.off_order = take(BH * pl.S * sizeof(int32_t));
-  pl.off_items = take(BH * pl.NIT * sizeof(int4));
-  pl.off_nitem = take(BH * sizeof(int32_t));
-  pl.off_parrive = take(BH * pl.Rcap * sizeof(int32_t));
-  pl.off_part = take(BH * pl.NPART * 2 * pl.D * sizeof(double));
-  pl.off_selh = take(BH * kSelHist * sizeof(int32_t));
-  pl.off_sels = take(BH * 8 * sizeof(uint32_t));
+  pl.off_score = take(CH * pl.S * sizeof(float));
+  pl.off_elist = take(CH * pl.S * sizeof(int32_t));
+  pl.off_seeds = take(CH * pl.Rcap * sizeof(int32_t));
+  pl.off_cent = take(CH * pl.Rcap * pl.D * sizeof(float));
+  pl.off_chi = take(CH * pl.Rcap * pl.D * sizeof(uint16_t));
+  pl.off_clo = take(CH * pl.Rcap * pl.D * sizeof(uint16_t));
+  pl.off_cnorm = take(CH * pl.Rcap * sizeof(float));
+  pl.off_assign = take(CH * pl.S * sizeof(int32_t));
+  pl.off_hist = take(pl.one_sort ? 0 : CH * pl.NBLK * pl.Rcap * sizeof(int32_t));
+  pl.off_order = take(CH * pl.S * sizeof(int32_t));
+  pl.off_items = take(CH * pl.NIT * sizeof(int4));
+  pl.off_nitem = take(CH * sizeof(int32_t));
+  pl.off_parrive = take(CH * pl.Rcap * sizeof(int32_t));
+  pl.off_part = take(CH * pl.NPART * 2 * pl.D * sizeof(double));
+  pl.off_selh = take(CH * kSelHist * sizeof(int32_t));
+  pl.off_sels = take(CH * 8 * sizeof(uint32_t));
   pl.bytes = off;
   return true;
 }
@@ -2003,15 +2012,15 @@ bool make_build_plan(const reskv_shape_t& s, const reskv_build_params_t& p, cons
 }
 
 hipError_t upload_meta(const BuildPlan& pl, const int32_t* seq_len, const int32_t* budget,
-                       const int32_t* res_count, int recent, HeadMeta* meta, hipStream_t stream) {
-  const int BH = pl.B * pl.Hkv;
+                       const int32_t* res_count, int sets, int recent, HeadMeta* meta, hipStream_t stream) {
+  const int SBH = pl.B * pl.Hkv, BH = sets * SBH;
   for (int first = 0; first < BH; first += kMetaChunk) {
     MetaChunk c;
     c.first = first;
     c.count = BH - first < kMetaChunk ? BH - first : kMetaChunk;
     c.recent = recent;
     for (int i = 0; i < c.count; ++i) {
-      const int bh = first + i, b = bh / pl.Hkv;
+      const int bh = first + i, b = bh % SBH / pl.Hkv;
       c.s[i] = seq_len[b];
       c.r[i] = res_count[bh];
       c.budget[i] = budget[b];
@@ -2040,7 +2049,7 @@ hipError_t launch_build_adakv(const reskv_shape_t& s, const reskv_build_params_t
                               float* dbg_centers, void* workspace, hipStream_t stream) {
   (void)s;
   HeadMeta* meta = reinterpret_cast<HeadMeta*>(static_cast<char*>(workspace) + pl.off_meta);
-  hipError_t e = upload_meta(pl, seq_len, budget, res_count, p.recent_window, meta, stream);
+  hipError_t e = upload_meta(pl, seq_len, budget, res_count, 1, p.recent_window, meta, stream);
   if (e != hipSuccess) return e;
   e = launch_build_scores(pl, k, q_obs, meta, workspace, stream);
   if (e != hipSuccess) return e;
@@ -2062,7 +2071,8 @@ hipError_t launch_build_adakv(const reskv_shape_t& s, const reskv_build_params_t
 hipError_t launch_build_candidate(const BuildPlan& pl, const void* k, const void* v, const HeadMeta* meta,
                                   const BuildOut& out, float* dbg_scores, int32_t* dbg_assign, float* dbg_centers,
                                   void* workspace, hipStream_t stream) {
-  const BuildArgs a = make_args(pl, k, v, nullptr, meta, out, dbg_scores, dbg_assign, dbg_centers, workspace);
+  BuildArgs a = make_args(pl, k, v, nullptr, meta, out, dbg_scores, dbg_assign, dbg_centers, workspace);
+  a.B = pl.B * pl.NC;
   const bool bf = pl.dtype == RESKV_BF16;
   if (pl.D == 128) return bf ? launch_candidate_typed<uint16_t, 128>(pl, a, stream) : launch_candidate_typed<float, 128>(pl, a, stream);
   if (pl.D == 64) return bf ? launch_candidate_typed<uint16_t, 64>(pl, a, stream) : launch_candidate_typed<float, 64>(pl, a, stream);
@@ -2077,7 +2087,7 @@ hipError_t launch_build(const reskv_shape_t& s, const reskv_build_params_t& p, c
                         hipStream_t stream) {
   (void)s;
   HeadMeta* meta = reinterpret_cast<HeadMeta*>(static_cast<char*>(workspace) + pl.off_meta);
-  hipError_t e = upload_meta(pl, seq_len, budget, res_count, p.recent_window, meta, stream);
+  hipError_t e = upload_meta(pl, seq_len, budget, res_count, 1, p.recent_window, meta, stream);
   if (e != hipSuccess) return e;
   e = launch_build_scores(pl, k, q_obs, meta, workspace, stream);
   if (e != hipSuccess) return e;

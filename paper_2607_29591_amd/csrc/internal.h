@@ -85,6 +85,7 @@ struct BuildPlan {
   int wr;     // leading window rows per query head that score
   int pool_half;  // score pooling taps on each side
   int R;      // scoring rows per kv head, G * wr
+  int NC;     // candidate counts built in one batch (scratch and grids for B * NC sequences), 1 but for the proxy
   int LG;     // 256-key groups per lse block
   int NCH;    // lse key chunks (256 * LG keys) of the longest sequence
   int KG;     // 256-key groups per score-pass block
@@ -120,14 +121,14 @@ void head_meta(const BuildPlan& pl, const int32_t* seq_len, const int32_t* budge
 bool fold_build_plan(const std::vector<HeadMeta>& hm, BuildPlan* plan);
 bool layout_build_plan(BuildPlan* plan);
 
-// Writes the head sizes of res_count[B*Hkv] to meta[B*Hkv] on the stream.
+// Writes the head sizes of res_count[sets][B*Hkv] to meta[sets][B*Hkv] on the stream.
 hipError_t upload_meta(const BuildPlan& pl, const int32_t* seq_len, const int32_t* budget,
-                       const int32_t* res_count, int recent, HeadMeta* meta, hipStream_t stream);
+                       const int32_t* res_count, int sets, int recent, HeadMeta* meta, hipStream_t stream);
 // Raw window scores into the workspace, for the scored positions of `meta`.
 hipError_t launch_build_scores(const BuildPlan& pl, const void* k, const void* q_obs, const HeadMeta* meta,
                                void* workspace, hipStream_t stream);
 // Pooling, selection, gather and Lloyd rounds from the workspace's raw
-// scores, for the counts of `meta`, writing `out`.
+// scores, for the counts of `meta` (pl.NC sets of them), writing `out`.
 hipError_t launch_build_candidate(const BuildPlan& pl, const void* k, const void* v, const HeadMeta* meta,
                                   const BuildOut& out, float* dbg_scores, int32_t* dbg_assign, float* dbg_centers,
                                   void* workspace, hipStream_t stream);
@@ -166,8 +167,7 @@ struct ProxyPlan {
   int val;                  // validation rows per query head
   int GV;                   // validation queries per kv head, G * val
   int NQC, GC;              // query chunks of at most 16 queries, queries per chunk
-  std::vector<int32_t> counts;  // [NG][B*Hkv] candidate counts
-  std::vector<int32_t> r_max;   // [B*Hkv] largest candidate count (its scored positions cover all)
+  std::vector<int32_t> counts;  // [NG + 1][B*Hkv] candidate counts, then the largest (its scored positions cover all)
   DecodePlan dec_full, dec_cand;
   size_t off_meta;          // [NG + 1][B*Hkv] HeadMeta (candidates, then scoring)
   size_t off_kc, off_vc;    // [NG*B][Hkv][C][d]

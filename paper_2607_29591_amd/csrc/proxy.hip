@@ -5,8 +5,9 @@
 //   scoring        the fit rows score once, for the scored positions of the
 //                  largest candidate count (every smaller count scores a
 //                  prefix of them; raw scores do not depend on the count)
-//   candidates     for each grid count: pooling, selection, gather and Lloyd
-//                  rounds into that candidate's own cache in the workspace
+//   candidates     for each grid count (all of them in one batch when the
+//                  heads are few): pooling, selection, gather and Lloyd rounds
+//                  into that candidate's own cache in the workspace
 //   gather_q       the G * val validation queries of every kv head, in
 //                  chunks of at most 16 heads, as decode queries (repeated
 //                  once per candidate: candidate c of sequence b is decode
@@ -28,6 +29,7 @@ namespace reskv {
 namespace {
 
 constexpr int kThreads = 256;
+constexpr int kBatchHeads = 64;       // (b, kv head) pairs up to which the candidates are built in one batch
 constexpr int kMaxChunkQueries = 16;  // decode handles groups of at most 16 query heads
 
 // Validation query jj = h * val + i of kv head kvh is window row fit + i of
@@ -226,19 +228,23 @@ bool make_proxy_plan(const reskv_shape_t& s, const reskv_build_params_t& p, cons
   pl.NQC = (pl.GV + kMaxChunkQueries - 1) / kMaxChunkQueries;
   pl.GC = (pl.GV + pl.NQC - 1) / pl.NQC;
   // candidate counts r = floor(f * b + 1/2), the same for the kv heads of a sequence
-  pl.counts.assign((size_t)pl.NG * BH, 0);
-  pl.r_max.assign(BH, 0);
+  pl.counts.assign((size_t)(pl.NG + 1) * BH, 0);
+  int32_t* r_max = pl.counts.data() + (size_t)pl.NG * BH;
   for (int c = 0; c < pl.NG; ++c)
     for (int bh = 0; bh < BH; ++bh) {
       const int r = (int)floor(x.grid_host[c] * (double)budget[bh / bp.Hkv] + 0.5);
       pl.counts[(size_t)c * BH + bh] = r;
-      if (r > pl.r_max[bh]) pl.r_max[bh] = r;
+      if (r > r_max[bh]) r_max[bh] = r;
     }
   std::vector<HeadMeta> hm;
   for (int c = 0; c < pl.NG; ++c) {
     head_meta(bp, seq_len, budget, pl.counts.data() + (size_t)c * BH, p.recent_window, hm);
     if (!fold_build_plan(hm, &bp)) return false;
   }
+  // All candidates in one batch while a candidate's heads leave the launches
+  // short (16 heads of 32K tokens, five candidates: 2320 -> 1790 us); a larger
+  // batch fills the GPU by itself and would only take the scratch five times.
+  bp.NC = BH <= kBatchHeads ? pl.NG : 1;
   if (!layout_build_plan(&bp)) return false;
   pl.dec_full = make_decode_plan(full_shape(pl));
   pl.dec_cand = make_decode_plan(cand_shape(pl));
@@ -290,14 +296,11 @@ hipError_t launch_build_proxy(const reskv_shape_t& s, const reskv_build_params_t
   int32_t* mlen_c = reinterpret_cast<int32_t*>(ws + pl.off_mlen);
   hipError_t e;
 #define RESKV_TRY(expr) do { e = (expr); if (e != hipSuccess) return e; } while (0)
-  for (int c = 0; c < pl.NG; ++c)
-    RESKV_TRY(upload_meta(bp, seq_len, budget, pl.counts.data() + (size_t)c * BH, p.recent_window,
-                          cmeta + (size_t)c * BH, stream));
-  RESKV_TRY(upload_meta(bp, seq_len, budget, pl.r_max.data(), p.recent_window, smeta, stream));
+  RESKV_TRY(upload_meta(bp, seq_len, budget, pl.counts.data(), pl.NG + 1, p.recent_window, cmeta, stream));
   // scoring once with the fit rows; the build scratch sits at the start of the workspace
   RESKV_TRY(launch_build_scores(bp, k, q_obs, smeta, workspace, stream));
   const size_t cache_elems = (size_t)BH * bp.C * bp.D;  // elements of one candidate's kc
-  for (int c = 0; c < pl.NG; ++c) {
+  for (int c = 0; c < pl.NG; c += bp.NC) {  // candidates c .. c + NC - 1, laid out one after the other
     const BuildOut out{kc_c + c * cache_elems * esz, vc_c + c * cache_elems * esz,
                        logc_c + (size_t)c * BH * bp.Rcap, midx_c + (size_t)c * BH * bp.C,
                        rlen_c + (size_t)c * BH, mlen_c + (size_t)c * BH};

@@ -10,6 +10,7 @@ from tests.test_adakv_gpu import check_sequence, workload as ada_workload
 from tests.test_build_gpu import host_copies
 from tests.test_decode_gpu import cache_case, check
 from tests.test_decode_ragged_gpu import run_ragged
+from tests.test_proxy_gpu import GRID, check_proxy
 from tests.test_graph_gpu import test_decode_step_graph_replays_match_eager as graph_replays
 
 pytestmark = pytest.mark.gpu
@@ -154,3 +155,14 @@ def test_ragged_schedule_line(dtype, d, B, Hkv, G, C, longest):
     main = rng.integers(1, longest - 64, size=(B, Hkv))
     main[0, 0] = longest - res[0, 0]
     run_ragged(dtype, B, Hkv, G, d, C, 64, res, main, seed=C, compare_head=True)
+
+
+@pytest.mark.parametrize("B", [8, 9])
+def test_proxy_candidate_batches(B):
+    """64 heads: every candidate in one batch; 72 heads: one after the other.
+    Each candidate equal to the same construction alone either way."""
+    wl = synth.tiny_workload(s=150, d=64, hq=8, hkv=8, budget=40, res=0, window=8, dtype="bf16", batch=B, n_heavy=3)
+    wl.ctx = [150 - 7 * b for b in range(B)]
+    wl.res = np.full((1, B, 8), 8)
+    x = host_copies(synth.gen_layer(wl, 0, seed=B, n_decode=1))
+    check_proxy(wl, x, GRID, 2, 0.01, full_heads=[(0, 0), (B - 1, 7)])
