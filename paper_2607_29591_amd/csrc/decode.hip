@@ -4,7 +4,8 @@
 //   decode_head    one block of 8 waves per (b, kv head) streams every slot
 //                  of the head, merges the waves in LDS, applies the gate
 //                  and writes the outputs (used when the (b, kv head) pairs
-//                  alone fill the GPU); it can append this step's token.
+//                  fill enough of the GPU or the caches are short,
+//                  make_decode_plan); it can append this step's token.
 //   decode_split + decode_combine
 //                  split-K: one block = 256 slots of one (b, kv head), all of
 //                  one kind (residual slots [0, r) or main slots [r, r+n)),
@@ -424,7 +425,10 @@ __global__ __launch_bounds__(kThreads) void decode_split(DecodeArgs a) {
 // kSliced: the outputs are dealt to gridDim.z blocks (256 each in turn), every
 // block forming all weights; only for calls without an append, since main_len
 // may advance only after every block has read it.
-template <int D, int GP, bool kSliced>
+// kBranches: two-branch form. Each kind's records are merged under its own
+// softmax: out = main-branch output, out_res = residual-branch output (0
+// without populated entries), the log-sum-exps without the gate, the gate.
+template <int D, int GP, bool kSliced, bool kBranches>
 __global__ __launch_bounds__(kThreads) void decode_combine(DecodeArgs a) {
   extern __shared__ float s_w[];  // [GP][P] weights of the records
   const int kvh = blockIdx.x, b = blockIdx.y;
@@ -488,11 +492,13 @@ __global__ __launch_bounds__(kThreads) void decode_combine(DecodeArgs a) {
     if (mM != kNegInf) den += lM * exp2f(mM - Mx);
     if (mRg != kNegInf) den += lR * exp2f(mRg - Mx);
     const float inv = den > 0.f ? 1.f / den : 0.f;
+    const float invM = lM > 0.f ? 1.f / lM : 0.f, invR = lR > 0.f ? 1.f / lR : 0.f;
     for (int k = 0, p = lane16; p < a.P; ++k, p += 16) {
       const float m = rec(k, p).x;
       float w = 0.f;
       if (valid(p) && m != kNegInf) {
-        if (p >= a.PR) w = exp2f(m - Mx) * inv;
+        if (kBranches) w = p >= a.PR ? exp2f(m - mM) * invM : exp2f(m - mR) * invR;
+        else if (p >= a.PR) w = exp2f(m - Mx) * inv;
         else if (mRg != kNegInf) w = exp2f(m + lg2g - Mx) * inv;
       }
       s_w[h * a.P + p] = w;
@@ -510,88 +516,28 @@ __global__ __launch_bounds__(kThreads) void decode_combine(DecodeArgs a) {
     if (idx >= a.G * D) continue;
     const int hh = idx / D, d = idx % D;
     const float* w = s_w + hh * a.P;
-    float o = 0.f;
+    float o = 0.f, oR = 0.f;
+    auto add = [&](int j, float v) {
+      if (j >= a.P || !valid(j)) return;
+      if (kBranches && j < a.PR) oR = fmaf(w[j], v, oR);
+      else o = fmaf(w[j], v, o);
+    };
 #pragma unroll
-    for (int j = 0; j < kPF; ++j)
-      if (j < a.P && valid(j)) o = fmaf(w[j], pv[k][j], o);
+    for (int j = 0; j < kPF; ++j) add(j, pv[k][j]);
     for (int j0 = kPF; j0 < a.P; j0 += kPF) {  // further records, kPF requests in flight
       float v[kPF];
 #pragma unroll
       for (int j = 0; j < kPF; ++j) v[j] = j0 + j < a.P ? pacc[((j0 + j) * GP + hh) * D + d] : 0.f;
 #pragma unroll
-      for (int j = 0; j < kPF; ++j)
-        if (j0 + j < a.P && valid(j0 + j)) o = fmaf(w[j0 + j], v[j], o);
+      for (int j = 0; j < kPF; ++j) add(j0 + j, v[j]);
     }
-    a.out[((size_t)b * a.Hq + kvh * a.G + hh) * D + d] = o;
+    const size_t at = ((size_t)b * a.Hq + kvh * a.G + hh) * D + d;
+    a.out[at] = o;
+    if (kBranches) a.out_res[at] = oR;
   }
   // the appended token is in the cache: advance main_len (one block per
   // head, and every thread of it read the length above)
   if (app && tid == 0) a.main_len[bh] = n;
-}
-
-
-// Two-branch combine: the split records of each kind are merged under that
-// kind's own softmax. out = main-branch output, out_res = residual-branch
-// output (0 without populated entries), dbg_lse_main / dbg_lse_res their
-// natural log-sum-exp (the residual one without the gate), dbg_gate the gate.
-template <int D, int GP>
-__global__ __launch_bounds__(kThreads) void decode_branches(DecodeArgs a) {
-  extern __shared__ float s_w[];  // [GP][P] weights of the records
-  const int kvh = blockIdx.x, b = blockIdx.y;
-  const int bh = b * a.Hkv + kvh;
-  int r, n;
-  cache_lengths(a.res_len, a.main_len, bh, a.C, a.Rcap, r, n);
-  const int nRC = (r + kChunk - 1) / kChunk, nMC = (n + kChunk - 1) / kChunk;
-  const float* ml = a.part_ml + (size_t)bh * a.P * GP * 2;
-  const float* pacc = a.part_acc + (size_t)bh * a.P * GP * D;
-  const int tid = threadIdx.x, lane16 = tid & 15, h = tid >> 4;
-  if (h < a.G) {
-    float mM = kNegInf, mR = kNegInf;
-    for (int q = lane16; q < nMC; q += 16) mM = fmaxf(mM, ml[((a.PR + q) * GP + h) * 2]);
-    for (int q = lane16; q < nRC; q += 16) mR = fmaxf(mR, ml[(q * GP + h) * 2]);
-#pragma unroll
-    for (int msk = 1; msk < 16; msk <<= 1) { mM = wave_xor_max(mM, msk); mR = wave_xor_max(mR, msk); }
-    float lM = 0.f, lR = 0.f;
-    for (int q = lane16; q < nMC; q += 16) {
-      const float* e = ml + ((a.PR + q) * GP + h) * 2;
-      if (e[0] != kNegInf) lM = fmaf(e[1], exp2f(e[0] - mM), lM);
-    }
-    for (int q = lane16; q < nRC; q += 16) {
-      const float* e = ml + (q * GP + h) * 2;
-      if (e[0] != kNegInf) lR = fmaf(e[1], exp2f(e[0] - mR), lR);
-    }
-#pragma unroll
-    for (int msk = 1; msk < 16; msk <<= 1) { lM = wave_xor_add(lM, msk); lR = wave_xor_add(lR, msk); }
-    const float pmax = lM > 0.f ? 1.f / lM : 1.f;
-    const int qh = b * a.Hq + kvh * a.G + h;
-    const float tau = a.tau ? a.tau[qh] : a.tau_scalar;
-    const float g = fmaxf(a.g_min, 1.f / (1.f + expf(-(tau - pmax) * a.alpha)));
-    const float invM = lM > 0.f ? 1.f / lM : 0.f, invR = lR > 0.f ? 1.f / lR : 0.f;
-    for (int q = lane16; q < nMC; q += 16) {
-      const float m = ml[((a.PR + q) * GP + h) * 2];
-      s_w[h * a.P + a.PR + q] = m != kNegInf ? exp2f(m - mM) * invM : 0.f;
-    }
-    for (int q = lane16; q < nRC; q += 16) {
-      const float m = ml[(q * GP + h) * 2];
-      s_w[h * a.P + q] = m != kNegInf ? exp2f(m - mR) * invR : 0.f;
-    }
-    if (lane16 == 0) {
-      a.dbg_lse_main[qh] = lM > 0.f ? (mM + log2f(lM)) * kLn2 : kNegInf;
-      a.dbg_lse_res[qh] = lR > 0.f ? (mR + log2f(lR)) * kLn2 : kNegInf;
-      a.dbg_gate[qh] = g;
-    }
-  }
-  __syncthreads();
-  for (int idx = tid; idx < a.G * D; idx += kThreads) {
-    const int hh = idx / D, d = idx % D;
-    const float* w = s_w + hh * a.P;
-    float oR = 0.f, oM = 0.f;
-    for (int q = 0; q < nRC; ++q) oR = fmaf(w[q], pacc[(q * GP + hh) * D + d], oR);
-    for (int q = 0; q < nMC; ++q) oM = fmaf(w[a.PR + q], pacc[((a.PR + q) * GP + hh) * D + d], oM);
-    const size_t o = ((size_t)b * a.Hq + kvh * a.G + hh) * D + d;
-    a.out[o] = oM;
-    a.out_res[o] = oR;
-  }
 }
 
 // Merge of the two branches, one thread per output element: the
@@ -623,8 +569,9 @@ __global__ __launch_bounds__(kThreads) void merge_branches_kernel(const float* o
 
 // One block of 8 waves per (b, kv head): streams every slot of the head,
 // merges the wave states in LDS, applies the gate and writes the G outputs;
-// optionally appends this step's token first. Used when the (b, kv head)
-// pairs alone fill the GPU, so no split-K records or second launch are needed.
+// optionally appends this step's token first. No split-K records or second
+// launch; make_decode_plan says when. kBranches: the two branches' own outputs
+// instead (64 pairs of 1024 slots: 17.1 us split and merged, 14.6 us here).
 // 8 waves (2 per SIMD, up to 256 registers each): every variant that needed
 // more registers (a second key buffer for prefetch, or 12-16 waves) spilled
 // to scratch and ran 1.5-3x slower.
@@ -635,7 +582,7 @@ constexpr int kHeadThreads = 64 * kHeadWaves;
 constexpr int kStaggerMod = 24;
 constexpr int kStaggerMul = 5;
 
-template <typename T, int D, int GP>
+template <typename T, int D, int GP, bool kBranches>
 __global__ __launch_bounds__(kHeadThreads) void decode_head(DecodeArgs a) {
   const int kvh = blockIdx.x, b = blockIdx.y;
   const int bh = b * a.Hkv + kvh;
@@ -829,7 +776,12 @@ __global__ __launch_bounds__(kHeadThreads) void decode_head(DecodeArgs a) {
     const float fR = mRg != kNegInf ? exp2f(mRg - Mx) : 0.f;
     const float den = l * fM + lR[k] * fR;
     const float num = oM * fM + oR[k] * fR;
-    a.out[(size_t)qh * D + d] = den > 0.f ? num / den : 0.f;
+    if constexpr (kBranches) {  // each branch under its own softmax
+      a.out[(size_t)qh * D + d] = l > 0.f ? oM / l : 0.f;
+      a.out_res[(size_t)qh * D + d] = lR[k] > 0.f ? oR[k] / lR[k] : 0.f;
+    } else {
+      a.out[(size_t)qh * D + d] = den > 0.f ? num / den : 0.f;
+    }
     if (d == 0) {
       if (a.dbg_lse_main) a.dbg_lse_main[qh] = l > 0.f ? (M + log2f(l)) * kLn2 : kNegInf;
       if (a.dbg_lse_res) a.dbg_lse_res[qh] = lR[k] > 0.f ? (mR[k] + log2f(lR[k])) * kLn2 : kNegInf;
@@ -1218,11 +1170,11 @@ __global__ void append_kernel(const T* k_new, const T* v_new, T* kc, T* vc, cons
   if (threadIdx.x == 0) main_len[bh] = n + 1;
 }
 
-template <typename T, int D, int GP>
+template <typename T, int D, int GP, bool kBranches>
 hipError_t launch_typed(const DecodePlan& pl, const DecodeArgs& da, hipStream_t stream) {
   if constexpr (sizeof(T) == 2 || D == 64) {  // the shapes make_decode_plan sends here
-    if (pl.whole_head && !da.out_res) {
-      hipLaunchKernelGGL((decode_head<T, D, GP>), dim3(pl.Hkv, pl.B), dim3(kHeadThreads), 0, stream, da);
+    if (pl.whole_head) {
+      hipLaunchKernelGGL((decode_head<T, D, GP, kBranches>), dim3(pl.Hkv, pl.B), dim3(kHeadThreads), 0, stream, da);
       return hipGetLastError();
     }
   }
@@ -1230,13 +1182,11 @@ hipError_t launch_typed(const DecodePlan& pl, const DecodeArgs& da, hipStream_t 
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
   const size_t lds = (size_t)GP * pl.P * sizeof(float);
-  if (da.out_res)
-    hipLaunchKernelGGL((decode_branches<D, GP>), dim3(pl.Hkv, pl.B), dim3(kThreads), lds, stream, da);
-  else if (pl.P >= kSliceRecords && GP * D > kThreads && !da.k_new)
-    hipLaunchKernelGGL((decode_combine<D, GP, true>), dim3(pl.Hkv, pl.B, (pl.G * D + kThreads - 1) / kThreads),
-                       dim3(kThreads), lds, stream, da);
+  if (pl.P >= kSliceRecords && GP * D > kThreads && !da.k_new)
+    hipLaunchKernelGGL((decode_combine<D, GP, true, kBranches>),
+                       dim3(pl.Hkv, pl.B, (pl.G * D + kThreads - 1) / kThreads), dim3(kThreads), lds, stream, da);
   else
-    hipLaunchKernelGGL((decode_combine<D, GP, false>), dim3(pl.Hkv, pl.B), dim3(kThreads), lds, stream, da);
+    hipLaunchKernelGGL((decode_combine<D, GP, false, kBranches>), dim3(pl.Hkv, pl.B), dim3(kThreads), lds, stream, da);
   return hipGetLastError();
 }
 
@@ -1263,15 +1213,24 @@ hipError_t launch_ragged_gp(const RaggedPlan& pl, const DecodeArgs& da, hipStrea
   return hipErrorInvalidValue;
 }
 
-template <typename T, int D>
+template <typename T, int D, bool kBranches>
 hipError_t launch_gp(const DecodePlan& pl, const DecodeArgs& da, hipStream_t stream) {
   switch (pl.GP) {
-    case 1: return launch_typed<T, D, 1>(pl, da, stream);
-    case 2: return launch_typed<T, D, 2>(pl, da, stream);
-    case 4: return launch_typed<T, D, 4>(pl, da, stream);
-    case 8: return launch_typed<T, D, 8>(pl, da, stream);
-    case 16: return launch_typed<T, D, 16>(pl, da, stream);
+    case 1: return launch_typed<T, D, 1, kBranches>(pl, da, stream);
+    case 2: return launch_typed<T, D, 2, kBranches>(pl, da, stream);
+    case 4: return launch_typed<T, D, 4, kBranches>(pl, da, stream);
+    case 8: return launch_typed<T, D, 8, kBranches>(pl, da, stream);
+    case 16: return launch_typed<T, D, 16, kBranches>(pl, da, stream);
   }
+  return hipErrorInvalidValue;
+}
+
+template <bool kBranches>
+hipError_t launch_planned(const DecodePlan& pl, bool bf, const DecodeArgs& da, hipStream_t stream) {
+  if (pl.D == 128)
+    return bf ? launch_gp<uint16_t, 128, kBranches>(pl, da, stream) : launch_gp<float, 128, kBranches>(pl, da, stream);
+  if (pl.D == 64)
+    return bf ? launch_gp<uint16_t, 64, kBranches>(pl, da, stream) : launch_gp<float, 64, kBranches>(pl, da, stream);
   return hipErrorInvalidValue;
 }
 
@@ -1406,10 +1365,7 @@ hipError_t launch_decode(const reskv_shape_t& s, const reskv_gate_t& g, const De
   da.qk_scale = kLog2e / sqrtf((float)pl.D);
   da.beta_log2 = g.beta * kLog2e;
   da.tau_scalar = g.tau_scalar; da.alpha = g.alpha; da.g_min = g.g_min;
-  const bool bf = s.dtype == RESKV_BF16;
-  if (pl.D == 128) return bf ? launch_gp<uint16_t, 128>(pl, da, stream) : launch_gp<float, 128>(pl, da, stream);
-  if (pl.D == 64) return bf ? launch_gp<uint16_t, 64>(pl, da, stream) : launch_gp<float, 64>(pl, da, stream);
-  return hipErrorInvalidValue;
+  return launch_planned<false>(pl, s.dtype == RESKV_BF16, da, stream);
 }
 
 namespace {
@@ -1452,10 +1408,7 @@ hipError_t launch_decode_branches(const reskv_shape_t& s, const reskv_gate_t& g,
   da.qk_scale = kLog2e / sqrtf((float)pl.D);
   da.beta_log2 = g.beta * kLog2e;
   da.tau_scalar = g.tau_scalar; da.alpha = g.alpha; da.g_min = g.g_min;
-  const bool bf = s.dtype == RESKV_BF16;
-  if (pl.D == 128) return bf ? launch_gp<uint16_t, 128>(pl, da, stream) : launch_gp<float, 128>(pl, da, stream);
-  if (pl.D == 64) return bf ? launch_gp<uint16_t, 64>(pl, da, stream) : launch_gp<float, 64>(pl, da, stream);
-  return hipErrorInvalidValue;
+  return launch_planned<true>(pl, s.dtype == RESKV_BF16, da, stream);
 }
 
 hipError_t launch_merge_branches(const reskv_shape_t& s, int mode, const float* out_main, const float* lse_main,

@@ -51,7 +51,7 @@ hipError_t launch_decode(const reskv_shape_t& s, const reskv_gate_t& g, const De
                          float* out, float* dbg_lse_main, float* dbg_lse_res, float* dbg_gate,
                          void* workspace, hipStream_t stream);
 
-// The two branches of one decode step under their own softmax (split path).
+// The two branches of one decode step under their own softmax.
 hipError_t launch_decode_branches(const reskv_shape_t& s, const reskv_gate_t& g, const DecodePlan& pl,
                                   const void* q, const void* kc, const void* vc, const float* logc,
                                   const int32_t* res_len, const int32_t* main_len, float* out_main,

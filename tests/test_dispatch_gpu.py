@@ -8,6 +8,7 @@ from paper_2607_29591_amd import synth
 from tests.build_check import check_head, run_build
 from tests.test_adakv_gpu import check_sequence, workload as ada_workload
 from tests.test_build_gpu import host_copies
+from tests.test_decode_branches_gpu import run_case as run_branches
 from tests.test_decode_gpu import cache_case, check
 from tests.test_decode_ragged_gpu import run_ragged
 from tests.test_proxy_gpu import GRID, check_proxy
@@ -166,3 +167,11 @@ def test_proxy_candidate_batches(B):
     wl.res = np.full((1, B, 8), 8)
     x = host_copies(synth.gen_layer(wl, 0, seed=B, n_decode=1))
     check_proxy(wl, x, GRID, 2, 0.01, full_heads=[(0, 0), (B - 1, 7)])
+
+
+@pytest.mark.parametrize("dtype,d,G,C", [("bf16", 128, 7, 600), ("f32", 64, 4, 300), ("bf16", 64, 16, 8300)])
+def test_branches_paths(dtype, d, G, C):
+    """Two-branch decode with one block per head, and through records dealt to
+    several merge blocks; a head without residual entries and one whose
+    entries may all be empty."""
+    run_branches(C, 1, 3 * G, 3, d, dtype, C, 130, [[0, 130, 1]], [[C - 4, 160, 1]])
