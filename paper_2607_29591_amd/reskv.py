@@ -115,10 +115,22 @@ def _ptr(t):
     return t.data_ptr()
 
 
+_raw_stream = None
+
+
 def _stream(stream):
-    import torch
-    s = torch.cuda.current_stream() if stream is None else stream
-    return s.cuda_stream
+    """HIP stream handle; None is the current stream of the current device."""
+    if stream is not None:
+        return stream.cuda_stream
+    global _raw_stream
+    if _raw_stream is None:
+        import torch
+        # the handle itself: building torch's Stream object for it took 2.7 us
+        # of a 7 us call, this 0.3 us
+        raw = getattr(torch._C, "_cuda_getCurrentRawStream", None)
+        dev = torch.cuda.current_device
+        _raw_stream = (lambda: raw(dev())) if raw else (lambda: torch.cuda.current_stream().cuda_stream)
+    return _raw_stream()
 
 
 def make_shape(batch, num_q_heads, num_kv_heads, head_dim, dtype, slot_cap, res_cap):
