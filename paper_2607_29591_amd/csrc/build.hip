@@ -461,6 +461,26 @@ __device__ __forceinline__ int sel_at(int pass, int q) {
   return pass == 0 ? 0 : pass == 1 ? kSelBins * (1 + q) : 3 * kSelBins + 1024 * q;
 }
 
+// Pooled scores of positions p0 .. p0 + kN - 1 (those below n).
+template <int kN>
+__device__ __forceinline__ void pool_run(const BuildArgs& a, const float* raw, int p0, int n, float (&v)[kN]) {
+  const int ph = a.pool_half;
+  float w[kN + 2 * kPoolHalfMax];  // raw[p0 - kPoolHalfMax + i]
+#pragma unroll
+  for (int i = 0; i < kN + 2 * kPoolHalfMax; ++i) {
+    const int q = p0 - kPoolHalfMax + i;
+    const bool tap = q >= p0 - ph && q < p0 + kN + ph;
+    w[i] = tap && q >= 0 && q < n ? raw[q] : 0.f;
+  }
+#pragma unroll
+  for (int k = 0; k < kN; ++k) {
+    v[k] = 0.f;
+#pragma unroll
+    for (int j = -kPoolHalfMax; j <= kPoolHalfMax; ++j)
+      if (j >= -ph && j <= ph) v[k] += w[k + kPoolHalfMax + j];
+  }
+}
+
 // The block also counts its scores' leading digits into the head's first
 // selection histogram.
 __global__ __launch_bounds__(kPoolThreads) void pool_scores(BuildArgs a) {
@@ -476,27 +496,14 @@ __global__ __launch_bounds__(kPoolThreads) void pool_scores(BuildArgs a) {
   const int tid = threadIdx.x, lane = tid & 63;
   for (int i = tid; i < kSelBins; i += kPoolThreads) s_hist[i] = 0;
   const int p0 = b0 + tid * kPoolPer;
-  const int ph = a.pool_half;
-  const float* raw = a.raw + (size_t)source_head(a, bh) * a.S;
-  float w[kPoolPer + 2 * kPoolHalfMax];  // raw[p0 - kPoolHalfMax + i]
-#pragma unroll
-  for (int i = 0; i < kPoolPer + 2 * kPoolHalfMax; ++i) {
-    const int q = p0 - kPoolHalfMax + i;
-    const bool tap = q >= p0 - ph && q < p0 + kPoolPer + ph;
-    w[i] = tap && q >= 0 && q < n ? raw[q] : 0.f;
-  }
+  float pooled[kPoolPer];
+  pool_run(a, a.raw + (size_t)source_head(a, bh) * a.S, p0, n, pooled);
   __syncthreads();  // the histogram is cleared
 #pragma unroll
   for (int k = 0; k < kPoolPer; ++k) {
     const int p = p0 + k;
-    float v = -1.f;
-    if (p < n) {
-      v = 0.f;
-#pragma unroll
-      for (int j = -kPoolHalfMax; j <= kPoolHalfMax; ++j)
-        if (j >= -ph && j <= ph) v += w[k + kPoolHalfMax + j];
-      a.score[(size_t)bh * a.S + p] = v;
-    }
+    const float v = p < n ? pooled[k] : -1.f;
+    if (p < n) a.score[(size_t)bh * a.S + p] = v;
     if (a.dbg_scores && p < a.S) a.dbg_scores[(size_t)bh * a.S + p] = v;
     wave_hist_add(s_hist, __float_as_uint(v) >> sel_shift(0), p < n, lane);
   }
@@ -551,15 +558,15 @@ struct SelState {
   int krem[2];
 };
 
-// Both thresholds' digits of pass `pass` from the head's completed histogram:
+// Both thresholds' digits of pass `pass` from the head's completed histograms
+// (laid out as sel_at says):
 // every thread holds two bins in descending digit order, a block scan counts
 // the scores above them, and the bin that reaches the remaining rank is the
 // digit. While the thresholds share their prefix one histogram serves both.
 // Called by every thread of a kSelThreads block.
-__device__ __forceinline__ void sel_digit(const BuildArgs& a, int bh, int pass, SelState& st) {
+__device__ __forceinline__ void sel_digit(const int* gh, int pass, SelState& st) {
   __shared__ unsigned long long s_scan[kSelThreads / 64];
   __shared__ int s_dig[2], s_above[2];
-  const int* gh = a.sel_hist + (size_t)bh * kSelHist;
   const int tid = threadIdx.x, top = sel_bins(pass) - 1 - 2 * tid;
   const bool shared = pass == 0 || (st.krem[0] > 0 && st.krem[1] > 0 && st.pref[0] == st.pref[1]);
   int c[2][2];
@@ -628,7 +635,7 @@ __global__ __launch_bounds__(kSelThreads) void select_hist(BuildArgs a) {
   }
   for (int i = tid; i < 2 * kBins; i += kSelThreads) (&s_hist[0][0])[i] = 0;
   SelState st = kPass == 1 ? SelState{{0u, 0u}, {hm.k_top, hm.k_top + hm.r_eff}} : sel_load(a, bh, 0);
-  sel_digit(a, bh, kPass - 1, st);  // synchronises the block
+  sel_digit(a.sel_hist + (size_t)bh * kSelHist, kPass - 1, st);  // synchronises the block
   if (blockIdx.x == 0 && tid == 0)
     *reinterpret_cast<uint4*>(a.sel_state + ((size_t)bh * 2 + kPass - 1) * 4) =
         make_uint4(st.pref[0], st.pref[1], (uint32_t)st.krem[0], (uint32_t)st.krem[1]);
@@ -649,15 +656,11 @@ __global__ __launch_bounds__(kSelThreads) void select_hist(BuildArgs a) {
   }
 }
 
-// Placement: main_idx (top-scored, ascending, then the protected recent
-// window), elist (every other scored position, ascending) and seeds (ranks
-// k1 .. k2 - 1, ascending). Each thread owns kSelPer consecutive positions
-// of the block's chunk and ranks them; the block's three runs are gathered
-// in LDS and stored with consecutive lanes on consecutive entries.
-__global__ __launch_bounds__(kSelThreads) void select_write(BuildArgs a) {
-  const int bh = blockIdx.z * a.Hkv + blockIdx.y;
-  const HeadMeta hm = a.meta[bh];
-  const int tid = threadIdx.x, blk = blockIdx.x;
+// Lengths of the outputs, the main list of a head that keeps every token, and
+// the protected recent window behind the top-scored tokens, by block blk of
+// the head.
+__device__ __forceinline__ void sel_fixed(const BuildArgs& a, const HeadMeta& hm, int bh, int blk) {
+  const int tid = threadIdx.x;
   int32_t* main_idx = a.main_idx + (size_t)bh * a.C;
   if (blk == 0 && tid == 0) {
     a.res_len[bh] = hm.r;
@@ -670,8 +673,100 @@ __global__ __launch_bounds__(kSelThreads) void select_write(BuildArgs a) {
   // the protected recent window follows the top-scored tokens
   if (blk == 0)
     for (int i = tid; i < hm.P; i += kSelThreads) main_idx[hm.k_top + i] = hm.n_sc + i;
-  if (blk * kSelChunk >= hm.n_sc) return;  // block-uniform
+}
+
+// Placement: main_idx (top-scored, ascending, then the protected recent
+// window), elist (every other scored position, ascending) and seeds (ranks
+// k1 .. k2 - 1, ascending). Each thread owns kSelPer consecutive positions
+// of the block's chunk and ranks them; the block's three runs are gathered
+// in LDS and stored with consecutive lanes on consecutive entries.
+// Scores of a block's chunk (per consecutive positions per thread in seg, at
+// most kSelPer) into the lists, given the thresholds, how many scores equal
+// to each are taken, and the counts of the blocks before.
+struct SelBase {
+  int e1, e2, top, seed;  // equal to the thresholds, top-scored, seeds
+};
+__device__ __forceinline__ void sel_place(const BuildArgs& a, const HeadMeta& hm, int bh, int blk,
+                                          const uint32_t (&seg)[kSelPer], int per, const SelState& st, const SelBase& base) {
   __shared__ int s_tmp[kSelThreads / 64];
+  const int n = hm.n_sc, i0 = blk * kSelChunk, tid = threadIdx.x, lo = i0 + tid * per;
+  int32_t* main_idx = a.main_idx + (size_t)bh * a.C;
+  const uint32_t T1 = st.pref[0], T2 = st.pref[1];
+  const int need1 = st.krem[0], need2 = st.krem[1];
+  const bool on1 = hm.k_top > 0, on2 = hm.k_top + hm.r_eff > 0;
+  const int base_e1 = base.e1, base_e2 = base.e2, base_top = base.top, base_seed = base.seed;
+  const int base_ev = blk * kSelChunk - base_top;
+  // equal-to-threshold counts per thread, scanned: the tie ranks
+  int e1 = 0, e2 = 0;
+#pragma unroll
+  for (int v = 0; v < kSelPer; ++v)
+    if (v < per && lo + v < n) { e1 += (seg[v] == T1); e2 += (seg[v] == T2); }
+  // both counts in one scan (each block total is at most kSelChunk < 2^16)
+  int tot;
+  const int eb12 = block_excl_scan<kSelThreads>(e1 | (e2 << 16), s_tmp, tot);
+  const int eb1 = base_e1 + (eb12 & 0xffff), eb2 = base_e2 + (eb12 >> 16);
+  auto classify = [&](uint32_t u, int& r1, int& r2, bool& top, bool& sel2) {
+    top = on1 && (u > T1 || (u == T1 && r1 < need1));
+    sel2 = on2 && (u > T2 || (u == T2 && r2 < need2));
+    r1 += (u == T1);
+    r2 += (u == T2);
+  };
+  int c_top = 0, c_seed = 0;
+  {
+    int r1 = eb1, r2 = eb2;
+#pragma unroll
+    for (int v = 0; v < kSelPer; ++v) {
+      if (v < per && lo + v < n) {
+        bool top, sel2;
+        classify(seg[v], r1, r2, top, sel2);
+        c_top += top;
+        c_seed += (sel2 && !top);
+      }
+    }
+  }
+  // block-local run offsets: top-scored from the front of s_run, evicted
+  // after them (the two partition the chunk), seeds in their own buffer
+  // (the evicted count of the threads before this one is their positions
+  // minus their top-scored ones: every earlier thread holds per)
+  int nts;
+  const int ots = block_excl_scan<kSelThreads>(c_top | (c_seed << 16), s_tmp, nts);
+  const int n_top = nts & 0xffff, n_seed = nts >> 16;
+  const int n_valid = min(kSelChunk, n - i0);
+  const int n_ev = n_valid - n_top;
+  int ob_top = ots & 0xffff;
+  int ob_seed = ots >> 16;
+  int ob_ev = n_top + min(tid * per, n_valid) - ob_top;
+  __shared__ uint16_t s_run[kSelChunk];  // positions within the block's chunk
+  __shared__ uint16_t s_seed[kSelChunk];
+  int r1 = eb1, r2 = eb2;
+#pragma unroll
+  for (int v = 0; v < kSelPer; ++v) {
+    if (v < per && lo + v < n) {
+      bool top, sel2;
+      classify(seg[v], r1, r2, top, sel2);
+      const uint16_t at = (uint16_t)(tid * per + v);
+      if (top) s_run[ob_top++] = at;
+      else s_run[ob_ev++] = at;
+      if (sel2 && !top) s_seed[ob_seed++] = at;
+    }
+  }
+  __syncthreads();
+  int32_t* elist = a.elist + (size_t)bh * a.S;
+  int32_t* seeds = a.seeds + (size_t)bh * a.Rcap;
+  for (int i = tid; i < n_top + n_ev; i += kSelThreads) {
+    if (i < n_top) main_idx[base_top + i] = i0 + s_run[i];
+    else elist[base_ev + i - n_top] = i0 + s_run[i];
+  }
+  for (int i = tid; i < n_seed; i += kSelThreads) seeds[base_seed + i] = i0 + s_seed[i];
+}
+
+__global__ __launch_bounds__(kSelThreads) void select_write(BuildArgs a) {
+  const int bh = blockIdx.z * a.Hkv + blockIdx.y;
+  const HeadMeta hm = a.meta[bh];
+  const int tid = threadIdx.x, blk = blockIdx.x;
+  sel_fixed(a, hm, bh, blk);
+  if (hm.all_main) return;
+  if (blk * kSelChunk >= hm.n_sc) return;  // block-uniform
   __shared__ unsigned long long s_cnt[2][kSelThreads / 64];
   const int n = hm.n_sc, i0 = blk * kSelChunk;
   const uint32_t* key = reinterpret_cast<const uint32_t*>(a.score + (size_t)bh * a.S);
@@ -687,12 +782,10 @@ __global__ __launch_bounds__(kSelThreads) void select_write(BuildArgs a) {
   // Thresholds T_q = the final prefixes; krem[q] = how many scores equal to
   // T_q are taken (lowest positions first); a threshold with k = 0 takes none.
   SelState st = sel_load(a, bh, 1);
-  sel_digit(a, bh, 2, st);  // synchronises the block
+  sel_digit(a.sel_hist + (size_t)bh * kSelHist, 2, st);  // synchronises the block
   const uint32_t T1 = st.pref[0], T2 = st.pref[1];
-  const int need1 = st.krem[0], need2 = st.krem[1];
-  const bool on1 = hm.k_top > 0, on2 = hm.k_top + hm.r_eff > 0;
   // scores before this block (full chunks) above and equal to each threshold
-  int base_e1 = 0, base_e2 = 0, base_top = 0, base_seed = 0;
+  SelBase base{0, 0, 0, 0};
   if (blk > 0) {  // block-uniform
     unsigned long long c1 = 0, c2 = 0;  // above in the low half, equal in the high half
     int g1 = 0, q1 = 0, g2 = 0, q2 = 0;
@@ -720,75 +813,69 @@ __global__ __launch_bounds__(kSelThreads) void select_write(BuildArgs a) {
     c1 = c2 = 0;
 #pragma unroll
     for (int w = 0; w < kSelThreads / 64; ++w) { c1 += s_cnt[0][w]; c2 += s_cnt[1][w]; }
-    base_e1 = (int)(c1 >> 32);
-    base_e2 = (int)(c2 >> 32);
+    base.e1 = (int)(c1 >> 32);
+    base.e2 = (int)(c2 >> 32);
     // top scores taken, and those of ranks k1 .. k2 - 1 (the top ones are among the first k2)
-    base_top = on1 ? (int)(c1 & 0xffffffffu) + min(need1, base_e1) : 0;
-    base_seed = (on2 ? (int)(c2 & 0xffffffffu) + min(need2, base_e2) : 0) - base_top;
+    base.top = hm.k_top > 0 ? (int)(c1 & 0xffffffffu) + min(st.krem[0], base.e1) : 0;
+    base.seed = (hm.k_top + hm.r_eff > 0 ? (int)(c2 & 0xffffffffu) + min(st.krem[1], base.e2) : 0) - base.top;
   }
-  const int base_ev = blk * kSelChunk - base_top;
-  // equal-to-threshold counts per thread, scanned: the tie ranks
-  int e1 = 0, e2 = 0;
+  sel_place(a, hm, bh, blk, seg, kSelPer, st, base);
+}
+
+// Pooling and the whole selection of a head with at most kSelChunk scores in
+// one block: the scores stay in registers, the passes' histograms in LDS. Such
+// lists are bound by launches (2 heads of 1008 scores: 24 us in the four
+// launches of the general path, 13 us here; a
+// construction of 8 or 256 heads of 8100 tokens 6 or 14 us less).
+__global__ __launch_bounds__(kSelThreads) void select_one(BuildArgs a) {
+  const int bh = blockIdx.z * a.Hkv + blockIdx.y;
+  const HeadMeta hm = a.meta[bh];
+  const int tid = threadIdx.x, lane = tid & 63, n = hm.all_main ? 0 : hm.n_sc;
+  const int per = (n + kSelThreads - 1) / kSelThreads, lo = tid * per;  // short lists spread over all waves
+  sel_fixed(a, hm, bh, 0);
+  if (a.dbg_scores)
+    for (int p = n + tid; p < a.S; p += kSelThreads) a.dbg_scores[(size_t)bh * a.S + p] = -1.f;
+  if (hm.all_main) return;
+  __shared__ int s_hist[kSelHist];
+  float v[kSelPer];
+  const float* raw = a.raw + (size_t)source_head(a, bh) * a.S;
+  if (per == 1) {
+    float v1[1];
+    pool_run(a, raw, lo, n, v1);
+    v[0] = v1[0];
 #pragma unroll
-  for (int v = 0; v < kSelPer; ++v)
-    if (lo + v < n) { e1 += (seg[v] == T1); e2 += (seg[v] == T2); }
-  // both counts in one scan (each block total is at most kSelChunk < 2^16)
-  int tot;
-  const int eb12 = block_excl_scan<kSelThreads>(e1 | (e2 << 16), s_tmp, tot);
-  const int eb1 = base_e1 + (eb12 & 0xffff), eb2 = base_e2 + (eb12 >> 16);
-  auto classify = [&](uint32_t u, int& r1, int& r2, bool& top, bool& sel2) {
-    top = on1 && (u > T1 || (u == T1 && r1 < need1));
-    sel2 = on2 && (u > T2 || (u == T2 && r2 < need2));
-    r1 += (u == T1);
-    r2 += (u == T2);
-  };
-  int c_top = 0, c_seed = 0;
-  {
-    int r1 = eb1, r2 = eb2;
+    for (int i = 1; i < kSelPer; ++i) v[i] = 0.f;
+  } else {
+    pool_run(a, raw, lo, n, v);
+  }
+  uint32_t seg[kSelPer];
 #pragma unroll
-    for (int v = 0; v < kSelPer; ++v) {
-      if (lo + v < n) {
-        bool top, sel2;
-        classify(seg[v], r1, r2, top, sel2);
-        c_top += top;
-        c_seed += (sel2 && !top);
-      }
+  for (int i = 0; i < kSelPer; ++i) {
+    seg[i] = __float_as_uint(v[i]);
+    if (a.dbg_scores && i < per && lo + i < n) a.dbg_scores[(size_t)bh * a.S + lo + i] = v[i];
+  }
+  for (int i = tid; i < kSelHist; i += kSelThreads) s_hist[i] = 0;
+  __syncthreads();  // the histograms are cleared
+  SelState st{{0u, 0u}, {hm.k_top, hm.k_top + hm.r_eff}};
+#pragma unroll
+  for (int pass = 0; pass < 3; ++pass) {
+    const int shift = sel_shift(pass), bins = sel_bins(pass);
+    const uint32_t mask = pass == 0 ? 0u : ~0u << sel_shift(pass > 0 ? pass - 1 : 0);
+    const bool shared = pass == 0 || (st.krem[0] > 0 && st.krem[1] > 0 && st.pref[0] == st.pref[1]);
+#pragma unroll
+    for (int i = 0; i < kSelPer; ++i) {
+      if (i >= per) break;  // block-uniform
+      const bool in = lo + i < n;
+      const int dig = (seg[i] >> shift) & (bins - 1);
+      wave_hist_add(s_hist + sel_at(pass, 0), dig, in && (pass == 0 || (st.krem[0] > 0 && (seg[i] & mask) == st.pref[0])),
+                    lane);
+      if (!shared) wave_hist_add(s_hist + sel_at(pass, 1), dig, in && st.krem[1] > 0 && (seg[i] & mask) == st.pref[1], lane);
     }
+    __syncthreads();
+    sel_digit(s_hist, pass, st);
+    __syncthreads();  // the digit scratch is free again
   }
-  // block-local run offsets: top-scored from the front of s_run, evicted
-  // after them (the two partition the chunk), seeds in their own buffer
-  // (the evicted count of the threads before this one is their positions
-  // minus their top-scored ones: every earlier thread holds kSelPer)
-  int nts;
-  const int ots = block_excl_scan<kSelThreads>(c_top | (c_seed << 16), s_tmp, nts);
-  const int n_top = nts & 0xffff, n_seed = nts >> 16;
-  const int n_valid = min(kSelChunk, n - i0);
-  const int n_ev = n_valid - n_top;
-  int ob_top = ots & 0xffff;
-  int ob_seed = ots >> 16;
-  int ob_ev = n_top + min(tid * kSelPer, n_valid) - ob_top;
-  __shared__ uint16_t s_run[kSelChunk];  // positions within the block's chunk
-  __shared__ uint16_t s_seed[kSelChunk];
-  int r1 = eb1, r2 = eb2;
-#pragma unroll
-  for (int v = 0; v < kSelPer; ++v) {
-    if (lo + v < n) {
-      bool top, sel2;
-      classify(seg[v], r1, r2, top, sel2);
-      const uint16_t at = (uint16_t)(tid * kSelPer + v);
-      if (top) s_run[ob_top++] = at;
-      else s_run[ob_ev++] = at;
-      if (sel2 && !top) s_seed[ob_seed++] = at;
-    }
-  }
-  __syncthreads();
-  int32_t* elist = a.elist + (size_t)bh * a.S;
-  int32_t* seeds = a.seeds + (size_t)bh * a.Rcap;
-  for (int i = tid; i < n_top + n_ev; i += kSelThreads) {
-    if (i < n_top) main_idx[base_top + i] = i0 + s_run[i];
-    else elist[base_ev + i - n_top] = i0 + s_run[i];
-  }
-  for (int i = tid; i < n_seed; i += kSelThreads) seeds[base_seed + i] = i0 + s_seed[i];
+  sel_place(a, hm, bh, 0, seg, per, st, SelBase{0, 0, 0, 0});
 }
 
 // ------------------------------------- AdaKV cross-head budget allocation
@@ -1838,17 +1925,21 @@ hipError_t launch_candidate_typed(const BuildPlan& pl, const BuildArgs& a, hipSt
     RESKV_CHECK();
   }
   constexpr int kPoolChunk = kPoolThreads * kPoolPer;
-  hipLaunchKernelGGL(pool_scores, grid((pl.S + kPoolChunk - 1) / kPoolChunk), dim3(kPoolThreads), 0, st, a);
-  RESKV_CHECK();
-  if (alloc_meta) {
-    hipLaunchKernelGGL(adakv_hist<1>, grid(pl.NSEL), dim3(kSelThreads), 0, st, a, safeguard); RESKV_CHECK();
-    hipLaunchKernelGGL(adakv_hist<2>, grid(pl.NSEL), dim3(kSelThreads), 0, st, a, safeguard); RESKV_CHECK();
-    hipLaunchKernelGGL(adakv_alloc, dim3(pl.B), dim3(kSelThreads), 0, st, a, alloc_meta, safeguard);
+  if (pl.NSEL == 1 && !alloc_meta) {
+    hipLaunchKernelGGL(select_one, bhg, dim3(kSelThreads), 0, st, a); RESKV_CHECK();
+  } else {
+    hipLaunchKernelGGL(pool_scores, grid((pl.S + kPoolChunk - 1) / kPoolChunk), dim3(kPoolThreads), 0, st, a);
     RESKV_CHECK();
+    if (alloc_meta) {
+      hipLaunchKernelGGL(adakv_hist<1>, grid(pl.NSEL), dim3(kSelThreads), 0, st, a, safeguard); RESKV_CHECK();
+      hipLaunchKernelGGL(adakv_hist<2>, grid(pl.NSEL), dim3(kSelThreads), 0, st, a, safeguard); RESKV_CHECK();
+      hipLaunchKernelGGL(adakv_alloc, dim3(pl.B), dim3(kSelThreads), 0, st, a, alloc_meta, safeguard);
+      RESKV_CHECK();
+    }
+    hipLaunchKernelGGL(select_hist<1>, grid(pl.NSEL), dim3(kSelThreads), 0, st, a); RESKV_CHECK();
+    hipLaunchKernelGGL(select_hist<2>, grid(pl.NSEL), dim3(kSelThreads), 0, st, a); RESKV_CHECK();
+    hipLaunchKernelGGL(select_write, grid(pl.NSEL), dim3(kSelThreads), 0, st, a); RESKV_CHECK();
   }
-  hipLaunchKernelGGL(select_hist<1>, grid(pl.NSEL), dim3(kSelThreads), 0, st, a); RESKV_CHECK();
-  hipLaunchKernelGGL(select_hist<2>, grid(pl.NSEL), dim3(kSelThreads), 0, st, a); RESKV_CHECK();
-  hipLaunchKernelGGL(select_write, grid(pl.NSEL), dim3(kSelThreads), 0, st, a); RESKV_CHECK();
   const int rows = pl.max_main + pl.Rcap;
   const int gblocks = (rows * (D * (int)sizeof(T) / 16) + kThreads - 1) / kThreads;
   hipLaunchKernelGGL((gather_init<T, D>), grid(gblocks < 64 ? gblocks : 64), dim3(kThreads), 0, st, a);

@@ -73,6 +73,9 @@ def test_scoring_row_chunks(dtype, d, G, window, s):
     (16385 + 8, 9000, (9, 800), 8),   # thresholds that cross the blocks
     (3 * 8192 - 5, 64, (63, 1), 70),  # all main slots protected: nothing selected, seeds only
     (5001, 5000, (1, 300), 4),        # nearly every score kept; unaligned rows of scores
+    (8192, 700, (30, 699), 8),        # the longest list of the one-block selection
+    (1024 + 8, 100, (20, 99), 8),     # one score per thread there, and two
+    (1025 + 8, 100, (20, 0), 8),
 ])
 def test_selection_blocks(s, budget, res, recent):
     """Score lists at the edges of the selection's 8192-score blocks, with the
