@@ -313,8 +313,8 @@ size_t reskv_build_proxy_workspace_size(const reskv_shape_t* shape,
  * lengths cannot make the kernels read outside the cache.
  *
  * Performance: the slot capacity C sets the head stride of kc and vc
- * (C * d * element bytes). With one block per (b, kv head) (from 256 pairs
- * on) every head is streamed at once, and a few strides put many heads on
+ * (C * d * element bytes). With one block per (b, kv head) (always from 256
+ * pairs on) every head is streamed at once, and a few strides put many heads on
  * the same HBM channels: at 256 heads of 2048 live slots, d = 128, bf16, a
  * call took 48-51 us at most capacities between 2056 and 2552 slots and up
  * to 57 us at the worst one measured (2064). The kernels accept any C; a
