@@ -339,6 +339,16 @@ def progress(msg):
     print(f"bench: {msg}", file=sys.stderr, flush=True)
 
 
+def decode_label(rk, shape, entry="attn"):
+    """Entry point and kernels of one layer-step's decode call, as the library chooses them for these sizes."""
+    name = {"attn": "reskv_decode_attn", "ragged": "reskv_decode_attn_ragged"}[entry]
+    kernels = rk.decode_kernels(shape, entry)
+    what = {"decode_head": "one block per (sequence, KV head)",
+            "decode_split + decode_combine": "256-slot blocks, then the merge with the gate",
+            "decode_ragged + decode_ragged_combine": "equal ranges of 64-slot units, then the merge"}[kernels]
+    return f"{name} ({kernels}: {what}; append fused)"
+
+
 def per_config_run(rk, torch, np, synth, idx, dev, reps, ragged):
     """Construction and decode of another workload, after the main job's
     buffers are freed. Every layer is generated into one reused prefill
@@ -441,9 +451,9 @@ def per_config_run(rk, torch, np, synth, idx, dev, reps, ragged):
         del g
         return e0.elapsed_time(e1)
 
-    # the per-head schedule (reskv_decode_attn), then for ragged batches the
-    # balanced-range one (reskv_decode_attn_ragged) beside it, each from the
-    # built lengths
+    # reskv_decode_attn, then for ragged batches reskv_decode_attn_ragged
+    # beside it, each from the built lengths (the line names the kernels that
+    # each takes at these sizes)
     dec_ms = timed_decode(False)
     rag_ms = timed_decode(True) if ragged else None
     progress(f"{wl.name}: decode phase timed")
@@ -477,10 +487,9 @@ def per_config_run(rk, torch, np, synth, idx, dev, reps, ragged):
         decode_tokens_per_s=B * L * wl.steps / (dec_ms * 1e-3),
         decode_roofline={"bound": "hbm", "achieved": dec_gbs, "peak": HBM_PEAK_GBS, "unit": "GB/s",
                          "frac": dec_gbs / HBM_PEAK_GBS, "calls_timed": calls,
-                         "kernel": ("reskv_decode_attn (decode_head: one block per (sequence, KV head), append "
-                                    "fused)" if B * Hkv >= 256 else "reskv_decode_attn (decode_split + "
-                                    "decode_combine, append fused)")},
-        decode_us_per_call_ragged_schedule=(rag_ms * 1e3 / calls if rag_ms is not None else None),
+                         "kernel": decode_label(rk, shape)},
+        decode_ragged_entry=({"us_per_call": rag_ms * 1e3 / calls, "kernel": decode_label(rk, shape, "ragged")}
+                             if rag_ms is not None else None),
         decode_launch="hip_graph")
 
 
@@ -729,10 +738,7 @@ def main():
         "construction_mfma": cmfma,
         "roofline": {"bound": "hbm", "achieved": achieved, "peak": HBM_PEAK_GBS, "unit": "GB/s",
                      "frac": achieved / HBM_PEAK_GBS, "traffic": traffic,
-                     "kernel": ("reskv_decode_attn (one launch per layer-step: decode_head, one block per "
-                                "(sequence, KV head), append fused)" if B * Hkv >= 256 and (elem == 2 or d == 64) else
-                                "reskv_decode_attn (per layer-step: decode_split over 256-slot blocks with the "
-                                "append fused, decode_combine with the gate)"),
+                     "kernel": decode_label(rk, shape),
                      "bytes_per_call": avg_bytes, "us_per_call": avg_ms * 1e3,
                      "us_per_call_range": [min(dec_job_ms) / calls * 1e3, max(dec_job_ms) / calls * 1e3],
                      "calls_timed": calls * args.steps},
@@ -763,7 +769,7 @@ def main():
         dsrc = source_hash("paper_2607_29591_amd/csrc/decode.hip", "paper_2607_29591_amd/csrc/common.h")
         for idx in others:
             # the ragged GQA-7 batch (budgets and contexts differ per sequence)
-            # also decodes with the balanced-range schedule, reported beside
+            # also decodes through reskv_decode_attn_ragged, reported beside
             wl_i, rec = per_config_run(rk, torch, np, synth, idx, dev, args.per_config_reps, ragged=idx == 4)
             names = PROFILES.get(idx, {})
             if "construction" in names:

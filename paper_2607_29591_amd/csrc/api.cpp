@@ -203,6 +203,18 @@ reskv_status_t reskv_decode_branches(const reskv_shape_t* shape, const reskv_gat
   return ok();
 }
 
+int reskv_internal_decode_kernels(const reskv_shape_t* shape, int entry) {
+  if (entry < 0 || entry > 2 || check_shape(shape) != RESKV_OK) return -1;
+  if (entry == 2) {
+    RaggedPlan rp;
+    if (!make_ragged_plan(*shape, &rp)) return -1;
+    if (!ragged_takes_decode(*shape)) return kEqualRanges;
+  }
+  const DecodePlan plan = make_decode_plan(*shape);
+  if ((size_t)plan.GP * plan.P * sizeof(float) > decode_max_lds_weights()) return -1;
+  return plan.whole_head ? kOneBlockPerHead : kSplitCombine;
+}
+
 reskv_status_t reskv_merge_branches(const reskv_shape_t* shape, int32_t mode, const float* out_main,
                                     const float* lse_main, const float* out_res, const float* lse_res,
                                     const float* gate, float* out, void* stream) {

@@ -65,6 +65,13 @@ hipError_t launch_merge_branches(const reskv_shape_t& s, int mode, const float* 
 hipError_t launch_append(const reskv_shape_t& s, const void* k_new, const void* v_new, void* kc,
                          void* vc, const int32_t* res_len, int32_t* main_len, hipStream_t stream);
 
+// Which kernels a decode call of these sizes takes, for the tests and the
+// benchmark's labels (not part of the C ABI): entry 0 reskv_decode_attn, 1
+// reskv_decode_branches, 2 reskv_decode_attn_ragged with the workspace its
+// size query names; -1 where the call is refused.
+enum { kOneBlockPerHead = 0, kSplitCombine = 1, kEqualRanges = 2 };
+extern "C" int reskv_internal_decode_kernels(const reskv_shape_t* shape, int entry);
+
 // Construction.
 // Sizes of one (b, kv head), fixed on the host from seq_len, budget and r.
 struct HeadMeta {

@@ -218,6 +218,15 @@ def reskv_decode_workspace_size(shape):
     return lib().reskv_decode_workspace_size(ctypes.byref(shape))
 
 
+def decode_kernels(shape, entry="attn"):
+    """Names of the kernels a decode call of these sizes takes; None where it is refused.
+    entry: "attn", "branches", or "ragged" (with the workspace its size query names)."""
+    fn = lib().reskv_internal_decode_kernels
+    fn.restype, fn.argtypes = ctypes.c_int, [ctypes.POINTER(Shape), ctypes.c_int]
+    return {0: "decode_head", 1: "decode_split + decode_combine", 2: "decode_ragged + decode_ragged_combine"}.get(
+        fn(ctypes.byref(shape), ("attn", "branches", "ragged").index(entry)))
+
+
 def reskv_decode_attn(shape, gate, q, kc, vc, logc, res_len, main_len, out, workspace,
                       dbg_lse_main=None, dbg_lse_res=None, dbg_gate=None, k_new=None, v_new=None, stream=None):
     _check(lib().reskv_decode_attn(ctypes.byref(shape), ctypes.byref(gate), _ptr(q), _ptr(kc), _ptr(vc),

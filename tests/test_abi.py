@@ -56,6 +56,20 @@ def test_decode_workspace_size(L):
     assert rk.reskv_decode_workspace_size(shape(num_q_heads=7)) == 0
 
 
+@pytest.mark.parametrize("kw,entry,kernels", [
+    (dict(batch=32, num_kv_heads=8, num_q_heads=32, slot_cap=2304), "attn", "decode_head"),
+    (dict(batch=8, num_kv_heads=8, num_q_heads=32, slot_cap=1024), "attn", "decode_head"),  # 64 pairs
+    (dict(batch=1, num_kv_heads=8, num_q_heads=32, slot_cap=640), "attn", "decode_head"),   # one round of slots
+    (dict(batch=4, num_kv_heads=8, num_q_heads=32, slot_cap=1088), "attn", "decode_split + decode_combine"),
+    (dict(batch=64, num_kv_heads=4, num_q_heads=28, slot_cap=1152), "ragged", "decode_head"),
+    (dict(batch=96, num_kv_heads=4, num_q_heads=28, slot_cap=2304), "ragged",
+     "decode_ragged + decode_ragged_combine")])
+def test_bench_labels_name_the_kernels_that_run(L, kw, entry, kernels):
+    import bench
+    assert rk.decode_kernels(shape(**kw), entry) == kernels
+    assert kernels in bench.decode_label(rk, shape(**kw), entry)
+
+
 class FakeTensor:
     """Stands in for a device tensor: a non-null pointer that is never
     dereferenced because validation fails first."""
