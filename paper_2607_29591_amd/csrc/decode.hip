@@ -1236,6 +1236,39 @@ hipError_t launch_planned(const DecodePlan& pl, bool bf, const DecodeArgs& da, h
 
 }  // namespace
 
+// One block per (b, kv head) or split-K blocks and a merge launch, below the
+// 256 pairs that fill the CUs. A block streams 512 slots a round (8 waves of
+// 64), about 4 us each while the pairs leave CUs idle, and saves the merge's
+// 5 us; heads of one length gain from it, one long head among short ones
+// waits its rounds out. Measured at d = 128, bf16, 4 query heads per KV head,
+// us split / one block, every head full and then one full head among eighths:
+//   pairs     C = 512      640        1024       1536       2048       2560
+//     8     11.3/ 9.7  11.7/10.9  12.1/14.4  12.2/19.6  12.7/24.5  13.0/29.4 full
+//           10.5/ 9.1  10.5/ 9.8  10.8/13.9  11.2/18.9  11.8/23.5  12.1/28.3 one
+//    64     12.1/10.0  12.9/11.7  16.0/15.5  19.0/23.4  25.4/29.6  26.8/35.5 full
+//           10.9/ 9.7  11.6/10.3  12.2/14.2  14.0/18.3  15.2/23.3  15.3/28.9 one
+//   128     15.8/10.6  17.8/14.2  24.4/18.2  29.7/27.0  35.8/33.8  41.0/41.0 full
+//           11.5/ 9.6  13.0/10.5  13.5/14.2  20.4/19.0  16.4/23.9  16.5/29.0 one
+//   240     23.9/14.4  27.3/17.5  34.5/25.4  47.3/36.9  57.9/46.8  66.4/56.5 full
+//           12.5/11.2  16.4/11.8  14.3/16.2  27.6/21.7  23.9/25.9  22.2/30.3 one
+// The lines lie where full heads, and lengths uniform in [C/4, C], stop being
+// slower (half-full heads gain more: 128 x 2048 26.4 / 18.5). Within them a
+// batch with few long heads loses (up to 1.6 times, see the lower rows). Past
+// 2304 slots groups of up to 4 query heads split: one block gains at most 20%
+// on full heads there and loses up to 1.9 times on uneven ones. For at most
+// one round one block serves any count, bf16 up to 640 slots, where only two
+// waves have a second unit.
+static bool one_block_per_head(const reskv_shape_t& s, int GP, long long pairs) {
+  const bool bf = s.dtype == RESKV_BF16;
+  const int round = kHeadWaves * kUnit, rounds = (s.slot_cap + round - 1) / round;
+  if (s.slot_cap <= (bf ? round + 2 * kUnit : round)) return true;
+  if (bf && GP <= 4 && s.slot_cap > 2304) return false;
+  // 32 pairs per round, and more where small groups or fp32 rows leave full
+  // heads slower (96 pairs of 1280 slots, one query head: 15.9 / 18.9)
+  const int more = rounds == 2 ? (bf ? 0 : 16) : GP > 4 ? 0 : rounds == 3 ? 24 : rounds == 4 ? 16 : 0;
+  return pairs >= 32LL * rounds + more;
+}
+
 DecodePlan make_decode_plan(const reskv_shape_t& s) {
   DecodePlan p{};
   p.B = s.batch; p.Hq = s.num_q_heads; p.Hkv = s.num_kv_heads;
@@ -1245,26 +1278,9 @@ DecodePlan make_decode_plan(const reskv_shape_t& s) {
   const int rmax = s.res_cap < s.slot_cap ? s.res_cap : s.slot_cap;
   p.PR = (rmax + kChunk - 1) / kChunk;
   p.P = p.PR + (s.slot_cap + kChunk - 1) / kChunk;
-  // One block per (b, kv head) or split-K blocks and a merge launch: a block
-  // streams 512 slots a round (8 waves of 64), about 4 us each while the pairs
-  // leave CUs idle, and saves the merge's 5 us. Measured at d = 128, bf16, 4
-  // query heads per KV head, us split / one block:
-  //   pairs     C = 320    512       640       1024      1536      2048
-  //     1     9.6/ 8.5  9.7/ 8.8 10.0/10.0 10.1/12.8 10.5/18.1 10.5/22.6
-  //    32    11.5/ 9.3 11.5/ 9.6 11.6/11.5 11.8/14.1 12.4/18.9 15.5/24.0
-  //    64    11.7/ 9.4 11.7/ 9.7 12.2/11.6 15.4/14.6 18.5/22.0 22.8/28.2
-  //    96    12.5/ 9.5 14.1/ 9.8 14.8/11.7 18.5/18.0 25.4/25.3 27.9/32.1
-  //   128    12.7/ 9.6 14.9/10.4 18.0/14.8 23.7/18.8 28.0/25.4 32.7/32.7
-  // so one block from 32 pairs per round on (two rounds: 64 pairs), always
-  // from 256 pairs on, which fill the CUs, and at any count for one round;
-  // bf16 up to 640 slots, where only two waves have a second unit (fp32 rows
-  // of 64 at 640: 14.8/15.9 at 32 pairs). fp32 rows of 128 always split: the
-  // head kernel would spill.
   const long long pairs = (long long)p.B * p.Hkv;
-  const int round = kHeadWaves * kUnit, rounds = (s.slot_cap + round - 1) / round;
-  const bool fits = s.dtype == RESKV_BF16 || p.D == 64;
-  p.whole_head = fits && (s.slot_cap <= (s.dtype == RESKV_BF16 ? round + 2 * kUnit : round) || pairs >= 256 ||
-                          pairs >= 32LL * rounds);
+  const bool fits = s.dtype == RESKV_BF16 || p.D == 64;  // fp32 rows of 128: the head kernel would spill
+  p.whole_head = fits && (pairs >= 256 || one_block_per_head(s, p.GP, pairs));
   p.no_records = fits && pairs >= 256;
   const size_t recs = (size_t)p.B * p.Hkv * p.P * p.GP;
   p.acc_off = 0;

@@ -1,0 +1,42 @@
+"""Which kernels a call takes, on the CPU: both sides of every line of the
+launch rules, as the library answers them (no kernel runs here; the results on
+both sides are compared with the oracle in the GPU tests)."""
+
+import os
+
+import pytest
+
+from paper_2607_29591_amd import reskv as rk
+
+HEAD, SPLIT, RANGES = "decode_head", "decode_split + decode_combine", "decode_ragged + decode_ragged_combine"
+
+
+@pytest.fixture(scope="module", autouse=True)
+def built():
+    if not os.path.exists(rk.LIB_PATH):
+        from paper_2607_29591_amd import build_lib
+        build_lib.build()
+
+
+def kernels(entry, dtype, d, G, pairs, C, Rcap=64):
+    return rk.decode_kernels(rk.make_shape(pairs, G, 1, d, dtype, C, Rcap), entry)
+
+
+@pytest.mark.parametrize("dtype,d,G,pairs,C,want", [
+    # one round of slots: any count
+    ("bf16", 128, 4, 1, 640, HEAD), ("bf16", 128, 4, 1, 641, SPLIT),
+    ("f32", 64, 4, 1, 512, HEAD), ("f32", 64, 4, 1, 513, SPLIT),
+    # two rounds: fp32 rows need more pairs (64 x 768: 15.8 us split, 18.8 in one block)
+    ("bf16", 128, 4, 63, 1024, SPLIT), ("bf16", 128, 4, 64, 1024, HEAD),
+    ("f32", 64, 4, 79, 768, SPLIT), ("f32", 64, 4, 80, 768, HEAD),
+    # three and four rounds: small groups need more pairs (96 x 1280, one query head: 15.9 and 18.9)
+    ("bf16", 128, 1, 119, 1280, SPLIT), ("bf16", 128, 1, 120, 1280, HEAD), ("bf16", 128, 8, 96, 1280, HEAD),
+    ("bf16", 128, 4, 143, 2048, SPLIT), ("bf16", 128, 4, 144, 2048, HEAD), ("bf16", 128, 16, 128, 2048, HEAD),
+    ("bf16", 128, 4, 160, 2304, HEAD), ("bf16", 128, 4, 159, 2304, SPLIT),
+    # long caches of small groups below 256 pairs (192 x 2560 with one long head: 18.4 and 29.0)
+    ("bf16", 128, 4, 255, 2305, SPLIT), ("bf16", 128, 4, 256, 2305, HEAD), ("bf16", 128, 8, 160, 2560, HEAD),
+    # fp32 rows of 128 always split
+    ("f32", 128, 4, 256, 300, SPLIT),
+])
+def test_decode_one_block_per_head(dtype, d, G, pairs, C, want):
+    assert kernels("attn", dtype, d, G, pairs, C) == want
