@@ -191,7 +191,7 @@ reskv_status_t reskv_decode_branches(const reskv_shape_t* shape, const reskv_gat
   if (!q || !kc || !vc || !logc || !res_len || !main_len || !out_main || !lse_main || !out_res || !lse_res ||
       !gate_out)
     return fail(RESKV_ERR_INVALID_ARG, "a required pointer is NULL");
-  const DecodePlan plan = make_decode_plan(*shape);
+  const DecodePlan plan = make_decode_plan(*shape, true);
   if ((size_t)plan.GP * plan.P * sizeof(float) > decode_max_lds_weights())
     return fail(RESKV_ERR_UNSUPPORTED, "%d split-K records per head do not fit the combine", plan.P);
   if (!workspace || workspace_bytes < plan.bytes)
@@ -210,7 +210,7 @@ int reskv_internal_decode_kernels(const reskv_shape_t* shape, int entry) {
     if (!make_ragged_plan(*shape, &rp)) return -1;
     if (!ragged_takes_decode(*shape)) return kEqualRanges;
   }
-  const DecodePlan plan = make_decode_plan(*shape);
+  const DecodePlan plan = make_decode_plan(*shape, entry == 1);
   if ((size_t)plan.GP * plan.P * sizeof(float) > decode_max_lds_weights()) return -1;
   return plan.whole_head ? kOneBlockPerHead : kSplitCombine;
 }

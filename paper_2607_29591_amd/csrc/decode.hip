@@ -1236,6 +1236,12 @@ hipError_t launch_planned(const DecodePlan& pl, bool bf, const DecodeArgs& da, h
 
 }  // namespace
 
+// Caches on which one block per head gains little and can lose much (both
+// rules below).
+static bool long_small_group(const reskv_shape_t& s, int GP) {
+  return s.dtype == RESKV_BF16 && GP <= 4 && s.slot_cap > 2304;
+}
+
 // One block per (b, kv head) or split-K blocks and a merge launch, below the
 // 256 pairs that fill the CUs. A block streams 512 slots a round (8 waves of
 // 64), about 4 us each while the pairs leave CUs idle, and saves the merge's
@@ -1262,14 +1268,14 @@ static bool one_block_per_head(const reskv_shape_t& s, int GP, long long pairs) 
   const bool bf = s.dtype == RESKV_BF16;
   const int round = kHeadWaves * kUnit, rounds = (s.slot_cap + round - 1) / round;
   if (s.slot_cap <= (bf ? round + 2 * kUnit : round)) return true;
-  if (bf && GP <= 4 && s.slot_cap > 2304) return false;
+  if (long_small_group(s, GP)) return false;
   // 32 pairs per round, and more where small groups or fp32 rows leave full
   // heads slower (96 pairs of 1280 slots, one query head: 15.9 / 18.9)
   const int more = rounds == 2 ? (bf ? 0 : 16) : GP > 4 ? 0 : rounds == 3 ? 24 : rounds == 4 ? 16 : 0;
   return pairs >= 32LL * rounds + more;
 }
 
-DecodePlan make_decode_plan(const reskv_shape_t& s) {
+DecodePlan make_decode_plan(const reskv_shape_t& s, bool branches) {
   DecodePlan p{};
   p.B = s.batch; p.Hq = s.num_q_heads; p.Hkv = s.num_kv_heads;
   p.G = s.num_q_heads / s.num_kv_heads;
@@ -1280,7 +1286,12 @@ DecodePlan make_decode_plan(const reskv_shape_t& s) {
   p.P = p.PR + (s.slot_cap + kChunk - 1) / kChunk;
   const long long pairs = (long long)p.B * p.Hkv;
   const bool fits = s.dtype == RESKV_BF16 || p.D == 64;  // fp32 rows of 128: the head kernel would spill
-  p.whole_head = fits && (pairs >= 256 || one_block_per_head(s, p.GP, pairs));
+  // From 256 pairs on always, but for the two-branch form of long caches and
+  // small groups: there one block gains at most 20% on full heads and waits
+  // for long ones (384 pairs of 3072 slots, every 16th full among eighths,
+  // one query head: 35.0 us split, 77.9 in one block; all full 109.9, 115.7).
+  const bool fills = pairs >= 256 && !(branches && long_small_group(s, p.GP));
+  p.whole_head = fits && (fills || one_block_per_head(s, p.GP, pairs));
   p.no_records = fits && pairs >= 256;
   const size_t recs = (size_t)p.B * p.Hkv * p.P * p.GP;
   p.acc_off = 0;

@@ -27,7 +27,7 @@ size_t decode_max_lds_weights();
 constexpr size_t kStaticScratchBytes = (size_t)16 << 20;
 hipError_t static_scratch(void** ptr);
 
-DecodePlan make_decode_plan(const reskv_shape_t& s);
+DecodePlan make_decode_plan(const reskv_shape_t& s, bool branches = false);
 
 // Ragged schedule: balanced ranges of 64-slot units over the whole batch.
 struct RaggedPlan {

@@ -40,3 +40,12 @@ def kernels(entry, dtype, d, G, pairs, C, Rcap=64):
 ])
 def test_decode_one_block_per_head(dtype, d, G, pairs, C, want):
     assert kernels("attn", dtype, d, G, pairs, C) == want
+
+
+@pytest.mark.parametrize("dtype,G,pairs,C,want", [
+    ("bf16", 4, 64, 1024, HEAD), ("bf16", 4, 255, 2304, HEAD), ("bf16", 4, 512, 2304, HEAD),
+    # long caches of small groups at any count (384 x 3072, few long heads: 35.0 us split, 77.9 in one block)
+    ("bf16", 4, 256, 2305, SPLIT), ("bf16", 1, 512, 3072, SPLIT), ("bf16", 8, 256, 3072, HEAD),
+])
+def test_branches_one_block_per_head(dtype, G, pairs, C, want):
+    assert kernels("branches", dtype, 128, G, pairs, C) == want
