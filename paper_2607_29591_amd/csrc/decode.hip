@@ -1327,24 +1327,32 @@ bool make_ragged_plan(const reskv_shape_t& s, RaggedPlan* plan) {
 }
 
 // Equal unit ranges cost a plan prologue in every block and a merge launch
-// (about 13 us together); per-head kernels cost the wait for the longest head.
-// Measured with lengths uniform in [C/4, C], with one full head among quarter
-// ones and with every 16th full among eighths, us per head / equal ranges at
-// the three:
-//     8 pairs, C = 2304:  14/ 49   13/50   13/49
-//   128 pairs, C = 2304:  29/ 30   19/23   19/22
-//   192 pairs, C = 1536:  25/ 36   23/26   23/30
-//   192 pairs, C = 2304:  36/ 61   31/31   31/30
-//   256 pairs, C = 1152:  23/ 37   20/26   20/25
-//   256 pairs, C = 1536:  30/ 43   25/30   26/28
-//   256 pairs, C = 2304:  42/ 65   34/35   34/32
-//   384 pairs, C = 1152:  34/ 55   21/25   34/23
-// so up to 256 pairs (one block per head runs them all at once) and 256 x 1536
-// slots the per-head kernels, never slower there; beyond, and on caches longer
-// than measured, the equal ranges.
+// (about 13 us together) and more per slot with wide groups; one block per head
+// costs the wait for the longest head, split-K blocks their merge. Measured at
+// d = 128, bf16, us reskv_decode_attn's kernel / equal ranges with lengths uniform
+// in [C/4, C], all half full, and every 16th full among eighths:
+//                        1 query head       4 query heads      8 query heads
+//   256 pairs, C = 1088    22/28 17/25 19/17  22/30 17/27 19/19  24/37 19/33 21/25
+//   160 pairs, C = 1280    19/23 14/21 18/16  21/27 14/23 19/18  22/33 16/29 20/25
+//   160 pairs, C = 2048    29/32 19/28 27/19  30/33 19/29 27/23  32/40 21/35 29/31
+//    96 pairs, C = 1536 s  22/20 21/18 17/17  25/22 23/20 18/21  28/28 26/26 23/30
+//    64 pairs, C = 2112 s  17/20 16/18 14/18  23/22 17/20 16/24  26/29 21/25 19/36
+//   fp32 rows of 64, 192 pairs, C = 2048      40/46 26/42 39/27
+//   fp32 rows of 64,  48 pairs, C = 2112 s    30/27 21/23 19/25
+// (s: split-K blocks). The entry is for uneven heads, so the per-head kernels
+// serve it where they are no slower on the first two kinds and lose less on the
+// third than they gain there: one block per head up to 256 x 1536 slots, with
+// fp32 rows or up to 2 query heads up to 1792 slots a head; split-K blocks with
+// wide groups, short caches or few pairs. bf16 rows of 64 are faster in them
+// throughout.
 bool ragged_takes_decode(const reskv_shape_t& s) {
   const long long pairs = (long long)s.batch * s.num_kv_heads;
-  return pairs <= 256 && s.slot_cap <= 2304 && pairs * s.slot_cap <= 256LL * 1536;
+  if (pairs > 256 || s.slot_cap > 2304 || pairs * s.slot_cap > 256LL * 1536) return false;
+  const bool bf = s.dtype == RESKV_BF16;
+  const DecodePlan dp = make_decode_plan(s);
+  if (bf && (s.head_dim == 64 || dp.GP > 4)) return true;
+  if (dp.whole_head) return s.slot_cap <= (bf && dp.GP > 2 ? 2304 : 1792);
+  return bf ? s.slot_cap <= 1280 || pairs <= 64 : s.slot_cap <= 1024 || pairs <= 32;
 }
 
 hipError_t launch_decode_ragged(const reskv_shape_t& s, const reskv_gate_t& g, const RaggedPlan& pl,

@@ -49,3 +49,20 @@ def test_decode_one_block_per_head(dtype, d, G, pairs, C, want):
 ])
 def test_branches_one_block_per_head(dtype, G, pairs, C, want):
     assert kernels("branches", dtype, 128, G, pairs, C) == want
+
+
+@pytest.mark.parametrize("dtype,d,G,pairs,C,want", [
+    ("bf16", 128, 7, 256, 1152, HEAD), ("bf16", 128, 7, 256, 1536, HEAD), ("bf16", 128, 7, 256, 1537, RANGES),
+    ("bf16", 128, 7, 257, 600, RANGES),
+    # one block per head on longer caches: not with few query heads or fp32 rows
+    ("bf16", 128, 4, 160, 2304, HEAD), ("bf16", 128, 2, 160, 1792, HEAD), ("bf16", 128, 2, 160, 1793, RANGES),
+    ("f32", 64, 4, 192, 1792, HEAD), ("f32", 64, 4, 160, 2048, RANGES),
+    # split-K blocks: short caches or few pairs, any with wide groups
+    ("bf16", 128, 4, 96, 1280, SPLIT), ("bf16", 128, 4, 96, 1281, RANGES), ("bf16", 128, 8, 64, 2304, SPLIT),
+    ("bf16", 128, 4, 64, 2304, SPLIT), ("bf16", 128, 4, 65, 2304, RANGES),
+    ("f32", 64, 4, 48, 1024, SPLIT), ("f32", 64, 4, 48, 1025, RANGES), ("f32", 64, 4, 32, 2304, SPLIT),
+    # bf16 rows of 64 at any
+    ("bf16", 64, 1, 100, 2304, SPLIT), ("bf16", 64, 1, 170, 2304, HEAD), ("bf16", 64, 4, 100, 2305, RANGES),
+])
+def test_ragged_entry(dtype, d, G, pairs, C, want):
+    assert kernels("ragged", dtype, d, G, pairs, C) == want
