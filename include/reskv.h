@@ -357,7 +357,11 @@ size_t reskv_decode_workspace_size(const reskv_shape_t* shape);
  *
  *   workspace       device scratch of reskv_decode_ragged_workspace_size()
  *                   bytes (the per-call plan and the partial records of
- *                   shared heads); calls sharing one must not overlap.
+ *                   shared heads); calls sharing one must not overlap. Where
+ *                   reskv_decode_attn's split kernels serve the call and
+ *                   need more than the equal ranges, a smaller buffer that
+ *                   holds the ranges' records is accepted: the equal ranges
+ *                   then serve it (the same result within rounding).
  * Supported: G <= 8, B*Hkv <= 2048, C <= 64960 slots, bf16 rows (fp32
  * rows of d = 64); otherwise RESKV_ERR_UNSUPPORTED. Errors as for
  * reskv_decode_attn.

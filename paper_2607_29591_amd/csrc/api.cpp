@@ -57,6 +57,9 @@ reskv_status_t check_gate(const reskv_gate_t* g) {
   return RESKV_OK;
 }
 
+// Workspace that a decode call writes: one block per head leaves no records.
+size_t decode_records_bytes(const DecodePlan& plan) { return plan.whole_head ? 0 : plan.bytes; }
+
 }  // namespace
 
 extern "C" {
@@ -141,7 +144,7 @@ size_t reskv_decode_ragged_workspace_size(const reskv_shape_t* shape) {
   if (check_shape(shape) != RESKV_OK) return 0;
   RaggedPlan plan;
   if (!make_ragged_plan(*shape, &plan)) return 0;
-  const size_t other = ragged_takes_decode(*shape) ? make_decode_plan(*shape).bytes : 0;
+  const size_t other = ragged_takes_decode(*shape) ? decode_records_bytes(make_decode_plan(*shape)) : 0;
   return plan.bytes > other ? plan.bytes : other;
 }
 
@@ -167,7 +170,7 @@ reskv_status_t reskv_decode_attn_ragged(const reskv_shape_t* shape, const reskv_
                 workspace ? workspace_bytes : (size_t)0);
   if (ragged_takes_decode(*shape)) {
     const DecodePlan dp = make_decode_plan(*shape);
-    if (workspace_bytes >= dp.bytes) {
+    if (workspace_bytes >= decode_records_bytes(dp)) {  // a smaller one holds the equal ranges' records
       const hipError_t e = launch_decode(*shape, *gate, dp, q, kc, vc, logc, res_len, main_len, k_new, v_new, out,
                                          dbg_lse_main, dbg_lse_res, dbg_gate, workspace, (hipStream_t)stream);
       if (e != hipSuccess) return fail(RESKV_ERR_HIP, "decode launch failed: %s", hipGetErrorString(e));

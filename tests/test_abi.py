@@ -56,6 +56,20 @@ def test_decode_workspace_size(L):
     assert rk.reskv_decode_workspace_size(shape(num_q_heads=7)) == 0
 
 
+def test_ragged_workspace_counts_only_what_is_written(L):
+    """A ragged call served by one block per head writes no split-K records: its workspace is that of the equal
+    ranges, so a buffer sized for them takes it. Split-K records are counted where they are written."""
+    s = shape(batch=64, num_kv_heads=4, num_q_heads=28, slot_cap=1152)
+    past = shape(batch=65, num_kv_heads=4, num_q_heads=28, slot_cap=1152)  # 260 pairs: equal ranges
+    assert rk.decode_kernels(s, "ragged") == "decode_head"
+    assert rk.decode_kernels(past, "ragged") == "decode_ragged + decode_ragged_combine"
+    n, n_past = rk.reskv_decode_ragged_workspace_size(s), rk.reskv_decode_ragged_workspace_size(past)
+    assert n <= n_past < rk.reskv_decode_workspace_size(s)
+    split = shape(batch=16, num_kv_heads=8, num_q_heads=56, slot_cap=2304, res_cap=1000)
+    assert rk.decode_kernels(split, "ragged") == "decode_split + decode_combine"
+    assert rk.reskv_decode_ragged_workspace_size(split) == rk.reskv_decode_workspace_size(split)
+
+
 @pytest.mark.parametrize("kw,entry,kernels", [
     (dict(batch=32, num_kv_heads=8, num_q_heads=32, slot_cap=2304), "attn", "decode_head"),
     (dict(batch=8, num_kv_heads=8, num_q_heads=32, slot_cap=1024), "attn", "decode_head"),  # 64 pairs

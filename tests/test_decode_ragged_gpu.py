@@ -38,12 +38,13 @@ def ragged_case(seed, B, Hkv, G, d, dtype, C, Rcap, res, main, appends):
     return q, kc, vc, logc, tau, kn, vn
 
 
-def run_ragged(dtype, B, Hkv, G, d, C, Rcap, res, main, seed=0, appends=True, compare_head=False):
+def run_ragged(dtype, B, Hkv, G, d, C, Rcap, res, main, seed=0, appends=True, compare_head=False,
+               nws=None):
     res = np.asarray(res, np.int64)
     main = np.asarray(main, np.int64)
     q, kc, vc, logc, tau, kn, vn = ragged_case(seed, B, Hkv, G, d, dtype, C, Rcap, res, main, appends)
     shape = rk.make_shape(B, Hkv * G, Hkv, d, dtype, C, Rcap)
-    nws = rk.reskv_decode_ragged_workspace_size(shape)
+    nws = rk.reskv_decode_ragged_workspace_size(shape) if nws is None else nws
     assert nws > 0
     ws = torch.empty(nws, dtype=torch.uint8, device="cuda")
     dev = dict(q=to_dev(q, dtype), kc=to_dev(kc, dtype), vc=to_dev(vc, dtype),
@@ -175,3 +176,19 @@ def test_ragged_skewed_batch():
     main = rng.integers(200, 300, size=(B, Hkv)) - res
     main[7, 2] = 8000 - res[7, 2]
     run_ragged("bf16", B, Hkv, G, d, C, Rcap, res, main, seed=23, compare_head=True)
+
+
+def test_ragged_small_workspace_takes_equal_ranges():
+    """Split-K records larger than the equal ranges need: a buffer one byte
+    short of the query still holds the ranges' records, and they serve the
+    call."""
+    rng = np.random.default_rng(29)
+    B, Hkv, G, d, C, Rcap = 16, 8, 7, 64, 2304, 1000
+    shape = rk.make_shape(B, Hkv * G, Hkv, d, "bf16", C, Rcap)
+    nws = rk.reskv_decode_ragged_workspace_size(shape)
+    assert rk.decode_kernels(shape, "ragged") == "decode_split + decode_combine"
+    assert nws == rk.reskv_decode_workspace_size(shape)
+    res = rng.choice([0, 16, 64, 200], size=(B, Hkv))
+    main = rng.integers(1, 300, size=(B, Hkv))
+    main[3, 1] = C - res[3, 1]
+    run_ragged("bf16", B, Hkv, G, d, C, Rcap, res, main, seed=31, nws=nws - 1, compare_head=True)
