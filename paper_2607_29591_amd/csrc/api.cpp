@@ -295,6 +295,16 @@ size_t reskv_build_workspace_size(const reskv_shape_t* shape, const reskv_build_
   return plan.bytes;
 }
 
+int reskv_internal_build_rules(const reskv_shape_t* shape, const reskv_build_params_t* params,
+                               const int32_t* seq_len, const int32_t* budget, const int32_t* res_count,
+                               BuildRules* rules) {
+  if (check_build(shape, params, seq_len, budget, res_count) != RESKV_OK) return 1;
+  BuildPlan pl;
+  if (!make_build_plan(*shape, *params, seq_len, budget, res_count, &pl)) return 1;
+  *rules = BuildRules{pl.deal_rows, pl.KG};
+  return 0;
+}
+
 reskv_status_t reskv_build_cache(const reskv_shape_t* shape, const reskv_build_params_t* params, const void* k,
                                  const void* v, const int32_t* seq_len_host, const void* q_obs,
                                  const int32_t* budget_host, const int32_t* res_count_host, void* kc, void* vc,

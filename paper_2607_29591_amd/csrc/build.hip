@@ -52,7 +52,12 @@ namespace {
 
 constexpr int kThreads = 256;
 constexpr int kKeyGroups = 4;     // 256-key groups per lse chunk (at least) and per score-pass block
-constexpr int kFewChunks = 512;   // lse chunks (score-pass blocks) below which each is spread over more waves (blocks)
+constexpr int kFewScoreBlocks = 512;  // score-pass blocks below which each takes one key group
+// fp32 lse chunks up to which their rows are dealt to blocks 16 at a time: each
+// such block reads the chunk's keys again. A whole scoring construction (d = 128,
+// 128 window rows), undealt / dealt: 4 chunks 135 / 75 us, 64 156 / 118, 128 174 /
+// 176, 160 200 / 218, 256 228 / 302, 384 334 / 426; 64 to 1024 rows cross there too
+constexpr int kDealtChunks = 128;
 // window rows staged in LDS per scoring step: 128, or 256 when there are
 // more than 128 (each key group is then loaded once for all of them)
 constexpr int kRowChunk = 128;
@@ -1888,9 +1893,8 @@ hipError_t launch_scores_typed(const BuildPlan& pl, const BuildArgs& a, hipStrea
   auto grid = [&](int x) { return dim3(x < 1 ? 1 : x, pl.Hkv, pl.B); };
   hipError_t e;
   const dim3 gf = grid((pl.R + kThreads - 1) / kThreads);
-  const bool few = (size_t)pl.B * pl.Hkv * pl.NCH < kFewChunks;
   constexpr bool kBf = sizeof(T) == 2;
-  const bool wide = (kBf || D == 64) && pl.R > kRowChunk;
+  const bool wide = (kBf || D == 64) && pl.R > kRowChunk, few = pl.deal_rows;
   if constexpr (!kBf)
     if (few)
       hipLaunchKernelGGL((lse_partial<T, D, 16, 1, true>), grid(pl.NCH * ((pl.R + 15) / 16)), dim3(256), 0, st, a);
@@ -2031,7 +2035,8 @@ bool layout_build_plan(BuildPlan* plan) {
       break;
     }
   pl.NCH = (pl.max_s + 256 * pl.LG - 1) / (256 * pl.LG);
-  pl.KG = BH * (size_t)((pl.max_s + 256 * kKeyGroups - 1) / (256 * kKeyGroups)) < kFewChunks ? 1 : kKeyGroups;
+  pl.deal_rows = pl.dtype == RESKV_F32 && BH * pl.NCH <= kDealtChunks;
+  pl.KG = BH * (size_t)((pl.max_s + 256 * kKeyGroups - 1) / (256 * kKeyGroups)) < kFewScoreBlocks ? 1 : kKeyGroups;
   pl.NSC = (pl.max_s + 256 * pl.KG - 1) / (256 * pl.KG);
   pl.NBLK = (pl.max_E + kTokBlock - 1) / kTokBlock;
   if (pl.NBLK < 1) pl.NBLK = 1;

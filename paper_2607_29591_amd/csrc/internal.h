@@ -95,6 +95,7 @@ struct BuildPlan {
   int NC;     // candidate counts built in one batch (scratch and grids for B * NC sequences), 1 but for the proxy
   int LG;     // 256-key groups per lse block
   int NCH;    // lse key chunks (256 * LG keys) of the longest sequence
+  bool deal_rows;  // lse rows dealt to blocks 16 at a time (fp32, few chunks)
   int KG;     // 256-key groups per score-pass block
   int NSC;    // score-pass key chunks of the longest sequence
   int NBLK;   // 256-token blocks of the largest evicted set
@@ -106,6 +107,15 @@ struct BuildPlan {
       off_clo, off_cnorm, off_assign, off_hist, off_order, off_items, off_nitem, off_parrive, off_part, off_selh,
       off_sels, off_adah, off_adas, bytes;
 };
+
+// Launch rules of a construction of these sizes, for the tests (not part of
+// the C ABI); nonzero when the arguments are refused.
+struct BuildRules {
+  int32_t deal_rows, key_groups;  // scoring: deal_rows, KG
+};
+extern "C" int reskv_internal_build_rules(const reskv_shape_t* shape, const reskv_build_params_t* params,
+                                          const int32_t* seq_len, const int32_t* budget, const int32_t* res_count,
+                                          BuildRules* rules);
 
 // Device buffers one construction writes.
 struct BuildOut {

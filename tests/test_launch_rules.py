@@ -2,6 +2,7 @@
 launch rules, as the library answers them (no kernel runs here; the results on
 both sides are compared with the oracle in the GPU tests)."""
 
+import ctypes
 import os
 
 import pytest
@@ -66,3 +67,28 @@ def test_branches_one_block_per_head(dtype, G, pairs, C, want):
 ])
 def test_ragged_entry(dtype, d, G, pairs, C, want):
     assert kernels("ragged", dtype, d, G, pairs, C) == want
+
+
+class BuildRules(ctypes.Structure):
+    _fields_ = [(n, ctypes.c_int32) for n in ("deal_rows", "key_groups")]
+
+
+def build_rules(dtype, d, G, heads, s, window, budget=512, res=0):
+    """Launch rules of a construction of `heads` equal heads of s tokens."""
+    i32 = lambda x: (ctypes.c_int32 * len(x))(*x)
+    rules = BuildRules()
+    fn = rk.lib().reskv_internal_build_rules
+    fn.restype, fn.argtypes = ctypes.c_int, None
+    assert fn(ctypes.byref(rk.make_shape(1, G * heads, heads, d, dtype, budget, max(1, res))),
+              ctypes.byref(rk.BuildParams(s, window, window, 4, 0, 0)), i32([s]), i32([budget]), i32([res] * heads),
+              ctypes.byref(rules)) == 0
+    return rules
+
+
+@pytest.mark.parametrize("dtype,heads,s,want", [
+    ("f32", 2, 1024, 1), ("f32", 8, 16384, 1),   # 2 and 128 chunks of 1024 keys
+    ("f32", 8, 16385, 0), ("f32", 8, 32768, 0),  # 136 and 256: 228 us of scoring undealt, 302 dealt
+    ("bf16", 2, 1024, 0),
+])
+def test_lse_rows_dealt(dtype, heads, s, want):
+    assert build_rules(dtype, 128, 4, heads, s, 32).deal_rows == want
