@@ -52,7 +52,15 @@ namespace {
 
 constexpr int kThreads = 256;
 constexpr int kKeyGroups = 4;     // 256-key groups per lse chunk (at least) and per score-pass block
-constexpr int kFewScoreBlocks = 512;  // score-pass blocks below which each takes one key group
+// Score-pass blocks of four key groups up to which the pass takes one group per
+// block instead: more blocks for short passes, but each stages every window row.
+// Whole scoring constructions (d = 128, bf16), four groups / one: 128 rows, 128
+// blocks 89 / 80 us, 256 95 / 91, 384 107 / 109, 480 113 / 118; more rows, whose
+// blocks of eight waves leave four without keys: 256 rows, 128 blocks 103 / 98, 192
+// 107 / 112, 256 111 / 122, 480 144 / 169. fp32 passes are longer per row and
+// gain up to 384 blocks at any count (256 rows 784 / 746 us, 480 blocks 921 / 952).
+constexpr int kFewScoreBlocks = 384;
+constexpr int kFewScoreBlocksWide = 128;  // bf16, more than kRowChunk rows
 // fp32 lse chunks up to which their rows are dealt to blocks 16 at a time: each
 // such block reads the chunk's keys again. A whole scoring construction (d = 128,
 // 128 window rows), undealt / dealt: 4 chunks 135 / 75 us, 64 156 / 118, 128 174 /
@@ -2036,7 +2044,9 @@ bool layout_build_plan(BuildPlan* plan) {
     }
   pl.NCH = (pl.max_s + 256 * pl.LG - 1) / (256 * pl.LG);
   pl.deal_rows = pl.dtype == RESKV_F32 && BH * pl.NCH <= kDealtChunks;
-  pl.KG = BH * (size_t)((pl.max_s + 256 * kKeyGroups - 1) / (256 * kKeyGroups)) < kFewScoreBlocks ? 1 : kKeyGroups;
+  const size_t score_blocks = BH * (size_t)((pl.max_s + 256 * kKeyGroups - 1) / (256 * kKeyGroups));
+  const int few_blocks = pl.dtype == RESKV_BF16 && pl.R > kRowChunk ? kFewScoreBlocksWide : kFewScoreBlocks;
+  pl.KG = score_blocks <= (size_t)few_blocks ? 1 : kKeyGroups;
   pl.NSC = (pl.max_s + 256 * pl.KG - 1) / (256 * pl.KG);
   pl.NBLK = (pl.max_E + kTokBlock - 1) / kTokBlock;
   if (pl.NBLK < 1) pl.NBLK = 1;

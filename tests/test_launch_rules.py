@@ -92,3 +92,12 @@ def build_rules(dtype, d, G, heads, s, window, budget=512, res=0):
 ])
 def test_lse_rows_dealt(dtype, heads, s, want):
     assert build_rules(dtype, 128, 4, heads, s, 32).deal_rows == want
+
+
+@pytest.mark.parametrize("dtype,G,heads,s,want", [
+    ("bf16", 4, 8, 32768, 1), ("bf16", 4, 8, 49152, 1), ("bf16", 4, 8, 49153, 4),   # 128 rows: 256, 384, 392 blocks
+    ("bf16", 8, 8, 16384, 1), ("bf16", 8, 8, 16385, 4), ("bf16", 8, 8, 62000, 4),   # 256 rows: 144 us, 169 with one group
+    ("f32", 8, 8, 49152, 1), ("f32", 8, 8, 62000, 4),
+])
+def test_score_pass_key_groups(dtype, G, heads, s, want):
+    assert build_rules(dtype, 128, G, heads, s, 32).key_groups == want
