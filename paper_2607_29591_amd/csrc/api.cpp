@@ -301,7 +301,7 @@ int reskv_internal_build_rules(const reskv_shape_t* shape, const reskv_build_par
   if (check_build(shape, params, seq_len, budget, res_count) != RESKV_OK) return 1;
   BuildPlan pl;
   if (!make_build_plan(*shape, *params, seq_len, budget, res_count, &pl)) return 1;
-  *rules = BuildRules{pl.deal_rows, pl.KG};
+  *rules = BuildRules{pl.deal_rows, pl.KG, pl.NSEL, pl.count_sel};
   return 0;
 }
 

@@ -16,8 +16,8 @@
 //                  heads' scores, per-head safeguard floor and slot cap) and
 //                  rewrites each head's sizes before the selection
 //   select_hist x2 radix select (11, 11 and 10 bits of the fp32 bit pattern)
-//   select_write   of the k_top-th and (k_top + r')-th largest score over blocks
-//                  of 8192 scores; ties at a threshold go to the lower
+//  [select_count]  of the k_top-th and (k_top + r')-th largest score over blocks
+//   select_write   of 8192 scores (counted by block where the list is long); ties at a threshold go to the lower
 //                  position. Stable compaction writes main_idx (top-k, then
 //                  the protected window), the evicted list E and the Lloyd
 //                  seeds, all ascending
@@ -77,6 +77,7 @@ constexpr int kTokBlock = 256;     // evicted tokens per counting-sort block (hi
 constexpr int kSelThreads = 1024;
 constexpr int kSelPer = 8;                          // scores per selection thread
 constexpr int kSelChunk = kSelPer * kSelThreads;   // scores per selection block
+constexpr int kSelUncounted = 8;                   // blocks up to which the placement counts the scores before a block itself
 constexpr int kSelBins = 2048;                     // digits of the wider selection passes
 constexpr int kAdaHist = kSelBins + 1024;          // cross-head search histograms per head (second and third pass)
 constexpr int kSelHist = 4 * kSelBins;             // selection pass histograms per head (sel_at)
@@ -117,9 +118,10 @@ struct BuildArgs {
   int32_t* ada_hist;   // [BH][kAdaHist] cross-head search histograms (zeroed by pool_scores), or NULL
   uint32_t* ada_state; // [2][B][kAdaState] per sequence: prefix, then the heads' tokens above its range
   uint32_t* sel_state; // [BH][2][4] thresholds' prefixes and remaining ranks after the first and second pass
+  uint4* sel_cnt;      // [BH][NSEL] per selection block: scores above / equal to each threshold (select_count), or NULL
   int NC;              // candidates built in one batch
   int SBH;             // heads with keys and values of their own, B * Hkv of one candidate
-  int B, Hq, Hkv, G, C, Rcap, S, w, R, LG, KG, NCH, NBLK, T;
+  int B, Hq, Hkv, G, C, Rcap, S, w, R, LG, KG, NCH, NBLK, NSEL, T;
   int lpiece, NIT, NPART;  // log2 of the members per update piece, pieces and partial slots per head
   int wr;              // leading window rows per query head that score (R = G * wr)
   int pool_half;       // pooling taps on each side of a position
@@ -558,7 +560,8 @@ __device__ __forceinline__ I block_excl_scan(I v, I* s_tmp, I& total) {
 // still matching a threshold's prefix into the head's pass histogram; the
 // blocks of the next kernel find the digits from the completed histogram.
 // Finally each block places its scores: the counts of the scores before the
-// block above and equal to each threshold give its output offsets and the tie
+// block above and equal to each threshold, taken by the block itself or on long
+// lists by a launch of their own, give its output offsets and the tie
 // ranks of its equal scores (ties are taken lowest position first). Short
 // lists are bound by the launches and the chain of digits: 8 heads of 32K
 // scores took 52 us in seven launches (8-bit passes, a count of their own) and
@@ -773,6 +776,59 @@ __device__ __forceinline__ void sel_place(const BuildArgs& a, const HeadMeta& hm
   for (int i = tid; i < n_seed; i += kSelThreads) seeds[base_seed + i] = i0 + s_seed[i];
 }
 
+// Block sums of the four counts (above and equal to each threshold), above in
+// the low half and equal in the high half. Called by every thread of a
+// kSelThreads block.
+__device__ __forceinline__ void sel_block_counts(int g1, int q1, int g2, int q2, unsigned long long& c1,
+                                                 unsigned long long& c2) {
+  __shared__ unsigned long long s_cnt[2][kSelThreads / 64];
+  const int tid = threadIdx.x;
+  c1 = (unsigned)g1 | (unsigned long long)(unsigned)q1 << 32;
+  c2 = (unsigned)g2 | (unsigned long long)(unsigned)q2 << 32;
+#pragma unroll
+  for (int o = 32; o > 0; o >>= 1) { c1 += __shfl_xor(c1, o, 64); c2 += __shfl_xor(c2, o, 64); }
+  if ((tid & 63) == 0) { s_cnt[0][tid >> 6] = c1; s_cnt[1][tid >> 6] = c2; }
+  __syncthreads();
+  c1 = c2 = 0;
+#pragma unroll
+  for (int w = 0; w < kSelThreads / 64; ++w) { c1 += s_cnt[0][w]; c2 += s_cnt[1][w]; }
+}
+
+// Counts of one block's scores above and equal to the thresholds, for the
+// placement of the blocks after it. Long lists only (kSelUncounted): a block of
+// the placement that counts the scores before it itself saves this launch, but
+// reads 32 KB per block before it through one CU, in all quadratic in the list.
+// Whole constructions without residuals, 8 heads, uncounted / counted: 32K
+// tokens 93 / 98 us, 64K 120 / 120, 128K 181 / 177, 512K 584 / 526, 1M 1172 / 979 (one
+// head 328 / 262); other head counts cross at 64K too.
+__global__ __launch_bounds__(kSelThreads) void select_count(BuildArgs a) {
+  const int bh = blockIdx.z * a.Hkv + blockIdx.y, blk = blockIdx.x, tid = threadIdx.x;
+  const HeadMeta hm = a.meta[bh];
+  const int i0 = blk * kSelChunk, n = hm.n_sc;
+  if (hm.all_main || i0 >= n) return;  // block-uniform
+  const uint32_t* key = reinterpret_cast<const uint32_t*>(a.score + (size_t)bh * a.S);
+  uint32_t u[kSelPer];
+#pragma unroll
+  for (int v = 0; v < kSelPer; ++v) {
+    const int i = i0 + v * kSelThreads + tid;
+    u[v] = i < n ? key[i] : 0u;
+  }
+  SelState st = sel_load(a, bh, 1);
+  sel_digit(a.sel_hist + (size_t)bh * kSelHist, 2, st);  // synchronises the block
+  int g1 = 0, q1 = 0, g2 = 0, q2 = 0;
+#pragma unroll
+  for (int v = 0; v < kSelPer; ++v)
+    if (i0 + v * kSelThreads + tid < n) {
+      g1 += u[v] > st.pref[0]; q1 += u[v] == st.pref[0];
+      g2 += u[v] > st.pref[1]; q2 += u[v] == st.pref[1];
+    }
+  unsigned long long c1, c2;
+  sel_block_counts(g1, q1, g2, q2, c1, c2);
+  if (tid == 0)
+    a.sel_cnt[(size_t)bh * a.NSEL + blk] =
+        make_uint4((uint32_t)c1, (uint32_t)(c1 >> 32), (uint32_t)c2, (uint32_t)(c2 >> 32));
+}
+
 __global__ __launch_bounds__(kSelThreads) void select_write(BuildArgs a) {
   const int bh = blockIdx.z * a.Hkv + blockIdx.y;
   const HeadMeta hm = a.meta[bh];
@@ -780,7 +836,6 @@ __global__ __launch_bounds__(kSelThreads) void select_write(BuildArgs a) {
   sel_fixed(a, hm, bh, blk);
   if (hm.all_main) return;
   if (blk * kSelChunk >= hm.n_sc) return;  // block-uniform
-  __shared__ unsigned long long s_cnt[2][kSelThreads / 64];
   const int n = hm.n_sc, i0 = blk * kSelChunk;
   const uint32_t* key = reinterpret_cast<const uint32_t*>(a.score + (size_t)bh * a.S);
   const int lo = i0 + tid * kSelPer;
@@ -800,32 +855,33 @@ __global__ __launch_bounds__(kSelThreads) void select_write(BuildArgs a) {
   // scores before this block (full chunks) above and equal to each threshold
   SelBase base{0, 0, 0, 0};
   if (blk > 0) {  // block-uniform
-    unsigned long long c1 = 0, c2 = 0;  // above in the low half, equal in the high half
     int g1 = 0, q1 = 0, g2 = 0, q2 = 0;
-    constexpr int kV = 8;  // 16-byte requests in flight
-    for (int x0 = 4 * tid; x0 < i0; x0 += 4 * kV * kSelThreads) {
-      uint32_t u[kV][4];
+    if (a.sel_cnt) {
+      const uint4* cnt = a.sel_cnt + (size_t)bh * a.NSEL;
+      for (int x = tid; x < blk; x += kSelThreads) {
+        const uint4 c = cnt[x];
+        g1 += (int)c.x; q1 += (int)c.y;
+        g2 += (int)c.z; q2 += (int)c.w;
+      }
+    } else {
+      constexpr int kV = 8;  // 16-byte requests in flight
+      for (int x0 = 4 * tid; x0 < i0; x0 += 4 * kV * kSelThreads) {
+        uint32_t u[kV][4];
 #pragma unroll
-      for (int v = 0; v < kV; ++v)
-        if (x0 + 4 * v * kSelThreads < i0) load4(u[v], key + x0 + 4 * v * kSelThreads);
+        for (int v = 0; v < kV; ++v)
+          if (x0 + 4 * v * kSelThreads < i0) load4(u[v], key + x0 + 4 * v * kSelThreads);
 #pragma unroll
-      for (int v = 0; v < kV; ++v)
-        if (x0 + 4 * v * kSelThreads < i0)
+        for (int v = 0; v < kV; ++v)
+          if (x0 + 4 * v * kSelThreads < i0)
 #pragma unroll
-          for (int e = 0; e < 4; ++e) {
-            g1 += u[v][e] > T1; q1 += u[v][e] == T1;
-            g2 += u[v][e] > T2; q2 += u[v][e] == T2;
-          }
+            for (int e = 0; e < 4; ++e) {
+              g1 += u[v][e] > T1; q1 += u[v][e] == T1;
+              g2 += u[v][e] > T2; q2 += u[v][e] == T2;
+            }
+      }
     }
-    c1 = (unsigned)g1 | (unsigned long long)(unsigned)q1 << 32;
-    c2 = (unsigned)g2 | (unsigned long long)(unsigned)q2 << 32;
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1) { c1 += __shfl_xor(c1, o, 64); c2 += __shfl_xor(c2, o, 64); }
-    if ((tid & 63) == 0) { s_cnt[0][tid >> 6] = c1; s_cnt[1][tid >> 6] = c2; }
-    __syncthreads();
-    c1 = c2 = 0;
-#pragma unroll
-    for (int w = 0; w < kSelThreads / 64; ++w) { c1 += s_cnt[0][w]; c2 += s_cnt[1][w]; }
+    unsigned long long c1, c2;  // above in the low half, equal in the high half
+    sel_block_counts(g1, q1, g2, q2, c1, c2);
     base.e1 = (int)(c1 >> 32);
     base.e2 = (int)(c2 >> 32);
     // top scores taken, and those of ranks k1 .. k2 - 1 (the top ones are among the first k2)
@@ -1881,9 +1937,11 @@ BuildArgs make_args(const BuildPlan& pl, const void* k, const void* v, const voi
   a.lpiece = pl.lpiece; a.NIT = pl.NIT; a.NPART = pl.NPART;
   a.sel_hist = reinterpret_cast<int32_t*>(ws + pl.off_selh);
   a.sel_state = reinterpret_cast<uint32_t*>(ws + pl.off_sels);
+  a.sel_cnt = pl.count_sel ? reinterpret_cast<uint4*>(ws + pl.off_selc) : nullptr;
   a.NC = pl.NC; a.SBH = pl.B * pl.Hkv;
   a.B = pl.B; a.Hq = pl.Hq; a.Hkv = pl.Hkv; a.G = pl.G; a.C = pl.C; a.Rcap = pl.Rcap; a.S = pl.S; a.w = pl.w;
-  a.wr = pl.wr; a.pool_half = pl.pool_half; a.R = pl.R; a.LG = pl.LG; a.KG = pl.KG; a.NCH = pl.NCH; a.NBLK = pl.NBLK; a.T = pl.T;
+  a.wr = pl.wr; a.pool_half = pl.pool_half; a.R = pl.R; a.LG = pl.LG; a.KG = pl.KG; a.NCH = pl.NCH; a.NBLK = pl.NBLK;
+  a.NSEL = pl.NSEL; a.T = pl.T;
   a.cap_slots = pl.C;
   a.scale2 = kLog2e / sqrtf((float)pl.D);
   return a;
@@ -1950,6 +2008,9 @@ hipError_t launch_candidate_typed(const BuildPlan& pl, const BuildArgs& a, hipSt
     }
     hipLaunchKernelGGL(select_hist<1>, grid(pl.NSEL), dim3(kSelThreads), 0, st, a); RESKV_CHECK();
     hipLaunchKernelGGL(select_hist<2>, grid(pl.NSEL), dim3(kSelThreads), 0, st, a); RESKV_CHECK();
+    if (pl.count_sel) {
+      hipLaunchKernelGGL(select_count, grid(pl.NSEL), dim3(kSelThreads), 0, st, a); RESKV_CHECK();
+    }
     hipLaunchKernelGGL(select_write, grid(pl.NSEL), dim3(kSelThreads), 0, st, a); RESKV_CHECK();
   }
   const int rows = pl.max_main + pl.Rcap;
@@ -2052,6 +2113,7 @@ bool layout_build_plan(BuildPlan* plan) {
   if (pl.NBLK < 1) pl.NBLK = 1;
   pl.NSEL = (pl.max_s + kSelChunk - 1) / kSelChunk;
   if (pl.NSEL < 1) pl.NSEL = 1;
+  pl.count_sel = pl.NSEL > kSelUncounted;
   const int nb64 = (pl.max_E + 63) / 64;
   pl.one_sort = nb64 <= kSortBatches * (kSortThreads / 64) && pl.max_reff <= kSortThreads &&
                 (long long)nb64 * pl.max_reff <= kSortTable;
@@ -2083,6 +2145,7 @@ bool layout_build_plan(BuildPlan* plan) {
   pl.off_part = take(CH * pl.NPART * 2 * pl.D * sizeof(double));
   pl.off_selh = take(CH * kSelHist * sizeof(int32_t));
   pl.off_sels = take(CH * 8 * sizeof(uint32_t));
+  pl.off_selc = take(pl.count_sel ? CH * pl.NSEL * sizeof(uint4) : 0);
   pl.bytes = off;
   return true;
 }

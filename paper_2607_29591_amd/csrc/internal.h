@@ -100,18 +100,20 @@ struct BuildPlan {
   int NSC;    // score-pass key chunks of the longest sequence
   int NBLK;   // 256-token blocks of the largest evicted set
   int NSEL;   // selection blocks (8192 scores each) of the longest sequence
+  bool count_sel;  // selection blocks leave their counts for the placement (long lists)
   int max_s, max_main, max_reff, max_E;
   bool one_sort;  // one block sorts a head's evicted tokens (short lists)
   int lpiece, NIT, NPART;  // log2 of the members per update piece; pieces and partial-sum slots per head
   size_t off_meta, off_lsep, off_lse, off_raw, off_score, off_elist, off_seeds, off_cent, off_chi,
       off_clo, off_cnorm, off_assign, off_hist, off_order, off_items, off_nitem, off_parrive, off_part, off_selh,
-      off_sels, off_adah, off_adas, bytes;
+      off_sels, off_selc, off_adah, off_adas, bytes;
 };
 
 // Launch rules of a construction of these sizes, for the tests (not part of
 // the C ABI); nonzero when the arguments are refused.
 struct BuildRules {
   int32_t deal_rows, key_groups;  // scoring: deal_rows, KG
+  int32_t select_blocks, count_sel;  // selection: NSEL, count_sel
 };
 extern "C" int reskv_internal_build_rules(const reskv_shape_t* shape, const reskv_build_params_t* params,
                                           const int32_t* seq_len, const int32_t* budget, const int32_t* res_count,

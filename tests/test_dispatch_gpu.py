@@ -76,6 +76,9 @@ def test_scoring_row_chunks(dtype, d, G, window, s):
     (8192, 700, (30, 699), 8),        # the longest list of the one-block selection
     (1024 + 8, 100, (20, 99), 8),     # one score per thread there, and two
     (1025 + 8, 100, (20, 0), 8),
+    (65536, 900, (50, 3), 8),         # eight blocks, counted by the placement itself
+    (65537, 900, (50, 3), 8),         # nine blocks (by context length): counts in a launch of their own
+    (9 * 8192 + 9, 40000, (7, 600), 8),  # ten blocks, one score in the last, both thresholds deep
 ])
 def test_selection_blocks(s, budget, res, recent):
     """Score lists at the edges of the selection's 8192-score blocks, with the
@@ -89,14 +92,16 @@ def test_selection_blocks(s, budget, res, recent):
         check_head(wl, x, got, 0, h, recent=recent, iters=1)
 
 
-def test_selection_tied_scores():
+@pytest.mark.parametrize("s,budget", [(20000, 10100), (80000, 45000)])
+def test_selection_tied_scores(s, budget):
     """Equal keys give equal scores over several blocks: the lowest positions
-    are taken, counted over the blocks before."""
-    s, window = 20000, 8
-    wl = synth.tiny_workload(s=s, d=64, hq=4, hkv=2, budget=10100, res=0, window=window, dtype="bf16", n_heavy=6)
+    are taken, counted over the blocks before (by the placement itself, and on
+    the long list by a launch of its own)."""
+    window = 8
+    wl = synth.tiny_workload(s=s, d=64, hq=4, hkv=2, budget=budget, res=0, window=window, dtype="bf16", n_heavy=6)
     wl.res = np.asarray((40, 0), np.int64).reshape(1, 1, 2)
     x = synth.gen_layer(wl, 0, seed=3, n_decode=1)
-    x["K"][:, :, 200:19000] = x["K"][:, :, 200:201]
+    x["K"][:, :, 200:s - 1000] = x["K"][:, :, 200:201]
     got = run_build(wl, host_copies(x), iters=1)
     for h in range(2):
         check_head(wl, x, got, 0, h, iters=1)

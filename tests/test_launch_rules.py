@@ -70,7 +70,7 @@ def test_ragged_entry(dtype, d, G, pairs, C, want):
 
 
 class BuildRules(ctypes.Structure):
-    _fields_ = [(n, ctypes.c_int32) for n in ("deal_rows", "key_groups")]
+    _fields_ = [(n, ctypes.c_int32) for n in ("deal_rows", "key_groups", "select_blocks", "count_sel")]
 
 
 def build_rules(dtype, d, G, heads, s, window, budget=512, res=0):
@@ -101,3 +101,11 @@ def test_lse_rows_dealt(dtype, heads, s, want):
 ])
 def test_score_pass_key_groups(dtype, G, heads, s, want):
     assert build_rules(dtype, 128, G, heads, s, 32).key_groups == want
+
+
+@pytest.mark.parametrize("s,blocks,counted", [(8192, 1, 0), (65536, 8, 0), (65537, 9, 1), (1 << 20, 128, 1)])
+def test_long_score_lists_are_counted(s, blocks, counted):
+    """The placement rereads the scores before a block only on lists of up to 8 blocks (1M tokens, 8 heads: 979 us of
+    construction counted, 1172 reread)."""
+    rules = build_rules("bf16", 64, 4, 2, s, 8)
+    assert (rules.select_blocks, rules.count_sel) == (blocks, counted)
