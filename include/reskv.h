@@ -255,7 +255,11 @@ typedef struct {
  *   val_loss        optional (NULL) out fp32 [B*Hkv, n_grid]: the loss of
  *                   every candidate, in grid order
  *   workspace       device scratch of reskv_build_proxy_workspace_size()
- *                   bytes; it holds every candidate cache
+ *                   bytes; it holds every candidate cache. For up to 64
+ *                   (sequence, KV head) pairs that size has construction
+ *                   scratch for every candidate (built together); a buffer
+ *                   with scratch for one is accepted too, and gives the same
+ *                   result with the candidates built one after the other.
  *
  * Every candidate must satisfy r_f < b and r_f <= Rcap.
  * Returns RESKV_OK or an error code before launching anything.

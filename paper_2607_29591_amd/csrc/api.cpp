@@ -430,8 +430,21 @@ size_t reskv_build_proxy_workspace_size(const reskv_shape_t* shape, const reskv_
   reskv_build_params_t pf;
   if (check_proxy(shape, params, proxy, seq_len_host, budget_host, &pf) != RESKV_OK) return 0;
   ProxyPlan plan;
-  if (!make_proxy_plan(*shape, pf, *proxy, seq_len_host, budget_host, &plan)) return 0;
+  if (!make_proxy_plan(*shape, pf, *proxy, seq_len_host, budget_host, true, &plan)) return 0;
   return plan.bytes;
+}
+
+int reskv_internal_proxy_rules(const reskv_shape_t* shape, const reskv_build_params_t* params,
+                               const reskv_proxy_params_t* proxy, const int32_t* seq_len, const int32_t* budget,
+                               ProxyRules* rules) {
+  reskv_build_params_t pf;
+  if (check_proxy(shape, params, proxy, seq_len, budget, &pf) != RESKV_OK) return 1;
+  ProxyPlan all, least;
+  if (!make_proxy_plan(*shape, pf, *proxy, seq_len, budget, true, &all) ||
+      !make_proxy_plan(*shape, pf, *proxy, seq_len, budget, false, &least))
+    return 1;
+  *rules = ProxyRules{all.build.NC, least.bytes};
+  return 0;
 }
 
 reskv_status_t reskv_build_cache_proxy(const reskv_shape_t* shape, const reskv_build_params_t* params,
@@ -447,7 +460,10 @@ reskv_status_t reskv_build_cache_proxy(const reskv_shape_t* shape, const reskv_b
   if (!k || !v || !q_obs || !kc || !vc || !logc || !main_idx || !res_len || !main_len)
     return fail(RESKV_ERR_INVALID_ARG, "a required pointer is NULL");
   ProxyPlan plan;
-  if (!make_proxy_plan(*shape, pf, *proxy, seq_len_host, budget_host, &plan))
+  // a workspace too small for all candidates at once may still hold one at a time
+  if (!make_proxy_plan(*shape, pf, *proxy, seq_len_host, budget_host, true, &plan) ||
+      (plan.build.NC > 1 && workspace_bytes < plan.bytes &&
+       !make_proxy_plan(*shape, pf, *proxy, seq_len_host, budget_host, false, &plan)))
     return fail(RESKV_ERR_UNSUPPORTED, "proxy plan could not be formed for these sizes");
   if (!workspace || workspace_bytes < plan.bytes)
     return fail(RESKV_ERR_WORKSPACE, "proxy build needs %zu workspace bytes, got %zu", plan.bytes,

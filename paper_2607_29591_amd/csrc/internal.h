@@ -203,8 +203,20 @@ struct ProxyPlan {
   size_t bytes;
 };
 
+// batch: all candidates in one batch where that is faster; false: one after
+// the other, the least workspace.
 bool make_proxy_plan(const reskv_shape_t& s, const reskv_build_params_t& p, const reskv_proxy_params_t& x,
-                     const int32_t* seq_len, const int32_t* budget, ProxyPlan* plan);
+                     const int32_t* seq_len, const int32_t* budget, bool batch, ProxyPlan* plan);
+
+// How a proxy construction of these sizes builds its candidates, for the tests
+// (not part of the C ABI); nonzero when the arguments are refused.
+struct ProxyRules {
+  int32_t batched;       // candidates built in one batch
+  uint64_t least_bytes;  // workspace that one candidate at a time needs
+};
+extern "C" int reskv_internal_proxy_rules(const reskv_shape_t* shape, const reskv_build_params_t* params,
+                                          const reskv_proxy_params_t* proxy, const int32_t* seq_len,
+                                          const int32_t* budget, ProxyRules* rules);
 
 hipError_t launch_build_proxy(const reskv_shape_t& s, const reskv_build_params_t& p,
                               const reskv_proxy_params_t& x, const reskv_gate_t& g, const ProxyPlan& pl,

@@ -29,7 +29,10 @@ namespace reskv {
 namespace {
 
 constexpr int kThreads = 256;
-constexpr int kBatchHeads = 64;       // (b, kv head) pairs up to which the candidates are built in one batch
+// (b, kv head) pairs and 256-token assignment blocks of a candidate up to which
+// the candidates are built in one batch
+constexpr int kBatchHeads = 64;
+constexpr int kBatchBlocks = 8192;
 constexpr int kMaxChunkQueries = 16;  // decode handles groups of at most 16 query heads
 
 // Validation query jj = h * val + i of kv head kvh is window row fit + i of
@@ -214,7 +217,7 @@ hipError_t launch_tail(const ProxyPlan& pl, const GatherArgs& ga, const CopyArgs
 }  // namespace
 
 bool make_proxy_plan(const reskv_shape_t& s, const reskv_build_params_t& p, const reskv_proxy_params_t& x,
-                     const int32_t* seq_len, const int32_t* budget, ProxyPlan* plan) {
+                     const int32_t* seq_len, const int32_t* budget, bool batch, ProxyPlan* plan) {
   ProxyPlan& pl = *plan;
   pl = ProxyPlan{};
   reskv_build_params_t pf = p;
@@ -242,9 +245,13 @@ bool make_proxy_plan(const reskv_shape_t& s, const reskv_build_params_t& p, cons
     if (!fold_build_plan(hm, &bp)) return false;
   }
   // All candidates in one batch while a candidate's heads leave the launches
-  // short (16 heads of 32K tokens, five candidates: 2320 -> 1790 us); a larger
-  // batch fills the GPU by itself and would only take the scratch five times.
-  bp.NC = BH <= kBatchHeads ? pl.NG : 1;
+  // short; a larger batch fills the GPU by itself and would only take the
+  // scratch once per candidate. Five candidates, one after the other / in one
+  // batch: 2 heads of 1K tokens 487 / 227 us, 64 x 8K (2K blocks) 1933 / 1448,
+  // 8 x 128K (4K) 3426 / 2792, 64 x 32K (8K) 5779 / 5494 with 345 / 577 MB of workspace,
+  // 32 x 128K (16K) 11211 / 10864 with 348 / 769 MB.
+  const size_t blocks = (size_t)BH * ((bp.max_E + 255) / 256);
+  bp.NC = batch && BH <= kBatchHeads && blocks <= kBatchBlocks ? pl.NG : 1;
   if (!layout_build_plan(&bp)) return false;
   pl.dec_full = make_decode_plan(full_shape(pl));
   pl.dec_cand = make_decode_plan(cand_shape(pl));

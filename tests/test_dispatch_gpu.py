@@ -4,6 +4,7 @@ one kernel variant to another, each against the fp64 oracle."""
 import numpy as np
 import pytest
 
+from paper_2607_29591_amd import reskv as rk
 from paper_2607_29591_amd import synth
 from tests.build_check import check_head, run_build
 from tests.test_adakv_gpu import check_sequence, workload as ada_workload
@@ -11,7 +12,8 @@ from tests.test_build_gpu import host_copies
 from tests.test_decode_branches_gpu import run_case as run_branches
 from tests.test_decode_gpu import cache_case, check
 from tests.test_decode_ragged_gpu import run_ragged
-from tests.test_proxy_gpu import GRID, check_proxy
+from tests.test_launch_rules import proxy_rules
+from tests.test_proxy_gpu import GRID, check_proxy, run_proxy
 from tests.test_graph_gpu import test_decode_step_graph_replays_match_eager as graph_replays
 
 pytestmark = pytest.mark.gpu
@@ -175,6 +177,32 @@ def test_proxy_candidate_batches(B):
     wl.res = np.full((1, B, 8), 8)
     x = host_copies(synth.gen_layer(wl, 0, seed=B, n_decode=1))
     check_proxy(wl, x, GRID, 2, 0.01, full_heads=[(0, 0), (B - 1, 7)])
+
+
+@pytest.mark.parametrize("B,Hkv", [(9, 8), (1, 3)])
+def test_proxy_candidates_one_after_the_other(B, Hkv):
+    """Candidates built one after the other on score lists of several selection
+    blocks, whose histograms each candidate must find cleared: 72 heads by the
+    rule; 3 heads through a workspace with scratch for one candidate only,
+    bit for bit what the batch gives."""
+    wl = synth.tiny_workload(s=8600, d=64, hq=Hkv, hkv=Hkv, budget=60, res=0, window=8, dtype="bf16", batch=B, n_heavy=3)
+    wl.ctx = [8600 - 41 * b for b in range(B)]
+    wl.res = np.full((1, B, Hkv), 12)
+    x = host_copies(synth.gen_layer(wl, 0, seed=40 + B, n_decode=1))
+    shape = rk.make_shape(B, wl.hq, Hkv, wl.d, "bf16", wl.slot_cap, wl.res_cap)
+    params = rk.BuildParams(x["K"].shape[2], wl.window, wl.window, wl.lloyd_iters, 0)
+    rules = proxy_rules(shape, params, rk.make_proxy(GRID, 2, 0.01), x["seq_len"], x["budget"])
+    assert rules.batched == (1 if B == 9 else len(GRID))
+    _, got = check_proxy(wl, x, GRID, 2, 0.01, full_heads=[(0, 0), (B - 1, Hkv - 1)])
+    if rules.batched > 1:
+        one = run_proxy(wl, x, GRID, 2, 0.01, nws=rules.least_bytes)
+        for b in range(B):
+            for h in range(Hkv):
+                r, n = got["res_len"][b, h], got["main_len"][b, h]
+                for k, m in (("kc", r + n), ("vc", r + n), ("logc", None), ("main_idx", n), ("val_loss", None)):
+                    np.testing.assert_array_equal(one[k][b, h, :m], got[k][b, h, :m], err_msg=k)
+        for k in ("res_len", "main_len"):
+            np.testing.assert_array_equal(one[k], got[k])
 
 
 @pytest.mark.parametrize("dtype,d,G,C", [("bf16", 128, 7, 600), ("f32", 64, 4, 300), ("bf16", 64, 16, 8300)])

@@ -109,3 +109,32 @@ def test_long_score_lists_are_counted(s, blocks, counted):
     construction counted, 1172 reread)."""
     rules = build_rules("bf16", 64, 4, 2, s, 8)
     assert (rules.select_blocks, rules.count_sel) == (blocks, counted)
+
+
+class ProxyRules(ctypes.Structure):
+    _fields_ = [("batched", ctypes.c_int32), ("least_bytes", ctypes.c_uint64)]
+
+
+def proxy_rules(shape, params, proxy, seq_len, budget):
+    i32 = lambda x: (ctypes.c_int32 * len(x))(*[int(v) for v in x])
+    rules = ProxyRules()
+    fn = rk.lib().reskv_internal_proxy_rules
+    fn.restype, fn.argtypes = ctypes.c_int, None
+    assert fn(ctypes.byref(shape), ctypes.byref(params), ctypes.byref(proxy), i32(seq_len), i32(budget),
+              ctypes.byref(rules)) == 0
+    return rules
+
+
+@pytest.mark.parametrize("batch,ctx,want", [
+    (8, 8192, 5), (9, 8192, 1),       # 64 and 72 pairs
+    (8, 32768, 5), (8, 34000, 1),     # 64 pairs: up to 8192 assignment blocks of a candidate
+    (4, 65536, 5), (4, 66000, 1),
+])
+def test_proxy_candidates_in_one_batch(batch, ctx, want):
+    """The batch and its scratch per candidate stop with the context too, and the size query follows."""
+    shape = rk.make_shape(batch, 32, 8, 128, "bf16", 256, 64)
+    params, proxy = rk.BuildParams(ctx, 32, 32, 4, 0, 0), rk.make_proxy()
+    rules = proxy_rules(shape, params, proxy, [ctx] * batch, [256] * batch)
+    assert rules.batched == want
+    size = rk.reskv_build_proxy_workspace_size(shape, params, proxy, [ctx] * batch, [256] * batch)
+    assert size > rules.least_bytes if want > 1 else size == rules.least_bytes

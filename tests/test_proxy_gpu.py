@@ -52,7 +52,7 @@ def to_dev(a, dtype):
     return (t.to(torch.bfloat16) if dtype == "bf16" else t).cuda().contiguous()
 
 
-def run_proxy(wl, x, grid, val, delta, gate=GATE, recent=None):
+def run_proxy(wl, x, grid, val, delta, gate=GATE, recent=None, nws=None):
     B, Hkv, d = wl.batch, wl.hkv, wl.d
     S = x["K"].shape[2]
     C, Rcap = wl.slot_cap, wl.res_cap
@@ -68,7 +68,8 @@ def run_proxy(wl, x, grid, val, delta, gate=GATE, recent=None):
     res_len = torch.full((B * Hkv,), -7, dtype=torch.int32, device="cuda")
     main_len = torch.full((B * Hkv,), -7, dtype=torch.int32, device="cuda")
     val_loss = torch.full((B * Hkv, len(grid)), float("nan"), device="cuda")
-    nws = rk.reskv_build_proxy_workspace_size(shape, params, proxy, x["seq_len"], x["budget"])
+    if nws is None:
+        nws = rk.reskv_build_proxy_workspace_size(shape, params, proxy, x["seq_len"], x["budget"])
     assert nws > 0, rk.last_error()
     ws = torch.empty(nws, dtype=torch.uint8, device="cuda")
     rk.reskv_build_cache_proxy(shape, params, proxy, g, to_dev(x["K"], wl.dtype), to_dev(x["V"], wl.dtype),
