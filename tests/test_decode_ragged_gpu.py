@@ -1,13 +1,14 @@
-"""GPU parity of reskv_decode_attn_ragged (the balanced-range schedule of
-the shared-softmax decode, Sec. 5.4, Sec. 5.5.2, App. D Algorithm 2) against
-the fp64 oracle, through the C ABI.
+"""GPU parity of reskv_decode_attn_ragged (Sec. 5.4, Sec. 5.5.2, App. D
+Algorithm 2) against the fp64 oracle, through the C ABI: the balanced-range
+schedule, and the per-head kernels that serve small batches. Every case says
+which of them it takes, so a change of the rule cannot move it unnoticed.
 
 Cases cover: fewer units than blocks (every head split over many blocks,
 each block one unit or none), more units than 16 per CU (more blocks than
 CUs), heads of one unit, r = 0 and empty residual entries, group sizes
-1-8, bf16 d 64/128 and fp32 d 64, the fused append (cache rows, main_len)
-with full caches left unchanged, per-query tau, and agreement with
-reskv_decode_attn on the same inputs."""
+1-8, bf16 d 64/128 and fp32 d 64, with and without the fused append (cache
+rows, main_len) with full caches left unchanged, per-query tau, bitwise
+equal reruns, and agreement with reskv_decode_attn on the same inputs."""
 
 import numpy as np
 import pytest
@@ -18,6 +19,8 @@ from paper_2607_29591_amd import reskv as rk
 from tests.helpers import TOL, gate_atol, random_cache, rel_err_rows, to_dev
 
 pytestmark = pytest.mark.gpu
+
+HEAD, SPLIT, RANGES = "decode_head", "decode_split + decode_combine", "decode_ragged + decode_ragged_combine"
 
 GATE = dict(tau_scalar=0.25, alpha=12.0, g_min=0.0, beta=1.0)
 
@@ -39,11 +42,12 @@ def ragged_case(seed, B, Hkv, G, d, dtype, C, Rcap, res, main, appends):
 
 
 def run_ragged(dtype, B, Hkv, G, d, C, Rcap, res, main, seed=0, appends=True, compare_head=False,
-               nws=None):
+               nws=None, kernels=None):
     res = np.asarray(res, np.int64)
     main = np.asarray(main, np.int64)
     q, kc, vc, logc, tau, kn, vn = ragged_case(seed, B, Hkv, G, d, dtype, C, Rcap, res, main, appends)
     shape = rk.make_shape(B, Hkv * G, Hkv, d, dtype, C, Rcap)
+    assert kernels in (None, rk.decode_kernels(shape, "ragged"))
     nws = rk.reskv_decode_ragged_workspace_size(shape) if nws is None else nws
     assert nws > 0
     ws = torch.empty(nws, dtype=torch.uint8, device="cuda")
@@ -103,15 +107,18 @@ def run_ragged(dtype, B, Hkv, G, d, C, Rcap, res, main, seed=0, appends=True, co
     return err
 
 
+@pytest.mark.parametrize("C,appends,kernels", [(1200, True, SPLIT), (2400, True, RANGES), (2400, False, RANGES)])
 @pytest.mark.parametrize("dtype,d,G", [("bf16", 128, 7), ("bf16", 128, 4), ("bf16", 64, 8), ("f32", 64, 2),
                                        ("bf16", 128, 1)])
-def test_ragged_few_units(dtype, d, G):
-    """Fewer units than blocks: long heads are shared by many blocks of one
-    unit each."""
-    B, Hkv, C, Rcap = 3, 4, 1200, 320
+def test_ragged_few_units(dtype, d, G, C, appends, kernels):
+    """Fewer units than blocks: in equal ranges (2400-slot caches) long heads
+    are shared by many blocks of one unit each; shorter caches take the split
+    kernels."""
+    B, Hkv, Rcap = 3, 4, 320
     res = [[0, 300, 16, 64], [257, 0, 1, 128], [0, 0, 64, 5]]
-    main = [[1, 850, 1100, 64], [900, 1200, 33, 1000], [65, 640, 1, 700]]
-    run_ragged(dtype, B, Hkv, G, d, C, Rcap, res, main, seed=d + G, compare_head=True)
+    main = [[1, 850, 1100, 64], [900, C, 33, 1000], [65, 640, 1, 700]]
+    run_ragged(dtype, B, Hkv, G, d, C, Rcap, res, main, seed=d + G, appends=appends, compare_head=True,
+               kernels=kernels)
 
 
 def test_ragged_many_units():
@@ -123,30 +130,35 @@ def test_ragged_many_units():
     res = rng.choice([0, 16, 64, 256, 512], size=(B, Hkv))
     main = np.minimum(rng.integers(1, 2000, size=(B, Hkv)), C - res)
     main[0, 0] = C - res[0, 0]  # full: no append
-    run_ragged("bf16", B, Hkv, G, d, C, Rcap, res, main, seed=7, compare_head=True)
+    run_ragged("bf16", B, Hkv, G, d, C, Rcap, res, main, seed=7, compare_head=True, kernels=RANGES)
 
 
+@pytest.mark.parametrize("B,kernels", [(64, HEAD), (65, RANGES)])
 @pytest.mark.parametrize("appends", [False, True])
-def test_ragged_gqa7_workload_shape(appends):
+def test_ragged_gqa7_workload_shape(appends, B, kernels):
     """The ragged GQA-7 layer's shape (64 sequences x 4 KV heads, budgets
-    256-1024 with r a fraction of the budget, room for 128 appends)."""
+    256-1024 with r a fraction of the budget, room for 128 appends), served
+    by one block per head; with one sequence more, by equal ranges."""
     rng = np.random.default_rng(11)
-    B, Hkv, G, d = 64, 4, 7, 128
+    Hkv, G, d = 4, 7, 128
     budget = rng.choice([256, 512, 1024], size=B)
     frac = rng.uniform(0, 0.5, size=(B, Hkv))
     res = (16 * np.floor(frac * budget[:, None] / 16 + 0.5)).astype(np.int64)
     main = budget[:, None] - res + rng.integers(0, 128, size=(B, Hkv))
     C, Rcap = 1152, int(res.max())
-    run_ragged("bf16", B, Hkv, G, d, C, Rcap, res, main, seed=13, appends=appends, compare_head=True)
+    run_ragged("bf16", B, Hkv, G, d, C, Rcap, res, main, seed=13, appends=appends, compare_head=True,
+               kernels=kernels)
 
 
-def test_ragged_is_deterministic():
-    B, Hkv, G, d, C, Rcap = 8, 4, 7, 128, 600, 64
+@pytest.mark.parametrize("G,C,kernels", [(7, 600, HEAD), (7, 2400, RANGES), (1, 2400, RANGES)])
+def test_ragged_is_deterministic(G, C, kernels):
+    B, Hkv, d, Rcap = 8, 4, 128, 64
     rng = np.random.default_rng(3)
     res = rng.choice([0, 16, 64], size=(B, Hkv))
-    main = rng.integers(1, 500, size=(B, Hkv))
+    main = rng.integers(1, C - 100, size=(B, Hkv))
     q, kc, vc, logc, tau, _, _ = ragged_case(3, B, Hkv, G, d, "bf16", C, Rcap, res, main, False)
     shape = rk.make_shape(B, Hkv * G, Hkv, d, "bf16", C, Rcap)
+    assert rk.decode_kernels(shape, "ragged") == kernels
     ws = torch.empty(rk.reskv_decode_ragged_workspace_size(shape), dtype=torch.uint8, device="cuda")
     args = [to_dev(q, "bf16"), to_dev(kc, "bf16"), to_dev(vc, "bf16"),
             torch.as_tensor(logc.astype(np.float32)).cuda(), torch.as_tensor(res.astype(np.int32).reshape(-1)).cuda(),
@@ -164,7 +176,8 @@ def test_ragged_long_heads():
     """Two 8000-slot heads over a grid of 256 blocks: the plan keeps at least
     two units per block so a head spans no more blocks than the combine
     merges, and each head is shared by about 60 blocks."""
-    run_ragged("bf16", 1, 2, 4, 128, 8192, 512, [[0, 512]], [[8000, 7000]], seed=17, compare_head=True)
+    run_ragged("bf16", 1, 2, 4, 128, 8192, 512, [[0, 512]], [[8000, 7000]], seed=17, compare_head=True,
+               kernels=RANGES)
 
 
 def test_ragged_skewed_batch():
@@ -175,7 +188,7 @@ def test_ragged_skewed_batch():
     res = rng.choice([0, 16, 64], size=(B, Hkv))
     main = rng.integers(200, 300, size=(B, Hkv)) - res
     main[7, 2] = 8000 - res[7, 2]
-    run_ragged("bf16", B, Hkv, G, d, C, Rcap, res, main, seed=23, compare_head=True)
+    run_ragged("bf16", B, Hkv, G, d, C, Rcap, res, main, seed=23, compare_head=True, kernels=RANGES)
 
 
 def test_ragged_small_workspace_takes_equal_ranges():

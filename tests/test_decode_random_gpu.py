@@ -10,12 +10,14 @@ applies: groups up to 8, bf16 or rows of 64) and reskv_decode_attn_static
 same inputs; for each, every query head is compared with the oracle
 decoding the same cache (after the append), to the bar of the other decode
 tests, and the appended rows and lengths bit for bit. About half of the
-seeds have 256 (b, kv head) pairs (the one-block-per-head kernel), the
-others a few pairs (the split kernels). Ten more seeds draw 256 pairs of
-520-1400-slot caches with up to 800 residual entries, so the one-block-per-
-head kernel streams main blocks past its first round in its staggered
-order, residual units run past the first round, and the block holding slot
-r is split between the kinds.
+first seeds have 256 (b, kv head) pairs (the one-block-per-head kernel), the
+others a few pairs (one block per head or the split kernels, by capacity).
+Ten more seeds draw 256 pairs of 520-1400-slot caches with up to 800 residual
+entries, so the one-block-per-head kernel streams main blocks past its first
+round in its staggered order, residual units run past the first round, and
+the block holding slot r is split between the kinds. Twelve more are shapes
+of the split kernels and twelve of the equal unit ranges of the ragged entry,
+each held to be so.
 """
 
 import numpy as np
@@ -53,18 +55,57 @@ def draw_case(seed, long_heads=False):
         B = int(rng.integers(1, 6))
         C = int(rng.integers(8, 1400))
         Rcap = int(rng.integers(1, 300))
+    return (rng, dtype, d, G, B, Hkv, C, Rcap) + draw_rest(rng, B, Hkv, C, Rcap)
+
+
+def draw_kernels(seed, kernels):
+    """Shapes of the split kernels (reskv_decode_attn) or of the equal ranges
+    (reskv_decode_attn_ragged): few pairs of longer caches, or more pairs than
+    one block per head serves at once."""
+    rng = np.random.default_rng(3000 + seed + (100 if kernels == "ranges" else 0))
+    dtype, d = [("bf16", 128), ("bf16", 64), ("bf16", 128), ("f32", 64)][seed % 4]
+    Hkv = int(rng.choice([1, 2, 4]))
+    if kernels == "split":
+        G = int(rng.choice([1, 2, 4, 7, 8, 16]))
+        B, C = int(rng.integers(1, 9)), int(rng.integers(700, 2600))
+    else:
+        G = int(rng.choice([1, 2, 3, 4, 7, 8]))
+        if seed % 3 == 0:  # more than 256 pairs
+            B, C = -(-int(rng.integers(257, 330)) // Hkv), int(rng.integers(64, 700))
+        else:
+            B, C = int(rng.integers(1, 9)), int(rng.integers(2305, 3400))
+    Rcap = int(rng.integers(1, 400))
+    return (rng, dtype, d, G, B, Hkv, C, Rcap) + draw_rest(rng, B, Hkv, C, Rcap)
+
+
+def draw_rest(rng, B, Hkv, C, Rcap):
     res = rng.integers(0, min(Rcap, C - 1) + 1, size=(B, Hkv))
     main = np.array([[int(rng.integers(1, C - r + 1)) for r in row] for row in res])
     gate = dict(tau_scalar=float(rng.uniform(0.05, 0.6)), alpha=float(rng.choice([4.0, 12.0])),
                 g_min=float(rng.choice([0.0, 0.2])), beta=float(rng.choice([0.5, 1.0])))
     per_query_tau = bool(rng.integers(0, 2))
     append = bool(rng.integers(0, 2))
-    return rng, dtype, d, G, B, Hkv, C, Rcap, res, main, gate, per_query_tau, append
+    return res, main, gate, per_query_tau, append
 
 
 @pytest.mark.parametrize("long_heads,seed", [(False, s) for s in range(40)] + [(True, s) for s in range(10)])
 def test_decode_random_shape(long_heads, seed):
-    rng, dtype, d, G, B, Hkv, C, Rcap, res, main, gate, per_query_tau, append = draw_case(seed, long_heads)
+    check_case(*draw_case(seed, long_heads))
+
+
+@pytest.mark.parametrize("kernels", ["split", "ranges"])
+@pytest.mark.parametrize("seed", range(12))
+def test_decode_random_shape_of(kernels, seed):
+    case = draw_kernels(seed, kernels)
+    _, dtype, d, G, B, Hkv, C, Rcap = case[:8]
+    shape = rk.make_shape(B, G * Hkv, Hkv, d, dtype, C, Rcap)
+    entry, names = {"split": ("attn", "decode_split + decode_combine"),
+                    "ranges": ("ragged", "decode_ragged + decode_ragged_combine")}[kernels]
+    assert rk.decode_kernels(shape, entry) == names
+    check_case(*case)
+
+
+def check_case(rng, dtype, d, G, B, Hkv, C, Rcap, res, main, gate, per_query_tau, append):
     Hq = G * Hkv
     kc, vc, logc = random_cache(rng, B, Hkv, C, Rcap, d, dtype, res, main)
     q = rng.normal(size=(B, Hq, d)) * 1.5

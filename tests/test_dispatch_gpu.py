@@ -11,7 +11,7 @@ from tests.test_adakv_gpu import check_sequence, workload as ada_workload
 from tests.test_build_gpu import host_copies
 from tests.test_decode_branches_gpu import run_case as run_branches
 from tests.test_decode_gpu import cache_case, check
-from tests.test_decode_ragged_gpu import run_ragged
+from tests.test_decode_ragged_gpu import HEAD, RANGES, SPLIT, run_ragged
 from tests.test_launch_rules import proxy_rules
 from tests.test_proxy_gpu import GRID, check_proxy, run_proxy
 from tests.test_graph_gpu import test_decode_step_graph_replays_match_eager as graph_replays
@@ -151,21 +151,25 @@ def test_split_decode_graph_replays():
     graph_replays(2, 2, 7, 900)
 
 
-@pytest.mark.parametrize("dtype,d,B,Hkv,G,C,longest", [
-    ("bf16", 128, 64, 4, 7, 1536, 1500),  # the per-head kernels' last capacity at 256 pairs
-    ("bf16", 64, 3, 4, 7, 2304, 700),     # and their longest capacity, split-K
-    ("bf16", 128, 3, 4, 7, 2305, 700),    # one slot more: fewer units than blocks, equal ranges
-    ("f32", 64, 2, 2, 2, 2400, 2390),     # equal ranges, a head over many one-unit blocks
-    ("bf16", 64, 65, 4, 4, 300, 290),     # 260 pairs: equal ranges
+@pytest.mark.parametrize("dtype,d,B,Hkv,G,C,longest,appends,kernels", [
+    ("bf16", 128, 64, 4, 7, 1536, 1500, True, HEAD),   # the per-head kernels' last capacity at 256 pairs
+    ("bf16", 64, 3, 4, 7, 2304, 700, True, SPLIT),     # and their longest capacity, split-K
+    ("bf16", 128, 3, 4, 7, 2305, 700, True, RANGES),   # one slot more: fewer units than blocks
+    ("f32", 64, 2, 2, 2, 2400, 2390, True, RANGES),    # a head over many one-unit blocks
+    ("bf16", 64, 65, 4, 4, 300, 290, True, RANGES),    # 260 pairs
+    ("bf16", 64, 65, 4, 1, 300, 290, False, RANGES),   # one query head per KV head, no append
+    ("bf16", 128, 24, 4, 4, 1281, 1200, True, RANGES),  # 96 pairs of small groups, a slot past their split-K line
+    ("f32", 64, 12, 4, 2, 1025, 1000, False, RANGES),  # 48 pairs of fp32 rows
+    ("bf16", 128, 40, 4, 2, 1793, 1700, False, RANGES),  # 160 pairs of up to two query heads
 ])
-def test_ragged_schedule_line(dtype, d, B, Hkv, G, C, longest):
+def test_ragged_schedule_line(dtype, d, B, Hkv, G, C, longest, appends, kernels):
     """Both sides of the line between the per-head kernels and the equal unit
-    ranges of ragged calls, with appends."""
+    ranges of ragged calls."""
     rng = np.random.default_rng(C)
     res = rng.choice([0, 16, 40, 64], size=(B, Hkv))
     main = rng.integers(1, longest - 64, size=(B, Hkv))
     main[0, 0] = longest - res[0, 0]
-    run_ragged(dtype, B, Hkv, G, d, C, 64, res, main, seed=C, compare_head=True)
+    run_ragged(dtype, B, Hkv, G, d, C, 64, res, main, seed=C, appends=appends, compare_head=True, kernels=kernels)
 
 
 @pytest.mark.parametrize("B", [8, 9])
