@@ -94,13 +94,29 @@ def test_branches_per_query_tau_and_gate_floor():
 
 
 def test_branches_whole_head_shape():
-    """B * Hkv = 256 pairs: reskv_decode_attn takes its one-block-per-head
-    kernel, the branches the split path; the shared merge agrees with it."""
+    """B * Hkv = 256 pairs: reskv_decode_attn and the branches both take one
+    block per head; the shared merge agrees with the single softmax."""
     B, Hkv, G = 64, 4, 4
     rng = np.random.default_rng(6)
     res = rng.choice([0, 64, 128], size=(B, Hkv))
     main = rng.integers(100, 384, size=(B, Hkv))
     run_case(6, B, G * Hkv, Hkv, 128, "bf16", 512, 128, res, main)
+    shape = rk.make_shape(B, G * Hkv, Hkv, 128, "bf16", 512, 128)
+    assert rk.decode_kernels(shape) == rk.decode_kernels(shape, "branches") == "decode_head"
+
+
+def test_branches_split_where_decode_takes_one_block():
+    """256 pairs of long caches: reskv_decode_attn takes one block per head, the
+    branches the split kernels; the shared merge agrees with it."""
+    B, Hkv, G, C = 64, 4, 1, 2400
+    rng = np.random.default_rng(8)
+    res = rng.choice([0, 64, 300], size=(B, Hkv))
+    main = rng.integers(1, 400, size=(B, Hkv))
+    main[2, 1] = C - res[2, 1]
+    shape = rk.make_shape(B, G * Hkv, Hkv, 64, "bf16", C, 300)
+    assert rk.decode_kernels(shape) == "decode_head"
+    assert rk.decode_kernels(shape, "branches") == "decode_split + decode_combine"
+    run_case(8, B, G * Hkv, Hkv, 64, "bf16", C, 300, res, main)
 
 
 @pytest.mark.parametrize("seed", list(range(12)))

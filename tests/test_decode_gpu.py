@@ -63,12 +63,14 @@ def test_decode_ragged_shapes(dtype, d, G):
     check(dtype, shape, q, kc, vc, logc, res, main)
 
 
-@pytest.mark.parametrize("dtype", ["f32", "bf16"])
-def test_decode_gate_variants(dtype):
-    B, Hkv, G, d, C, Rcap = 2, 2, 4, 128, 600, 128
+@pytest.mark.parametrize("dtype,C,kernels", [("f32", 600, "decode_split + decode_combine"), ("bf16", 600, "decode_head"),
+                                             ("bf16", 900, "decode_split + decode_combine")])
+def test_decode_gate_variants(dtype, C, kernels):
+    B, Hkv, G, d, Rcap = 2, 2, 4, 128, 128
     res = [[128, 40], [0, 100]]
     main = [[300, 472], [600, 20]]
     shape, q, kc, vc, logc = cache_case(3, B, Hkv * G, Hkv, d, dtype, C, Rcap, res, main)
+    assert rk.decode_kernels(shape) == kernels
     rng = np.random.default_rng(0)
     tau = rng.normal(0, 0.5, size=(B, Hkv * G)).astype(np.float32)
     check(dtype, shape, q, kc, vc, logc, res, main, tau=tau)
@@ -194,21 +196,26 @@ def test_append_then_decode(dtype):
     check(dtype, shape, q, kc2, vc2, logc, res, main2)
 
 
-@pytest.mark.parametrize("dtype,d,G,B,Hkv", [("bf16", 128, 4, 32, 8), ("f32", 64, 2, 64, 4), ("bf16", 64, 1, 16, 16),
-                                             ("bf16", 128, 4, 2, 2), ("f32", 128, 7, 2, 2), ("bf16", 128, 7, 64, 4),
-                                             ("bf16", 64, 16, 32, 8)])
-def test_decode_fused_append(dtype, d, G, B, Hkv):
+HEAD, SPLIT = "decode_head", "decode_split + decode_combine"
+
+
+@pytest.mark.parametrize("dtype,d,G,B,Hkv,C,kernels", [
+    ("bf16", 128, 4, 32, 8, 300, HEAD), ("f32", 64, 2, 64, 4, 300, HEAD), ("bf16", 64, 1, 16, 16, 300, HEAD),
+    ("bf16", 128, 4, 2, 2, 300, HEAD), ("f32", 128, 7, 2, 2, 300, SPLIT), ("bf16", 128, 7, 64, 4, 300, HEAD),
+    ("bf16", 64, 16, 32, 8, 300, HEAD), ("bf16", 128, 4, 2, 2, 900, SPLIT), ("bf16", 64, 1, 3, 2, 900, SPLIT),
+    ("f32", 64, 16, 2, 3, 900, SPLIT)])
+def test_decode_fused_append(dtype, d, G, B, Hkv, C, kernels):
     """reskv_decode_attn with this step's K/V: the token is appended as main
-    slot r + n (cache and main_len written) and attended in the same call.
-    B*Hkv >= 256 (bf16, or fp32 rows of 64) takes the one-block-per-head
-    kernel, for any group size up to 16; the others the split-K kernels;
-    full caches are left unchanged."""
+    slot r + n (cache and main_len written) and attended in the same call,
+    by the one-block-per-head kernel for any group size up to 16 and by the
+    split-K kernels; full caches are left unchanged."""
     rng = np.random.default_rng(11 + d + G)
-    C, Rcap = 300, 64
+    Rcap = 64
     res = rng.choice([0, 16, 64], size=(B, Hkv))
     main = rng.integers(1, C - 64, size=(B, Hkv))
     main[0, 0] = C - res[0, 0]  # full: no append
     shape, q, kc, vc, logc = cache_case(20 + d, B, G * Hkv, Hkv, d, dtype, C, Rcap, res, main)
+    assert rk.decode_kernels(shape) == kernels
     kn = rng.normal(size=(B, Hkv, d))
     vn = rng.normal(size=(B, Hkv, d))
     knd, vnd = to_dev(kn, dtype), to_dev(vn, dtype)

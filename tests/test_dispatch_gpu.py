@@ -125,13 +125,15 @@ def test_adakv_search_blocks(hkv, ctx, budget, alpha):
         check_sequence(wl, x, got, b, alpha, C, wl.window, replay_heads=())
 
 
-@pytest.mark.parametrize("dtype,d,B,Hkv,C", [
-    ("bf16", 128, 1, 2, 640), ("bf16", 128, 1, 2, 641),    # ten and eleven units of one head
-    ("f32", 64, 1, 2, 512), ("f32", 64, 1, 2, 513),
-    ("bf16", 64, 16, 4, 1024), ("bf16", 64, 16, 4, 1025),  # 64 pairs: two rounds of units, three
-    ("bf16", 64, 15, 4, 1024),                             # one pair count below
+@pytest.mark.parametrize("dtype,d,B,Hkv,C,kernels", [
+    ("bf16", 128, 1, 2, 640, HEAD), ("bf16", 128, 1, 2, 641, SPLIT),    # ten and eleven units of one head
+    ("f32", 64, 1, 2, 512, HEAD), ("f32", 64, 1, 2, 513, SPLIT),
+    ("bf16", 64, 16, 4, 1024, HEAD), ("bf16", 64, 16, 4, 1025, SPLIT),  # 64 pairs: two rounds of units, three
+    ("bf16", 64, 15, 4, 1024, SPLIT),                                   # one pair count below
+    ("f32", 64, 19, 4, 768, SPLIT), ("f32", 64, 20, 4, 768, HEAD),      # fp32 rows, two rounds
+    ("bf16", 128, 30, 4, 1280, HEAD), ("bf16", 128, 40, 4, 2305, SPLIT),  # three rounds; past the longest capacity
 ])
-def test_one_block_per_head_line(dtype, d, B, Hkv, C):
+def test_one_block_per_head_line(dtype, d, B, Hkv, C, kernels):
     """Both sides of the line between one block per head and split-K blocks,
     heads from nearly empty to full."""
     rng = np.random.default_rng(C)
@@ -140,6 +142,7 @@ def test_one_block_per_head_line(dtype, d, B, Hkv, C):
     main[0, 0] = C - res[0, 0]
     main[0, 1] = 1
     shape, q, kc, vc, logc = cache_case(C, B, 4 * Hkv, Hkv, d, dtype, C, 200, res, main)
+    assert rk.decode_kernels(shape) == kernels
     heads = [(0, 0), (0, 4)] + [(int(b), int(h)) for b, h in zip(rng.integers(0, B, 6), rng.integers(0, 4 * Hkv, 6))]
     check(dtype, shape, q, kc, vc, logc, res, main, heads=heads)
 

@@ -4,7 +4,7 @@
     r per head from {0, 16, 32, 64, 128}): every head built on the GPU and
     checked in full (scores, exact selection, Lloyd replay with the exported
     centres, entries), then all 128 decode queries decoded over the
-    GPU-built cache (split-K path) and every (query head, step) compared
+    GPU-built cache (one block per head) and every (query head, step) compared
     with the oracle, gate and log-sum-exps included;
   * batched decode layer (32 sequences x 8 KV heads, 32K context -> 2048
     slots, r per head from {0, 64, 128, 256, 512}): Lloyd replay on five

@@ -1,6 +1,6 @@
 """reskv_decode_attn_static (no workspace: split-K records in the library's
 static device scratch) against reskv_decode_attn with a caller workspace,
-through the C ABI: two calls in a row, the second on a smaller input, each
+through the C ABI: calls in a row, each on a smaller input than the one before,
 bit for bit equal to the workspace entry point on identical copies of the
 cache (outputs, debug outputs, appended rows and lengths)."""
 
@@ -60,9 +60,17 @@ def test_static_scratch_matches_workspace_two_calls():
     s1, d1 = case(3, 3, 14, 2, 128, 1100, 300, res1, main1)
     assert rk.reskv_decode_workspace_size(s1) > 0
     same(run(s1, d1, True), run(s1, d1, False))
-    # second call, smaller: fewer pairs, shorter caches, d = 64, G = 4
+    # second call, smaller, also through split-K records: fewer pairs, shorter
+    # caches, d = 64, G = 4, on the first call's stale records
     res2 = [[3, 40]]
-    main2 = [[60, 300]]
-    s2, d2 = case(4, 1, 8, 2, 64, 400, 64, res2, main2)
+    main2 = [[60, 800]]
+    s2, d2 = case(4, 1, 8, 2, 64, 900, 64, res2, main2)
+    assert rk.decode_kernels(s1) == rk.decode_kernels(s2) == "decode_split + decode_combine"
     assert rk.reskv_decode_workspace_size(s2) < rk.reskv_decode_workspace_size(s1)
     same(run(s2, d2, True), run(s2, d2, False))
+    # third call: one block per head, which writes no records
+    res3 = [[3, 40]]
+    main3 = [[60, 300]]
+    s3, d3 = case(4, 1, 8, 2, 64, 400, 64, res3, main3)
+    assert rk.decode_kernels(s3) == "decode_head"
+    same(run(s3, d3, True), run(s3, d3, False))
