@@ -126,7 +126,8 @@ def test_adakv_search_blocks(hkv, ctx, budget, alpha):
 
 
 @pytest.mark.parametrize("dtype,d,B,Hkv,C,kernels", [
-    ("bf16", 128, 1, 2, 640, HEAD), ("bf16", 128, 1, 2, 641, SPLIT),    # ten and eleven units of one head
+    ("bf16", 128, 1, 2, 640, SPLIT), ("bf16", 128, 1, 2, 641, SPLIT),   # ten and eleven units of one head
+    ("bf16", 128, 2, 4, 640, HEAD), ("bf16", 128, 2, 4, 641, SPLIT),    # 8 pairs
     ("f32", 64, 1, 2, 512, HEAD), ("f32", 64, 1, 2, 513, SPLIT),
     ("bf16", 64, 16, 4, 1024, HEAD), ("bf16", 64, 16, 4, 1025, SPLIT),  # 64 pairs: two rounds of units, three
     ("bf16", 64, 15, 4, 1024, SPLIT),                                   # one pair count below
@@ -212,9 +213,11 @@ def test_proxy_candidates_one_after_the_other(B, Hkv):
             np.testing.assert_array_equal(one[k], got[k])
 
 
-@pytest.mark.parametrize("dtype,d,G,C", [("bf16", 128, 7, 600), ("f32", 64, 4, 300), ("bf16", 64, 16, 8300)])
-def test_branches_paths(dtype, d, G, C):
-    """Two-branch decode with one block per head, and through records dealt to
-    several merge blocks; a head without residual entries and one whose
-    entries may all be empty."""
+@pytest.mark.parametrize("dtype,d,G,C,kernels", [("bf16", 128, 7, 500, HEAD), ("f32", 64, 4, 300, HEAD),
+                                                 ("bf16", 128, 7, 600, SPLIT), ("bf16", 64, 16, 8300, SPLIT)])
+def test_branches_paths(dtype, d, G, C, kernels):
+    """Two-branch decode with one block per head, and through records (on the
+    longest caches dealt to several merge blocks); a head without residual
+    entries and one whose entries may all be empty."""
+    assert rk.decode_kernels(rk.make_shape(1, 3 * G, 3, d, dtype, C, 130), "branches") == kernels
     run_branches(C, 1, 3 * G, 3, d, dtype, C, 130, [[0, 130, 1]], [[C - 4, 160, 1]])
