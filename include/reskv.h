@@ -322,7 +322,10 @@ size_t reskv_build_proxy_workspace_size(const reskv_shape_t* shape,
  * the same HBM channels: at 256 heads of 2048 live slots, d = 128, bf16, a
  * call took 48-51 us at most capacities between 2056 and 2552 slots and up
  * to 57 us at the worst one measured (2064). The kernels accept any C; a
- * caller tuning for speed can time a few capacities at its own shape.
+ * caller tuning for speed can time a few capacities at its own shape. Which
+ * kernels serve a call follows from its sizes alone, chosen for heads of like
+ * lengths; where few heads are much longer than the rest,
+ * reskv_decode_attn_ragged is the entry to use.
  */
 reskv_status_t reskv_decode_attn(const reskv_shape_t* shape,
                                  const reskv_gate_t* gate,
@@ -398,10 +401,10 @@ size_t reskv_decode_ragged_workspace_size(const reskv_shape_t* shape);
  *
  *   stream          must belong to the calling thread's current device (the
  *                   scratch of that device is used)
- * Errors: RESKV_ERR_WORKSPACE when the shape takes the split-K path (fewer
- * than 256 (sequence, KV head) pairs, or fp32 rows of 128) and its records
- * need more than 16 MiB (reskv_decode_workspace_size(shape) > 16 MiB);
- * otherwise as for reskv_decode_attn. All calls on one GPU share its scratch: calls that
+ * Errors: RESKV_ERR_WORKSPACE when the shape has fewer than 256 (sequence, KV
+ * head) pairs, or fp32 rows of 128, and reskv_decode_workspace_size(shape) >
+ * 16 MiB, whichever kernels its sizes take (the limit is that of the split-K
+ * path); otherwise as for reskv_decode_attn. All calls on one GPU share its scratch: calls that
  * overlap in time on one GPU (on different streams) race and must not be
  * issued; calls ordered on one stream are safe.
  */
