@@ -1230,26 +1230,8 @@ __device__ void prep_center(const BuildArgs& a, size_t ci, const float* mu, doub
 
 // ------------------------------------------------------------------ Lloyd
 
-// Centre fragments for one 16-centre tile: A operand rows.
-template <typename T, int D>
-struct CenterTile;
-
-template <int D>
-struct CenterTile<uint16_t, D> {   // split bf16: mu ~ hi + lo
-  Frag<uint16_t, D> hi, lo;
-};
-template <int D>
-struct CenterTile<float, D> {
-  Frag<float, D> f;
-};
-
-// One MFMA k-step of a centre tile against one token tile (bf16: 8 elements,
-// fp32: 1 element per lane).
-template <int D>
-__device__ __forceinline__ f32x4_t mma_step(const Frag<uint16_t, D>& c, const Frag<uint16_t, D>& t, int k,
-                                            f32x4_t acc) {
-  return __builtin_amdgcn_mfma_f32_16x16x32_bf16(as_bf16x8(c.w[k]), as_bf16x8(t.w[k]), acc, 0, 0, 0);
-}
+// One MFMA k-step of an fp32 centre tile against one token tile, 1 element per
+// lane.
 template <int D>
 __device__ __forceinline__ f32x4_t mma_step(const Frag<float, D>& c, const Frag<float, D>& t, int k, f32x4_t acc) {
   const float4 x = c.w[k >> 2], y = t.w[k >> 2];
