@@ -114,7 +114,8 @@ struct BuildArgs {
   int32_t* nitem;      // [BH]
   int32_t* parrive;    // [BH][Rcap] pieces of a split group that have left their sums
   double* part;        // [BH][NPART][2][D] key and value sums of split groups' pieces
-  int32_t* sel_hist;   // [BH][kSelHist] selection pass histograms (zeroed by lse_final and, for the next candidate, gather_init)
+  int32_t* sel_hist;   // [BH][kSelHist] selection pass histograms (zeroed by lse_final and, for the next candidate, gather_init), or NULL
+  bool more;           // another candidate's selection follows (gather_init zeroes sel_hist)
   int32_t* ada_hist;   // [BH][kAdaHist] cross-head search histograms (zeroed by pool_scores), or NULL
   uint32_t* ada_state; // [2][B][kAdaState] per sequence: prefix, then the heads' tokens above its range
   uint32_t* sel_state; // [BH][2][4] thresholds' prefixes and remaining ranks after the first and second pass
@@ -315,8 +316,9 @@ __global__ __launch_bounds__(256 * kRQ, (sizeof(T) == 4 ? 2 : kRQ > 1 ? 4 : 3)) 
   }
 }
 
-// The head's selection histograms start from zero.
+// The head's selection histograms start from zero (where there are any).
 __device__ __forceinline__ void zero_sel_hist(const BuildArgs& a, int bh, int i, int step) {
+  if (a.sel_hist == nullptr) return;
   for (int4* h = reinterpret_cast<int4*>(a.sel_hist + (size_t)bh * kSelHist); i < kSelHist / 4; i += step)
     h[i] = make_int4(0, 0, 0, 0);
 }
@@ -1170,7 +1172,7 @@ __global__ __launch_bounds__(kThreads) void gather_init(BuildArgs a) {
     reinterpret_cast<uint4*>(kc + (size_t)dst * D)[ck] = kv;
     reinterpret_cast<uint4*>(vc + (size_t)dst * D)[ck] = vv;
   }
-  zero_sel_hist(a, bh, blockIdx.x * kThreads + threadIdx.x, gridDim.x * kThreads);
+  if (a.more) zero_sel_hist(a, bh, blockIdx.x * kThreads + threadIdx.x, gridDim.x * kThreads);
   // every log-count starts empty
   for (int j = blockIdx.x * kThreads + threadIdx.x; j < a.Rcap; j += gridDim.x * kThreads)
     a.logc[(size_t)bh * a.Rcap + j] = kNegInf;
@@ -1917,7 +1919,7 @@ BuildArgs make_args(const BuildPlan& pl, const void* k, const void* v, const voi
   a.parrive = reinterpret_cast<int32_t*>(ws + pl.off_parrive);
   a.part = reinterpret_cast<double*>(ws + pl.off_part);
   a.lpiece = pl.lpiece; a.NIT = pl.NIT; a.NPART = pl.NPART;
-  a.sel_hist = reinterpret_cast<int32_t*>(ws + pl.off_selh);
+  a.sel_hist = pl.sel_multi ? reinterpret_cast<int32_t*>(ws + pl.off_selh) : nullptr;
   a.sel_state = reinterpret_cast<uint32_t*>(ws + pl.off_sels);
   a.sel_cnt = pl.count_sel ? reinterpret_cast<uint4*>(ws + pl.off_selc) : nullptr;
   a.NC = pl.NC; a.SBH = pl.B * pl.Hkv;
@@ -1977,7 +1979,7 @@ hipError_t launch_candidate_typed(const BuildPlan& pl, const BuildArgs& a, hipSt
     RESKV_CHECK();
   }
   constexpr int kPoolChunk = kPoolThreads * kPoolPer;
-  if (pl.NSEL == 1 && !alloc_meta) {
+  if (!pl.sel_multi) {
     hipLaunchKernelGGL(select_one, bhg, dim3(kSelThreads), 0, st, a); RESKV_CHECK();
   } else {
     hipLaunchKernelGGL(pool_scores, grid((pl.S + kPoolChunk - 1) / kPoolChunk), dim3(kPoolThreads), 0, st, a);
@@ -2095,6 +2097,7 @@ bool layout_build_plan(BuildPlan* plan) {
   if (pl.NBLK < 1) pl.NBLK = 1;
   pl.NSEL = (pl.max_s + kSelChunk - 1) / kSelChunk;
   if (pl.NSEL < 1) pl.NSEL = 1;
+  pl.sel_multi = pl.cross_head || pl.NSEL > 1;
   pl.count_sel = pl.NSEL > kSelUncounted;
   const int nb64 = (pl.max_E + 63) / 64;
   pl.one_sort = nb64 <= kSortBatches * (kSortThreads / 64) && pl.max_reff <= kSortThreads &&
@@ -2103,8 +2106,9 @@ bool layout_build_plan(BuildPlan* plan) {
   // kPieceMin of 1024 (short chains where few blocks are in flight), else 1024
   pl.lpiece = CH * (size_t)((pl.max_E + 1023) / 1024) < kPieceMin ? 8 : 10;
   while (pl.max_E >> pl.lpiece > 16384) ++pl.lpiece;  // piece counts stay below 2^16 (lloyd_offsets packs them)
-  pl.NIT = pl.max_reff + (pl.max_E >> pl.lpiece);  // sum over groups of max(1, ceil(count / piece))
-  pl.NPART = 2 * (pl.max_E >> pl.lpiece);        // groups above one piece: ceil(c / piece) <= 2 c / piece
+  const int pieces = pl.max_reff > 0 ? pl.max_E >> pl.lpiece : 0;
+  pl.NIT = pl.max_reff + pieces;  // sum over groups of max(1, ceil(count / piece))
+  pl.NPART = 2 * pieces;        // groups above one piece: ceil(c / piece) <= 2 c / piece
   size_t off = 0;
   auto take = [&](size_t bytes) { const size_t o = off; off = align_up(off + bytes, 256); return o; };
   pl.off_meta = take(BH * sizeof(HeadMeta));
@@ -2125,7 +2129,7 @@ bool layout_build_plan(BuildPlan* plan) {
   pl.off_nitem = take(CH * sizeof(int32_t));
   pl.off_parrive = take(CH * pl.Rcap * sizeof(int32_t));
   pl.off_part = take(CH * pl.NPART * 2 * pl.D * sizeof(double));
-  pl.off_selh = take(CH * kSelHist * sizeof(int32_t));
+  pl.off_selh = take(pl.sel_multi ? CH * kSelHist * sizeof(int32_t) : 0);
   pl.off_sels = take(CH * 8 * sizeof(uint32_t));
   pl.off_selc = take(pl.count_sel ? CH * pl.NSEL * sizeof(uint4) : 0);
   pl.bytes = off;
@@ -2136,6 +2140,7 @@ bool make_build_plan_adakv(const reskv_shape_t& s, const reskv_build_params_t& p
                            int decode_reserve, const int32_t* seq_len, const int32_t* budget,
                            const int32_t* res_count, BuildPlan* plan) {
   init_build_plan(s, p, plan);
+  plan->cross_head = true;
   std::vector<HeadMeta> hm;
   head_meta(*plan, seq_len, budget, res_count, p.recent_window, hm);
   const int cslots = s.slot_cap - decode_reserve;
@@ -2221,9 +2226,10 @@ hipError_t launch_build_adakv(const reskv_shape_t& s, const reskv_build_params_t
 
 hipError_t launch_build_candidate(const BuildPlan& pl, const void* k, const void* v, const HeadMeta* meta,
                                   const BuildOut& out, float* dbg_scores, int32_t* dbg_assign, float* dbg_centers,
-                                  void* workspace, hipStream_t stream) {
+                                  bool more, void* workspace, hipStream_t stream) {
   BuildArgs a = make_args(pl, k, v, nullptr, meta, out, dbg_scores, dbg_assign, dbg_centers, workspace);
   a.B = pl.B * pl.NC;
+  a.more = more;
   const bool bf = pl.dtype == RESKV_BF16;
   if (pl.D == 128) return bf ? launch_candidate_typed<uint16_t, 128>(pl, a, stream) : launch_candidate_typed<float, 128>(pl, a, stream);
   if (pl.D == 64) return bf ? launch_candidate_typed<uint16_t, 64>(pl, a, stream) : launch_candidate_typed<float, 64>(pl, a, stream);
@@ -2243,7 +2249,7 @@ hipError_t launch_build(const reskv_shape_t& s, const reskv_build_params_t& p, c
   e = launch_build_scores(pl, k, q_obs, meta, workspace, stream);
   if (e != hipSuccess) return e;
   const BuildOut out{kc, vc, logc, main_idx, res_len, main_len};
-  return launch_build_candidate(pl, k, v, meta, out, dbg_scores, dbg_assign, dbg_centers, workspace, stream);
+  return launch_build_candidate(pl, k, v, meta, out, dbg_scores, dbg_assign, dbg_centers, false, workspace, stream);
 }
 
 }  // namespace reskv

@@ -92,6 +92,7 @@ struct BuildPlan {
   int wr;     // leading window rows per query head that score
   int pool_half;  // score pooling taps on each side
   int R;      // scoring rows per kv head, G * wr
+  bool cross_head;  // cross-head allocation between pooling and selection
   int NC;     // candidate counts built in one batch (scratch and grids for B * NC sequences), 1 but for the proxy
   int LG;     // 256-key groups per lse block
   int NCH;    // lse key chunks (256 * LG keys) of the longest sequence
@@ -100,6 +101,7 @@ struct BuildPlan {
   int NSC;    // score-pass key chunks of the longest sequence
   int NBLK;   // 256-token blocks of the largest evicted set
   int NSEL;   // selection blocks (8192 scores each) of the longest sequence
+  bool sel_multi;  // selection in several launches (long lists, cross-head allocation), with histograms in the workspace
   bool count_sel;  // selection blocks leave their counts for the placement (long lists)
   int max_s, max_main, max_reff, max_E;
   bool one_sort;  // one block sorts a head's evicted tokens (short lists)
@@ -147,10 +149,11 @@ hipError_t upload_meta(const BuildPlan& pl, const int32_t* seq_len, const int32_
 hipError_t launch_build_scores(const BuildPlan& pl, const void* k, const void* q_obs, const HeadMeta* meta,
                                void* workspace, hipStream_t stream);
 // Pooling, selection, gather and Lloyd rounds from the workspace's raw
-// scores, for the counts of `meta` (pl.NC sets of them), writing `out`.
+// scores, for the counts of `meta` (pl.NC sets of them), writing `out`. more:
+// another candidate follows on the same scores.
 hipError_t launch_build_candidate(const BuildPlan& pl, const void* k, const void* v, const HeadMeta* meta,
                                   const BuildOut& out, float* dbg_scores, int32_t* dbg_assign, float* dbg_centers,
-                                  void* workspace, hipStream_t stream);
+                                  bool more, void* workspace, hipStream_t stream);
 
 // AdaKV cross-head allocation (App. B.2.2 compared methods): at most this
 // many KV heads per sequence share their budgets.

@@ -139,3 +139,13 @@ def test_proxy_candidates_in_one_batch(batch, ctx, want):
     assert rules.batched == want
     size = rk.reskv_build_proxy_workspace_size(shape, params, proxy, [ctx] * batch, [256] * batch)
     assert size > rules.least_bytes if want > 1 else size == rules.least_bytes
+
+
+def test_build_workspace_holds_what_is_read():
+    """No partial sums without residual entries, no selection histograms where one block selects."""
+    def size(s, r):
+        return rk.reskv_build_workspace_size(rk.make_shape(1, 32, 8, 128, "bf16", 512, 256),
+                                             rk.BuildParams(s, 32, 32, 4, 0, 0), [s], [512], [r] * 8)
+    sums = 8 * 2 * (131072 // 256) * 2 * 128 * 8  # heads x slots x (keys, values) x d x fp64, about
+    assert size(131072, 256) - size(131072, 0) > 0.9 * sums
+    assert size(8193, 0) - size(8192, 0) > 8 * 32768
