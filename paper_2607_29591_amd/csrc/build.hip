@@ -3,9 +3,9 @@
 //
 // Per (b, kv head), in launch order:
 //   lse_partial    MFMA logits of the G*w observation-window rows against a
-//                  256-key chunk (each wave owns 64 keys and runs over all
-//                  rows); per row the max and sum of exp (base 2) over the
-//                  keys it can see (causal inside the window)
+//                  chunk of 256-key groups (each wave owns 64 keys of a group
+//                  and runs over its rows); per row the max and sum of exp
+//                  (base 2) over the keys it can see (causal in the window)
 //   lse_final      merges the chunk partials into one log-sum-exp per row
 //   score_accum    recomputes the logits; raw[p] = sum over rows of the
 //                  normalised weight of key p, for the scored positions
@@ -17,10 +17,12 @@
 //                  rewrites each head's sizes before the selection
 //   select_hist x2 radix select (11, 11 and 10 bits of the fp32 bit pattern)
 //  [select_count]  of the k_top-th and (k_top + r')-th largest score over blocks
-//   select_write   of 8192 scores (counted by block where the list is long); ties at a threshold go to the lower
-//                  position. Stable compaction writes main_idx (top-k, then
-//                  the protected window), the evicted list E and the Lloyd
-//                  seeds, all ascending
+//   select_write   of 8192 scores, counted per block first where the list is
+//                  long; ties at a threshold go to the lower position. Stable
+//                  compaction writes main_idx (top-k, then the protected
+//                  window), the evicted list E and the Lloyd seeds, all
+//                  ascending
+//  [select_one]    pooling and selection in one launch on short lists
 //   gather_init    copies the main rows into slots [r, r + m), clears the
 //                  residual slots, seeds the Lloyd centres with K[seed] (fp32,
 //                  bf16 hi + lo and the squared norm)
@@ -1790,7 +1792,11 @@ __global__ __launch_bounds__(kThreads, (kKV && sizeof(T) == 2 ? 4 : sizeof(T) ==
     // Partial sums and arrivals go through agent-scope accesses (the pieces
     // run on several XCDs, whose L2s do not see each other's plain stores);
     // every store has completed before the block counts itself in, so the
-    // block that counts last reads complete sums.
+    // block that counts last reads complete sums. That order rests on the
+    // wait and on stores that write through and loads that bypass, not on
+    // the language's release and acquire: at agent scope those write back and
+    // invalidate the whole L2 (a split-K merge ordered that way ran 7 times
+    // slower).
     const int np = (total + (1 << a.lpiece) - 1) >> a.lpiece;
     unsigned long long* part = reinterpret_cast<unsigned long long*>(a.part) + (size_t)bh * a.NPART * 2 * D;
     auto slot = [&](int p, int q) { return &part[((size_t)p * 2 + q) * D + tid]; };
@@ -2103,7 +2109,11 @@ bool layout_build_plan(BuildPlan* plan) {
   pl.one_sort = nb64 <= kSortBatches * (kSortThreads / 64) && pl.max_reff <= kSortThreads &&
                 (long long)nb64 * pl.max_reff <= kSortTable;
   // update pieces of 256 members while the whole construction has fewer than
-  // kPieceMin of 1024 (short chains where few blocks are in flight), else 1024
+  // kPieceMin of 1024 (short chains where few blocks are in flight), else 1024.
+  // Whole constructions of 128K tokens, pieces of 1024 / 256: one head, 256
+  // groups of like size 347 / 336 us, one of them large 358 / 334; 8 heads 999 / 989
+  // and 1010 / 975; 30 heads 3205 / 3252. A group that holds all tokens has 512
+  // pieces to add: 8 heads in one group 830 / 1073 (one block per group: 6416).
   pl.lpiece = CH * (size_t)((pl.max_E + 1023) / 1024) < kPieceMin ? 8 : 10;
   while (pl.max_E >> pl.lpiece > 16384) ++pl.lpiece;  // piece counts stay below 2^16 (lloyd_offsets packs them)
   const int pieces = pl.max_reff > 0 ? pl.max_E >> pl.lpiece : 0;
