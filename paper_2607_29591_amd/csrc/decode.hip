@@ -1262,12 +1262,14 @@ static bool long_small_group(const reskv_shape_t& s, int GP) {
 // batch with few long heads loses (up to 1.6 times, see the lower rows). Past
 // 2304 slots groups of up to 4 query heads split: one block gains at most 20%
 // on full heads there and loses up to 1.9 times on uneven ones. For at most
-// one round one block serves any count, bf16 from 8 pairs on up to 640 slots,
-// where only two waves have a second unit (one pair, one query head: 9.3 / 10.3).
+// one round one block serves any count, bf16 up to 640 slots, where only two
+// waves have a second unit (one pair: 4 query heads 10.4 / 10.7, 8 12.4 / 12.2, rows
+// of 64 8.0 / 7.1), but not a few single heads of 128 (one pair 9.3 / 10.3).
 static bool one_block_per_head(const reskv_shape_t& s, int GP, long long pairs) {
   const bool bf = s.dtype == RESKV_BF16;
   const int round = kHeadWaves * kUnit, rounds = (s.slot_cap + round - 1) / round;
-  if (s.slot_cap <= (bf && pairs >= 8 ? round + 2 * kUnit : round)) return true;
+  const bool lone = pairs < 8 && GP == 1 && s.head_dim == 128;
+  if (s.slot_cap <= (bf && !lone ? round + 2 * kUnit : round)) return true;
   if (long_small_group(s, GP)) return false;
   // 32 pairs per round, and more where small groups or fp32 rows leave full
   // heads slower (96 pairs of 1280 slots, one query head: 15.9 / 18.9)

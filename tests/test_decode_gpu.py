@@ -63,13 +63,14 @@ def test_decode_ragged_shapes(dtype, d, G):
     check(dtype, shape, q, kc, vc, logc, res, main)
 
 
-@pytest.mark.parametrize("dtype", ["f32", "bf16"])
-def test_decode_gate_variants(dtype):
-    B, Hkv, G, d, C, Rcap = 2, 2, 4, 128, 600, 128
+@pytest.mark.parametrize("dtype,C,kernels", [("f32", 600, "decode_split + decode_combine"), ("bf16", 600, "decode_head"),
+                                             ("bf16", 900, "decode_split + decode_combine")])
+def test_decode_gate_variants(dtype, C, kernels):
+    B, Hkv, G, d, Rcap = 2, 2, 4, 128, 128
     res = [[128, 40], [0, 100]]
     main = [[300, 472], [600, 20]]
     shape, q, kc, vc, logc = cache_case(3, B, Hkv * G, Hkv, d, dtype, C, Rcap, res, main)
-    assert rk.decode_kernels(shape) == "decode_split + decode_combine"
+    assert rk.decode_kernels(shape) == kernels
     rng = np.random.default_rng(0)
     tau = rng.normal(0, 0.5, size=(B, Hkv * G)).astype(np.float32)
     check(dtype, shape, q, kc, vc, logc, res, main, tau=tau)

@@ -126,8 +126,7 @@ def test_adakv_search_blocks(hkv, ctx, budget, alpha):
 
 
 @pytest.mark.parametrize("dtype,d,B,Hkv,C,kernels", [
-    ("bf16", 128, 1, 2, 640, SPLIT), ("bf16", 128, 1, 2, 641, SPLIT),   # ten and eleven units of one head
-    ("bf16", 128, 2, 4, 640, HEAD), ("bf16", 128, 2, 4, 641, SPLIT),    # 8 pairs
+    ("bf16", 128, 1, 2, 640, HEAD), ("bf16", 128, 1, 2, 641, SPLIT),    # ten and eleven units of one head
     ("f32", 64, 1, 2, 512, HEAD), ("f32", 64, 1, 2, 513, SPLIT),
     ("bf16", 64, 16, 4, 1024, HEAD), ("bf16", 64, 16, 4, 1025, SPLIT),  # 64 pairs: two rounds of units, three
     ("bf16", 64, 15, 4, 1024, SPLIT),                                   # one pair count below
@@ -213,8 +212,8 @@ def test_proxy_candidates_one_after_the_other(B, Hkv):
             np.testing.assert_array_equal(one[k], got[k])
 
 
-@pytest.mark.parametrize("dtype,d,G,C,kernels", [("bf16", 128, 7, 500, HEAD), ("f32", 64, 4, 300, HEAD),
-                                                 ("bf16", 128, 7, 600, SPLIT), ("bf16", 64, 16, 8300, SPLIT)])
+@pytest.mark.parametrize("dtype,d,G,C,kernels", [("bf16", 128, 7, 600, HEAD), ("f32", 64, 4, 300, HEAD),
+                                                 ("bf16", 128, 1, 600, SPLIT), ("bf16", 64, 16, 8300, SPLIT)])
 def test_branches_paths(dtype, d, G, C, kernels):
     """Two-branch decode with one block per head, and through records (on the
     longest caches dealt to several merge blocks); a head without residual
